@@ -56,14 +56,24 @@ def iteration_hbm(kernels, alg_bytes_per_point, pts):
 #   rowinv : read spectrum, read P, write P, write P~
 #   upd    : read P~, read U_n (mixed: e_n and the FP32 copy of U), write U_{n+1}
 #   rowfwd : read U_{n+1} and U^k (mixed: e, U_b, r), write the spectrum
+#   rows   : rowinv, upd and rowfwd in one launch: read the spectrum, U_n, U^k and Q,
+#            write U_{n+1}, Q and the spectrum (mixed: e, U_b, r and Q read)
 BYTES_PER_POINT = {
-    "fp64": {"cols": 16, "rowinv": 32, "upd": 24, "rowfwd": 24, "yfwd": 16, "zsym": 16, "yinv": 16},
-    "mixed": {"cols": 8, "rowinv": 16, "upd": 16, "rowfwd": 16, "yfwd": 8, "zsym": 8, "yinv": 8},
+    "fp64": {"cols": 16, "rows": 56, "rowinv": 32, "upd": 24, "rowfwd": 24, "yfwd": 16, "zsym": 16, "yinv": 16},
+    "mixed": {"cols": 8, "rows": 32, "rowinv": 16, "upd": 16, "rowfwd": 16, "yfwd": 8, "zsym": 8, "yinv": 8},
 }
 
 
 def log(*a):
     print(*a, file=sys.stderr, flush=True)
+
+
+def launch_ms(ms):
+    """profile_iteration's durations by launch: "rows" where one launch makes the three
+    row-parallel steps."""
+    if ms.get("upd") == 0.0:
+        return {"cols": ms["cols"], "rows": ms["rowinv"]}
+    return ms
 
 
 def counted_traffic(prec, kernel, logn):
@@ -84,7 +94,7 @@ def counted_traffic(prec, kernel, logn):
     t = "float" if prec == "mixed" else "double"
     kind = {"mixed": 5, "fp64": 1}[prec]   # 5: the mixed row pass (its inner launches)
     names = {"cols": "k_cols<%s,%d,0,1,%d>" % (t, logn, kind), "rowinv": "k_rowinv<%s,%d,0,1>" % (t, logn),
-             "upd": "k_upd<%s,%d,0,0,%d>" % (t, logn, 1 if prec == "mixed" else 0),
+             "rows": "k_rows<%s,%d,0,0>" % (t, logn), "upd": "k_upd<%s,%d,0,0,%d>" % (t, logn, 1 if prec == "mixed" else 0),
              "rowfwd": "k_row_forward<%s,%d,0,0,%d>" % (t, logn, kind)}
     k = d["kernels"].get(names.get(kernel, ""))
     return None if k is None else k["hbm_bytes"]
@@ -257,7 +267,7 @@ def config_leg(ctx, rd, torch, wl, name, precs, steps=None, oracle=True):
             # iteration must move per grid point, times the number of species
             p = rd.problem_from_config(cfg)
             o = rd.make_opts(tol=cfg["tol"], tau_u=cfg["tau"], tau_p=cfg["tau"], omega=cfg["omega"], precision=prec)
-            ms = ctx.profile_iteration(u0, cfg["ht"], p, o, reps=20)
+            ms = launch_ms(ctx.profile_iteration(u0, cfg["ht"], p, o, reps=20))
             it_ms = sum(ms.values())
             b = ALG_BYTES[prec] * ncomp * cfg["N"] ** 2
             out[prec]["iteration"] = dict(kernels_us={k: round(v * 1e3, 2) for k, v in ms.items()},
@@ -378,7 +388,7 @@ def adaptive_leg(ctx, rd, torch, cfg, u0):
 def kernel_table(ctx, rd, cfg, u0, prec, pts, reps=20):
     p = rd.problem_from_config(cfg)
     o = rd.make_opts(tol=cfg["tol"], tau_u=cfg["tau"], tau_p=cfg["tau"], precision=prec)
-    ms = ctx.profile_iteration(u0, cfg["ht"], p, o, reps=reps)
+    ms = launch_ms(ctx.profile_iteration(u0, cfg["ht"], p, o, reps=reps))
     return {k: dict(ms=t, bytes=BYTES_PER_POINT[prec][k] * pts,
                     gbs=BYTES_PER_POINT[prec][k] * pts / (t * 1e-3) / 1e9) for k, t in ms.items()}
 
@@ -527,7 +537,7 @@ def main():
     p = rd.problem_from_config(cfg)
     for prec in ("fp64", "mixed"):
         o = rd.make_opts(tol=cfg["tol"], tau_u=cfg["tau"], tau_p=cfg["tau"], precision=prec)
-        ms = ctx.profile_iteration(u0, cfg["ht"], p, o, reps=args.reps)
+        ms = launch_ms(ctx.profile_iteration(u0, cfg["ht"], p, o, reps=args.reps))
         kernels[prec] = {}
         for k, t in ms.items():
             nbytes = BYTES_PER_POINT[prec][k] * N * N

@@ -60,34 +60,39 @@ template <typename T, int R, int DIR> __device__ __forceinline__ void dftR(cplx<
     else dft2<T, DIR>(v);
 }
 
-// Radix and butterfly count of pass q of a length-2^LOGN transform: radix 16
-// while at least 4 bits remain, then one pass of radix 8, 4 or 2.
-template <int LOGN> constexpr int npasses16() { return (LOGN + 3) / 4; }
-template <int LOGN> constexpr int pass_radix(int q) { return LOGN - 4 * q >= 4 ? 16 : (1 << (LOGN - 4 * q)); }
+// Values per thread of a transform, V: 16 where the chip is full of transforms, 8
+// where it is not (short serial chains; see row_values).  Radix of pass q of a
+// length-2^LOGN transform: radix V while that many bits remain, then one pass of
+// what is left.
+template <int V> constexpr int logv() { return V == 16 ? 4 : V == 8 ? 3 : 2; }
+template <int LOGN, int V = 16> constexpr int npasses16() { return (LOGN + logv<V>() - 1) / logv<V>(); }
+template <int LOGN, int V = 16> constexpr int pass_radix(int q) {
+    return LOGN - logv<V>() * q >= logv<V>() ? V : (1 << (LOGN - logv<V>() * q));
+}
 
 // The twiddles of one thread for every pass after the first: for butterfly b of
 // pass q, the gathered powers W^{k}, W^{2k}, W^{4k}, W^{8k} (forward sign) of
 // W = exp(-2 pi i / (NS R)), k = j mod NS.  They depend only on the thread's
 // index in its transform team, so a kernel loads them once, at its start, and
 // every transform (forward and inverse) of the kernel reuses them.
-template <typename T, int LOGN> struct Tw16 {
-    cplx<T> p[npasses16<LOGN>() > 1 ? npasses16<LOGN>() - 1 : 1][8][4];
+template <typename T, int LOGN, int V = 16> struct Tw16 {
+    cplx<T> p[npasses16<LOGN, V>() > 1 ? npasses16<LOGN, V>() - 1 : 1][V / 2][logv<V>()];
 };
 
-template <typename T, int LOGN>
-__device__ __forceinline__ void load_tw16(Tw16<T, LOGN> &w, const cplx<T> *__restrict__ tw, int t) {
+template <typename T, int LOGN, int V>
+__device__ __forceinline__ void load_tw16(Tw16<T, LOGN, V> &w, const cplx<T> *__restrict__ tw, int t) {
     constexpr int N = 1 << LOGN;
-    constexpr int TPF = N / 16;
+    constexpr int TPF = N / V;
     const auto tg = gp(tw);
 #pragma unroll
-    for (int q = 1; q < npasses16<LOGN>(); ++q) {
-        const int R = pass_radix<LOGN>(q), NS = 1 << (4 * q);
+    for (int q = 1; q < npasses16<LOGN, V>(); ++q) {
+        const int R = pass_radix<LOGN, V>(q), NS = 1 << (logv<V>() * q);
         const int TWSTEP = N / (NS * R);
 #pragma unroll
-        for (int b = 0; b < 16 / R; ++b) {
+        for (int b = 0; b < V / R; ++b) {
             const int k = (t + b * TPF) & (NS - 1);
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
+            for (int e = 0; e < logv<V>(); ++e)
                 if ((1 << e) < R) {
                     const int i = ((k * TWSTEP) << e) & (N - 1);
                     w.p[q - 1][b][e] = {tg[i].re, tg[i].im};
@@ -96,33 +101,33 @@ __device__ __forceinline__ void load_tw16(Tw16<T, LOGN> &w, const cplx<T> *__res
     }
 }
 
-template <typename T, int LOGN>
-__device__ __forceinline__ void load_tw16(Tw16<T, LOGN> &w, const cplx<T> *__restrict__ tw) {
-    load_tw16<T, LOGN>(w, tw, (int)(threadIdx.x % ((1 << LOGN) / 16)));
+template <typename T, int LOGN, int V>
+__device__ __forceinline__ void load_tw16(Tw16<T, LOGN, V> &w, const cplx<T> *__restrict__ tw) {
+    load_tw16<T, LOGN, V>(w, tw, (int)(threadIdx.x % ((1 << LOGN) / V)));
 }
 
 // One Stockham pass of radix R (NS = product of earlier radices).  Butterfly j
 // reads x[j + r N/R], twiddles input r by W_{NS R}^{r k} (k = j mod NS), applies
 // DFT_R, and writes output q to ((j - k) R + k) + q NS.  pw: the thread's
 // gathered powers for this pass (unused when NS = 1).  Thread t of a transform
-// runs butterflies j = t + b N/16, b < 16/R.
+// runs butterflies j = t + b N/V, b < V/R.
 //
 // pass_in: the reads, twiddles and butterflies of the thread (outputs in v).
-template <typename T, int LOGN, int R, int NS, int DIR>
-__device__ __forceinline__ void pass_in(const cplx<T> *x, int t, const cplx<T> (*pw)[4], cplx<T> (*v)[R]) {
+template <typename T, int LOGN, int R, int NS, int DIR, int V = 16>
+__device__ __forceinline__ void pass_in(const cplx<T> *x, int t, const cplx<T> (*pw)[logv<V>()], cplx<T> (*v)[R]) {
     constexpr int N = 1 << LOGN;
-    constexpr int TPF = N / 16;      // threads per transform
+    constexpr int TPF = N / V;       // threads per transform
     constexpr int NB = N / R;        // butterflies
-    constexpr int BPT = 16 / R;      // butterflies per thread
+    constexpr int BPT = V / R;       // butterflies per thread
 #pragma unroll
     for (int b = 0; b < BPT; ++b) {
         const int j = t + b * TPF;
 #pragma unroll
         for (int r = 0; r < R; ++r) v[b][r] = x[lds_pad(j + r * NB)];
         if constexpr (NS > 1) {
-            cplx<T> p[4];
+            cplx<T> p[logv<V>()];
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
+            for (int e = 0; e < logv<V>(); ++e)
                 if ((1 << e) < R) {
                     p[e] = pw[b][e];
                     if constexpr (DIR > 0) p[e].im = -p[e].im;
@@ -132,7 +137,7 @@ __device__ __forceinline__ void pass_in(const cplx<T> *x, int t, const cplx<T> (
                 cplx<T> w = {(T)1, (T)0};
                 bool first = true;
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
+                for (int e = 0; e < logv<V>(); ++e)
                     if (r & (1 << e)) {
                         w = first ? p[e] : cmul(w, p[e]);
                         first = false;
@@ -145,11 +150,11 @@ __device__ __forceinline__ void pass_in(const cplx<T> *x, int t, const cplx<T> (
 }
 
 // pass_out: the Stockham writes of the thread's butterfly outputs.
-template <typename T, int LOGN, int R, int NS>
+template <typename T, int LOGN, int R, int NS, int V = 16>
 __device__ __forceinline__ void pass_out(cplx<T> *x, int t, const cplx<T> (*v)[R]) {
-    constexpr int TPF = (1 << LOGN) / 16;
+    constexpr int TPF = (1 << LOGN) / V;
 #pragma unroll
-    for (int b = 0; b < 16 / R; ++b) {
+    for (int b = 0; b < V / R; ++b) {
         const int j = t + b * TPF;
         const int k = j & (NS - 1);
         const int base = (j - k) * R + k;
@@ -158,24 +163,35 @@ __device__ __forceinline__ void pass_out(cplx<T> *x, int t, const cplx<T> (*v)[R
     }
 }
 
-template <typename T, int LOGN, int R, int NS, int DIR>
-__device__ __forceinline__ void pass16(cplx<T> *x, int t, bool active, const cplx<T> (*pw)[4]) {
-    cplx<T> v[16 / R][R];
-    if (active) pass_in<T, LOGN, R, NS, DIR>(x, t, pw, v);
-    __syncthreads();
-    if (active) pass_out<T, LOGN, R, NS>(x, t, v);
-    __syncthreads();
+// Barrier between the passes of a transform.  WAVE: the transform's threads are
+// lanes of one wave, whose LDS accesses execute in order, so only the compiler
+// has to keep them in order and the workgroup's other waves need not be waited for.
+template <bool WAVE> __device__ __forceinline__ void pass_sync() {
+    if constexpr (WAVE) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    } else {
+        __syncthreads();
+    }
 }
 
-template <typename T, int LOGN, int DIR, int DONE>
-__device__ __forceinline__ void passes16(cplx<T> *x, int t, bool active, const Tw16<T, LOGN> &w) {
+template <typename T, int LOGN, int R, int NS, int DIR, int V = 16, bool WAVE = false>
+__device__ __forceinline__ void pass16(cplx<T> *x, int t, bool active, const cplx<T> (*pw)[logv<V>()]) {
+    cplx<T> v[V / R][R];
+    if (active) pass_in<T, LOGN, R, NS, DIR, V>(x, t, pw, v);
+    pass_sync<WAVE>();
+    if (active) pass_out<T, LOGN, R, NS, V>(x, t, v);
+    pass_sync<WAVE>();
+}
+
+template <typename T, int LOGN, int DIR, int DONE, int V, bool WAVE>
+__device__ __forceinline__ void passes16(cplx<T> *x, int t, bool active, const Tw16<T, LOGN, V> &w) {
     if constexpr (DONE < LOGN) {
-        constexpr int REM = LOGN - DONE;
-        constexpr int R = REM >= 4 ? 16 : (1 << REM);
-        constexpr int LOGR = REM >= 4 ? 4 : REM;
-        constexpr int q = DONE / 4;
-        pass16<T, LOGN, R, (1 << DONE), DIR>(x, t, active, w.p[q > 0 ? q - 1 : 0]);
-        passes16<T, LOGN, DIR, DONE + LOGR>(x, t, active, w);
+        constexpr int q = DONE / logv<V>();
+        constexpr int R = pass_radix<LOGN, V>(q);
+        constexpr int LOGR = LOGN - DONE >= logv<V>() ? logv<V>() : LOGN - DONE;
+        pass16<T, LOGN, R, (1 << DONE), DIR, V, WAVE>(x, t, active, w.p[q > 0 ? q - 1 : 0]);
+        passes16<T, LOGN, DIR, DONE + LOGR, V, WAVE>(x, t, active, w);
     }
 }
 
@@ -225,21 +241,23 @@ __device__ __forceinline__ void fft16_regs(cplx<T> *x, int t, const Tw16<T, LOGN
 }
 
 // In-place transforms of NREG regions (region i at buf + i * lds_region<LOGN>(),
-// padded indexing) by a workgroup of NTH threads; teams of N/16 threads take
-// regions round-robin.  Ends with a barrier.  DIR -1 forward, +1 inverse.
-// w: the thread's twiddles (load_tw16).
-template <typename T, int LOGN, int DIR, int NREG, int NTH>
-__device__ __forceinline__ void wg_fft16(cplx<T> *buf, const Tw16<T, LOGN> &w) {
-    constexpr int TPF = (1 << LOGN) / 16;
+// padded indexing) by a workgroup of NTH threads; teams of N/V consecutive
+// threads take regions round-robin.  Ends with a barrier.  DIR -1 forward, +1
+// inverse.  w: the thread's twiddles (load_tw16).
+template <typename T, int LOGN, int DIR, int NREG, int NTH, int V = 16>
+__device__ __forceinline__ void wg_fft16(cplx<T> *buf, const Tw16<T, LOGN, V> &w) {
+    constexpr int TPF = (1 << LOGN) / V;
     static_assert(NTH % TPF == 0 || TPF > NTH, "team must divide the workgroup");
     constexpr int NTEAMS = NTH / TPF;
+    constexpr bool WAVE = TPF <= 64;
     const int team = threadIdx.x / TPF, t = threadIdx.x % TPF;
 #pragma unroll 1
     for (int g = 0; g < NREG; g += NTEAMS) {
         const int reg = g + team;
         const bool active = reg < NREG;
-        passes16<T, LOGN, DIR, 0>(buf + (active ? reg : 0) * lds_region<LOGN>(), t, active, w);
+        passes16<T, LOGN, DIR, 0, V, WAVE>(buf + (active ? reg : 0) * lds_region<LOGN>(), t, active, w);
     }
+    if constexpr (WAVE) __syncthreads();
 }
 
 }  // namespace rdk

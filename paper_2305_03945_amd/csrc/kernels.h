@@ -1,7 +1,10 @@
 // HIP kernels of one G-prox PDHG iteration (Algorithm 1) and of the FP64 outer
 // residual passes of the mixed-precision step.
 //
-// One iteration n -> n+1 is four launches over every active slot:
+// One iteration n -> n+1 is the column pass and the row-parallel steps, over every
+// active slot.  The row-parallel steps are one launch, k_rows (kernels_rows.h),
+// where its rows fit in LDS, and k_rowinv, k_upd and k_row_forward elsewhere (FP64
+// on 4096^2, wide stencils and two components on 2048^2 and 4096^2):
 //   k_cols       column pass of Y = G^-1 W_n: forward column FFT, multiply by
 //                1 / (N^2 g), inverse column FFT, in place on the spectrum S
 //                (the row pass before it left S = row transforms of W_n).
@@ -341,10 +344,37 @@ template <int EQ> constexpr int stencil_hy() { return EQ == EQ_FCH ? 3 : EQ == E
 // (mu(U) under Lap, and the reaction difference under Lap^2); the others at the point.
 template <int EQ> constexpr int ftilde_hu() { return EQ == EQ_FCH ? 2 : EQ == EQ_BIH ? 1 : 0; }
 
+// ---------------------------------------------------------------- fused row pass: its plan
+// Sizes of k_rows (kernels_rows.h), the one launch for the three row-parallel steps.
+template <typename T, int LOGN, int EQ> struct RowsPlan {
+    static constexpr int C = EQ == EQ_SCHNAK ? 2 : 1;
+    static constexpr int N = 1 << LOGN;
+    static constexpr int HY = stencil_hy<EQ>();
+    static constexpr int R = rows_per_block<T, LOGN, C>();
+    static constexpr int RU = R + 2 * HY;        // rows of U_{n+1}
+    static constexpr int RP = R + 4 * HY;        // rows of P~
+    static constexpr int NRI = C * RP / 2;       // inverse transforms (row pairs)
+    static constexpr int NRF = C * R / 2;        // forward transforms
+    static constexpr int V = LOGN <= 9 ? 8 : 16; // values per thread of a transform
+    static constexpr int TPF = N / V;
+    static constexpr int want = NRI * TPF;
+    static constexpr int NTH = want <= 256 ? 256 : 512;
+    static constexpr size_t lds = (size_t)NRI * lds_region<LOGN>() * sizeof(cplx<T>);
+    // points per thread of the primal update and of the residual
+    static constexpr int QU = RU * N / 4 >= NTH ? 4 : RU * N / 2 >= NTH ? 2 : 1;
+    static constexpr int QW = R / 2 * N / 4 >= NTH ? 4 : R / 2 * N / 2 >= NTH ? 2 : 1;
+};
+
+// Whether the fused row pass serves (T, N, equation): its LDS fits.
+template <typename T, int LOGN, int EQ> constexpr bool rows_fused() {
+    return RowsPlan<T, LOGN, EQ>::lds + 1024 <= 163840 && RowsPlan<T, LOGN, EQ>::N >= RowsPlan<T, LOGN, EQ>::RP;
+}
+
 // ---------------------------------------------------------------- deterministic block sums
 // Workgroup sum of K values per thread, in a fixed order (wave butterflies, then
 // the waves in order); the totals are valid in thread 0 only.
-template <int K> __device__ __forceinline__ void block_sum(double *v, double *scratch /* K * NT/64 */) {
+template <int K, int NTH = NT>
+__device__ __forceinline__ void block_sum(double *v, double *scratch /* K * NTH/64 */) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         double x = v[k];
@@ -355,7 +385,7 @@ template <int K> __device__ __forceinline__ void block_sum(double *v, double *sc
     const int wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) {
 #pragma unroll
-        for (int k = 0; k < K; ++k) scratch[k * (NT / 64) + wave] = v[k];
+        for (int k = 0; k < K; ++k) scratch[k * (NTH / 64) + wave] = v[k];
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -363,7 +393,7 @@ template <int K> __device__ __forceinline__ void block_sum(double *v, double *sc
         for (int k = 0; k < K; ++k) {
             double x = 0.0;
 #pragma unroll
-            for (int w = 0; w < NT / 64; ++w) x += scratch[k * (NT / 64) + w];
+            for (int w = 0; w < NTH / 64; ++w) x += scratch[k * (NTH / 64) + w];
             v[k] = x;
         }
     }
@@ -388,9 +418,9 @@ __device__ __forceinline__ void finalize(SlotRef s, const double *sumsq, const d
 // Write this workgroup's partial sums (squared residual norm and sum(U - U^k)
 // per component) to the slot's partials array.  The stop decision is taken by
 // k_finalize, launched right after, which reads them after the kernel boundary.
-template <int C>
+template <int C, int NTH = NT>
 __device__ __forceinline__ void write_partials(SlotRef s, int tile, double *acc /* 2C */, double *scratch) {
-    block_sum<2 * C>(acc, scratch);
+    block_sum<2 * C, NTH>(acc, scratch);
     if (threadIdx.x == 0) {
 #pragma unroll
         for (int k = 0; k < 2 * C; ++k) s.partials[tile * (2 * C) + k] = acc[k];
@@ -549,6 +579,8 @@ __device__ __forceinline__ void produce_W4(SlotRef s, StateRef sst, int y, int x
             for (int c = 0; c < C; ++c) {
                 if constexpr (KIND == K_INIT64) {
                     store4<double>(gp((double *)s.U[0]) + c * NN + g0, Uc4[c]);
+                    // Q_1 = W_0 (mixed: the row pass takes it from r32)
+                    if constexpr (rows_fused<double, LOGN, EQ>()) store4<double>(gp((double *)s.P) + c * NN + g0, W4[c]);
                 } else if constexpr (KIND == K_OUTER_INIT) {
                     store4<double>(gp(s.U64[0]) + c * NN + g0, Uc4[c]);
                 } else {
@@ -838,9 +870,40 @@ __device__ __forceinline__ void rows_load_pre(cplx<T> *buf, const cplx<T> *S, in
 }
 
 // ---------------------------------------------------------------- row pass, forward
-template <typename T, int LOGN, int BC, int EQ, int KIND>
-__device__ __forceinline__ void row_forward_pass(SlotRef s, StateRef sst, cplx<T> *buf, double *scratch) {
+// A transformed block of rows (packed pairs in buf) -> its tiles of S.
+template <typename T, int LOGN, int BC, int C, int R, int NTH>
+__device__ __forceinline__ void rows_store_spectrum(cplx<T> *buf, cplx<T> *S, int y0, const cplx<T> *__restrict__ twd) {
     constexpr int N = 1 << LOGN, H = N / 2;
+    constexpr int NREG = C * R / 2;
+    if constexpr (BC == BC_P) {
+        rows_post_store<T, LOGN, C, R, NTH>(buf, S, y0);
+    } else {
+        rows_post_forward<T, LOGN, BC, NREG, NTH>(buf, twd);
+        // Tile store: this workgroup's R rows are one contiguous block per component;
+        // every access of the block is issued before any completes.
+        constexpr int SV = spec_vec<T>();
+        constexpr int TOT = C * R * H / SV;
+#pragma unroll
+        for (int i = 0; i < (TOT + NTH - 1) / NTH; ++i) {
+            const int idx = threadIdx.x + i * NTH;
+            if (TOT % NTH == 0 || idx < TOT) {
+                const int r0 = (idx % (R / SV)) * SV, rest = idx / (R / SV);
+                const int kx = rest % H, c = rest / H;
+                cplx<T> v[SV];
+#pragma unroll
+                for (int q = 0; q < SV; ++q) {
+                    const int r = r0 + q;
+                    v[q] = buf[rix<LOGN>(c * R / 2 + r / 2, (r & 1) * H + kx)];
+                }
+                spec_store<T>(&S[spec_off<R>(c, y0 + r0, kx, N)], v);
+            }
+        }
+    }
+}
+
+template <typename T, int LOGN, int BC, int EQ, int KIND, int NTH = NT>
+__device__ __forceinline__ void row_forward_pass(SlotRef s, StateRef sst, cplx<T> *buf, double *scratch) {
+    constexpr int N = 1 << LOGN;
     constexpr int C = EQ == EQ_SCHNAK ? 2 : 1;
     constexpr int R = rows_per_block<T, LOGN, C>();
     constexpr int NREG = C * R / 2;
@@ -860,7 +923,7 @@ __device__ __forceinline__ void row_forward_pass(SlotRef s, StateRef sst, cplx<T
         // share once the rows in flight exceed the L2 (75 -> 71 us); at 2048^2 the
         // FP32 inner pass measured no gain.
 #pragma unroll 2
-        for (int idx = threadIdx.x; idx < (R / 2) * N / 4; idx += NT) {
+        for (int idx = threadIdx.x; idx < (R / 2) * N / 4; idx += NTH) {
             const int p = idx >> (LOGN - 2), x0 = (idx & (N / 4 - 1)) * 4;
             T wv[2][4][C];
             produce_W4x2<T, LOGN, BC, EQ, KIND>(s, sst, y0 + 2 * p, x0, wv, acc);
@@ -874,7 +937,7 @@ __device__ __forceinline__ void row_forward_pass(SlotRef s, StateRef sst, cplx<T
     } else {
         // four consecutive points per thread and pass, vector loads
 #pragma unroll 2
-        for (int idx = threadIdx.x; idx < R * N / 4; idx += NT) {
+        for (int idx = threadIdx.x; idx < R * N / 4; idx += NTH) {
             const int r = idx >> (LOGN - 2), x0 = (idx & (N / 4 - 1)) * 4;
             T wv[4][C];
             produce_W4<T, LOGN, BC, EQ, KIND>(s, sst, y0 + r, x0, wv, acc);
@@ -887,36 +950,9 @@ __device__ __forceinline__ void row_forward_pass(SlotRef s, StateRef sst, cplx<T
         }
     }
     __syncthreads();
-    const cplx<T> *twd = (const cplx<T> *)s.twd;
-    wg_fft16<T, LOGN, -1, NREG, NT>(buf, twr);
-    cplx<T> *S = (cplx<T> *)s.S;
-    if constexpr (BC == BC_P) {
-        rows_post_store<T, LOGN, C, R, NT>(buf, S, y0);
-    } else {
-    rows_post_forward<T, LOGN, BC, NREG, NT>(buf, twd);
-    // Tile store: this workgroup's R rows are one contiguous block per component;
-    // every access of the block is issued before any completes.
-    {
-        constexpr int SV = spec_vec<T>();
-        constexpr int TOT = C * R * H / SV;
-#pragma unroll
-        for (int i = 0; i < (TOT + NT - 1) / NT; ++i) {
-            const int idx = threadIdx.x + i * NT;
-            if (TOT % NT == 0 || idx < TOT) {
-                const int r0 = (idx % (R / SV)) * SV, rest = idx / (R / SV);
-                const int kx = rest % H, c = rest / H;
-                cplx<T> v[SV];
-#pragma unroll
-                for (int q = 0; q < SV; ++q) {
-                    const int r = r0 + q;
-                    v[q] = buf[rix<LOGN>(c * R / 2 + r / 2, (r & 1) * H + kx)];
-                }
-                spec_store<T>(&S[spec_off<R>(c, y0 + r0, kx, N)], v);
-            }
-        }
-    }
-    }
-    write_partials<C>(s, tile, acc, scratch);
+    wg_fft16<T, LOGN, -1, NREG, NTH>(buf, twr);
+    rows_store_spectrum<T, LOGN, BC, C, R, NTH>(buf, (cplx<T> *)s.S, y0, (const cplx<T> *)s.twd);
+    write_partials<C, NTH>(s, tile, acc, scratch);
 }
 
 template <typename T, int LOGN, int BC, int EQ, int KIND>
@@ -996,7 +1032,7 @@ template <typename T, int LOGN, int C> constexpr bool cols_in_regs() {
 }
 
 template <typename T, int LOGN, int C, int CB>
-__device__ __forceinline__ void cols_regs(SlotRef s, int c, int kx0, cplx<T> *S, cplx<T> *buf) {
+__device__ __forceinline__ void cols_regs(SlotRef s, int c, int kx0, const cplx<T> *S, cplx<T> *S2, cplx<T> *buf) {
     constexpr int N = 1 << LOGN, H = N / 2, TPF = N / 16;
     constexpr int R = rows_per_block<T, LOGN, C>();
     typedef T v2_t __attribute__((ext_vector_type(2)));
@@ -1045,7 +1081,7 @@ __device__ __forceinline__ void cols_regs(SlotRef s, int c, int kx0, cplx<T> *S,
         load_tw16<T, LOGN>(twr, (const cplx<T> *)s.tw, t2);
         fft16_regs<T, LOGN, +1>(x2, t2, twr, v);
     }
-    const auto So = gp((v2_t *)S);
+    const auto So = gp((v2_t *)S2);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         v2_t a;
@@ -1087,10 +1123,11 @@ __global__ __launch_bounds__((col_threads<T, LOGN, C>()), (col_waves_per_eu<T, L
     const int bx = xcd_tile((int)blockIdx.x - (FIN != FIN_NONE ? 1 : 0), C * (H / CB));
     const int c = bx / (H / CB);
     const int kx0 = (bx % (H / CB)) * CB;
-    cplx<T> *S = (cplx<T> *)s.S;
+    const cplx<T> *S = (const cplx<T> *)s.S;
+    cplx<T> *S2 = (cplx<T> *)s.S2;
     if constexpr (BC == BC_P && cols_in_regs<T, LOGN, C>()) {
         if (kx0 > 0) {
-            cols_regs<T, LOGN, C, CB>(s, c, kx0, S, buf);
+            cols_regs<T, LOGN, C, CB>(s, c, kx0, S, S2, buf);
             return;
         }
     }
@@ -1143,7 +1180,7 @@ __global__ __launch_bounds__((col_threads<T, LOGN, C>()), (col_waves_per_eu<T, L
                 const int pos = (BC == BC_P) ? y + q : dct_pos(y + q, N);
                 v[q] = buf[rix<LOGN>(reg, pos)];
             }
-            spec_store<T>(&S[spec_off<R>(c, y, kx0 + reg, N)], v);
+            spec_store<T>(&S2[spec_off<R>(c, y, kx0 + reg, N)], v);
         }
     }
 }
@@ -1162,7 +1199,7 @@ __global__ __launch_bounds__(NT) void k_rowinv(Slot *const *slots) {
     const size_t NN = (size_t)N * N;
     Tw16<T, LOGN> twr;
     load_tw16<T, LOGN>(twr, (const cplx<T> *)s.tw);
-    const cplx<T> *S = (const cplx<T> *)s.S;
+    const cplx<T> *S = (const cplx<T> *)s.S2;
     const auto P = gp((T *)s.P);
     const auto Pt = gp((T *)s.Pt);
     const bool first = sst.iters == 0;
@@ -1424,7 +1461,7 @@ __global__ __launch_bounds__(NT) void k_rows_transform_out(Slot *const *slots, d
     const size_t NN = (size_t)N * N;
     Tw16<T, LOGN> twr;
     load_tw16<T, LOGN>(twr, (const cplx<T> *)s.tw);
-    const cplx<T> *S = (const cplx<T> *)s.S;
+    const cplx<T> *S = (const cplx<T> *)s.S2;
 #pragma unroll 8
     for (int idx = threadIdx.x; idx < C * R * H; idx += NT) {
         const int r = idx % R, rest = idx / R;

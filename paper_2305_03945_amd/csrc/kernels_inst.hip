@@ -2,6 +2,7 @@
 // the build) and registers the launchers.
 #include "kernels.h"
 #include "kernels3d.h"
+#include "kernels_rows.h"
 #include "kernels_wg.h"
 #include "registry.h"
 
@@ -71,6 +72,14 @@ void launch_upd(Slot *const *slots, int nslots, hipStream_t st, hipEvent_t *ev) 
                           ev_stop(ev), 0, slots);
 }
 
+// The row-parallel steps of an iteration in one launch.
+template <typename T, int BC, int EQ>
+void launch_rows(Slot *const *slots, int nslots, hipStream_t st, hipEvent_t *ev) {
+    using Pl = RowsPlan<T, L, EQ>;
+    hipExtLaunchKernelGGL((k_rows<T, L, BC, EQ>), dim3(Pl::N / Pl::R, nslots), dim3(Pl::NTH), 0, st, ev_start(ev),
+                          ev_stop(ev), 0, slots);
+}
+
 template <typename T, int BC, int EQ>
 void launch_tin(Slot *const *slots, int nslots, const double *in, double *, hipStream_t st) {
     constexpr int R = row_block<T, EQ>();
@@ -97,12 +106,16 @@ template <int BC, int EQ> void fill_mixed();
 template <int BC, int EQ> void fill() {
     KSet &f = g_kernels[MODE_F64][L][BC][EQ];
     f.init = launch_rowfwd_fin<double, BC, EQ, K_INIT64>;
-    f.rowfwd = launch_rowfwd<double, BC, EQ, K_ITER64>;
     f.fin = launch_fin<K_ITER64, EQ>;
     f.cols = launch_cols<double, BC, EQ, FIN_NONE>;
     f.cols_fin = launch_cols<double, BC, EQ, K_ITER64>;
-    f.rowinv = launch_rowinv<double, BC, EQ>;
-    f.upd = launch_upd<double, BC, EQ, MODE_F64>;
+    if constexpr (rows_fused<double, L, EQ>()) {
+        f.rows = launch_rows<double, BC, EQ>;
+    } else {
+        f.rowinv = launch_rowinv<double, BC, EQ>;
+        f.upd = launch_upd<double, BC, EQ, MODE_F64>;
+        f.rowfwd = launch_rowfwd<double, BC, EQ, K_ITER64>;
+    }
     f.tin = launch_tin<double, BC, EQ>;
     f.tout = launch_tout<double, BC, EQ>;
     f.rows_per_block = row_block<double, EQ>();
@@ -113,14 +126,18 @@ template <int BC, int EQ> void fill() {
 template <int BC, int EQ> void fill_mixed() {
     KSet &m = g_kernels[MODE_MIXED][L][BC][EQ];
     m.init = launch_rowfwd_fin<float, BC, EQ, K_OUTER_INIT>;
-    // the iteration row pass makes the outer update itself when the inner loop
-    // has stopped, and the decisions after it follow (no separate outer launch)
-    m.rowfwd = launch_rowfwd<float, BC, EQ, K_MIXED>;
     m.fin = launch_fin<K_MIXED, EQ>;
     m.cols = launch_cols<float, BC, EQ, FIN_NONE>;
     m.cols_fin = launch_cols<float, BC, EQ, K_MIXED>;
-    m.rowinv = launch_rowinv<float, BC, EQ>;
-    m.upd = launch_upd<float, BC, EQ, MODE_MIXED>;
+    // the iteration row pass makes the outer update itself when the inner loop
+    // has stopped, and the decisions after it follow (no separate outer launch)
+    if constexpr (rows_fused<float, L, EQ>()) {
+        m.rows = launch_rows<float, BC, EQ>;
+    } else {
+        m.rowinv = launch_rowinv<float, BC, EQ>;
+        m.upd = launch_upd<float, BC, EQ, MODE_MIXED>;
+        m.rowfwd = launch_rowfwd<float, BC, EQ, K_MIXED>;
+    }
     m.tin = launch_tin<float, BC, EQ>;
     m.tout = launch_tout<float, BC, EQ>;
     m.rows_per_block = row_block<float, EQ>();

@@ -75,8 +75,9 @@ struct Slot {
     // Iterate buffers, element type T of the PDHG loop (double for FP64, float for
     // the mixed inner loop), each [ncomp][N][N]:
     void *U[2];                  // FP64: U_n ping-pong; mixed: correction e_n ping-pong
-    void *P, *Pt;                // dual variable and its extrapolation
+    void *P, *Pt;                // dual variable and its extrapolation (one-launch row pass: Q, S2)
     void *S;                     // spectrum, [ncomp][N/2][N] complex, transposed
+    void *S2;                    // where the 2-D column pass writes: S, or (one-launch row pass) Pt
     double *Uk;                  // U^k (FP64)
     double *U64[2];              // mixed: FP64 U ping-pong across outer passes
     float *r32, *Ub32;           // mixed: FP32 outer residual and FP32 copy of U

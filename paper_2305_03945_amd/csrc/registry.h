@@ -18,6 +18,7 @@ struct KSet {
     launch_fn cols = nullptr;       // column pass (T)
     launch_fn cols_fin = nullptr;   // column pass + stop decision of the preceding iteration row pass
     launch_fn fin = nullptr;        // stop decision of an iteration row pass (k_finalize)
+    launch_fn rows = nullptr;       // where set: the next three in one launch (k_rows)
     launch_fn rowinv = nullptr;     // inverse rows + dual update (T)
     launch_fn upd = nullptr;        // primal update (T)
     launch_fn rowfwd = nullptr;     // FP64: K_ITER64; mixed: K_MIXED (inner or outer pass); no decision

@@ -427,7 +427,11 @@ void fill_params(Slot &s, const rd_problem *p, const rd_opts *o, const Desc &d, 
     }
 }
 
-void bind_workspace(Slot &s, const Workspace &w, const Tables &t) {
+// The column pass moves the spectrum to the extrapolated dual's buffer where the
+// row-parallel steps are one launch, which needs no such field (kernels_rows.h).
+void *column_output(const KSet &k, const Slot &s) { return k.rows ? s.Pt : s.S; }
+
+void bind_workspace(Slot &s, const Workspace &w, const Tables &t, const KSet &k) {
     const Slot &q = w.proto;
     for (int i = 0; i < 2; ++i) {
         s.U[i] = q.U[i];
@@ -436,6 +440,7 @@ void bind_workspace(Slot &s, const Workspace &w, const Tables &t) {
     s.P = q.P;
     s.Pt = q.Pt;
     s.S = q.S;
+    s.S2 = column_output(k, s);
     s.Uk = q.Uk;
     s.r32 = q.r32;
     s.Ub32 = q.Ub32;
@@ -471,6 +476,10 @@ void enqueue_round(const KSet &k, Slot *const *slots, int nslots, int iters, hip
     }
     for (int i = 0; i < iters; ++i) {
         (i == 0 ? k.cols : k.cols_fin)(slots, nslots, st, nullptr);
+        if (k.rows) {
+            k.rows(slots, nslots, st, nullptr);
+            continue;
+        }
         k.rowinv(slots, nslots, st, nullptr);
         k.upd(slots, nslots, st, nullptr);
         k.rowfwd(slots, nslots, st, nullptr);
@@ -714,7 +723,7 @@ rd_status rd_step(rd_ctx *ctx, const rd_problem *prob, const rd_opts *opts, doub
     Slot &s = *w->slot_host;
     std::memset(&s, 0, sizeof(Slot));
     fill_params(s, prob, opts, d, h_t);
-    bind_workspace(s, *w, *t);
+    bind_workspace(s, *w, *t, k);
     s.src = u_n;
     const size_t n = (size_t)d.C * d.pts;
     const bool dev_copy = ((uintptr_t)u_np1 % 32) == 0 && n % 4 == 0;
@@ -810,6 +819,7 @@ rd_status rd_step_noalloc(rd_ctx *ctx, const rd_problem *prob, const rd_opts *op
     s.P = B + o_p;
     s.Pt = B + o_pt;
     s.S = B + o_s;
+    s.S2 = column_output(k, s);
     s.Uk = (double *)(B + o_uk);
     if (mode == MODE_MIXED) {
         s.U64[0] = (double *)(B + o_v0);
@@ -880,7 +890,7 @@ rd_status rd_profile_iteration(rd_ctx *ctx, const rd_problem *prob, const rd_opt
     Slot &s = *w->slot_host;
     std::memset(&s, 0, sizeof(Slot));
     fill_params(s, prob, opts, d, h_t);
-    bind_workspace(s, *w, *t);
+    bind_workspace(s, *w, *t, k);
     s.src = u_n;
     s.max_iter = 1 << 30;   // the stop decision must not end the timed launches
     s.tol = 0.0;
@@ -891,6 +901,8 @@ rd_status rd_profile_iteration(rd_ctx *ctx, const rd_problem *prob, const rd_opt
     std::vector<launch_fn> fns;
     if (d.dim == 3)
         fns = {k.yfwd_fin, k.zsym, k.yinv, k.rowinv, k.upd, k.rowfwd};
+    else if (k.rows)
+        fns = {k.cols_fin, k.rows};
     else
         fns = {k.cols_fin, k.rowinv, k.upd, k.rowfwd};
     const int nk = (int)fns.size();
@@ -922,6 +934,7 @@ rd_status rd_profile_iteration(rd_ctx *ctx, const rd_problem *prob, const rd_opt
         for (int kk = 0; kk < nk; ++kk) fns[kk](w->slot_list_dev, 1, st, &ev[2 * (nk * i + kk)]);
     RD_CHECK(hipGetLastError());
     RD_CHECK(hipStreamSynchronize(st));
+    for (int kk = nk; kk < 4; ++kk) ms_out[kk] = 0.0;   // steps that the one row launch covers
     for (int kk = 0; kk < nk; ++kk) {
         double tot = 0.0;
         for (int i = 0; i < reps; ++i) {
@@ -1098,7 +1111,7 @@ rd_status rd_precond_solve(rd_ctx *ctx, const rd_problem *prob, double h_t, int3
     Slot &s = *w->slot_host;
     std::memset(&s, 0, sizeof(Slot));
     fill_params(s, prob, nullptr, d, h_t);
-    bind_workspace(s, *w, *t);
+    bind_workspace(s, *w, *t, k);
     RD_CHECK(hipMemcpyAsync(w->slot_dev, &s, sizeof(Slot), hipMemcpyHostToDevice, st));
     RD_CHECK(hipMemsetAsync(w->proto.st, 0, sizeof(State), st));   // unfinished State: the passes run
     k.tin(w->slot_list_dev, 1, w_in, nullptr, st);
@@ -1298,7 +1311,7 @@ rd_status launch_rounds(Ctx *c) {
                 Slot &s = *t->ws->slot_host;
                 std::memset(&s, 0, sizeof(Slot));
                 fill_params(s, &t->prob, &t->opts, t->d, ps.ht);
-                bind_workspace(s, *t->ws, *tb);
+                bind_workspace(s, *t->ws, *tb, k);
                 s.src = t->u;
                 RD_CHECK(hipMemcpyAsync(t->ws->slot_dev, &s, sizeof(Slot), hipMemcpyHostToDevice, st));
                 t->running = true;

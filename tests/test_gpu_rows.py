@@ -1,0 +1,60 @@
+"""The one-launch row pass (inverse rows, primal update, residual, forward rows): its
+halo rows at the edges of the grid and of its row blocks, both boundaries, every
+stencil, and step sizes and an extrapolation that are not all alike, against the FP64
+oracle.  FP64 steps agree to 1e-10 with equal iteration counts, mixed ones to 1e-5."""
+import numpy as np
+import pytest
+
+from oracle import equations as oeq, pdhg as opdhg
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+# kind, grid, h_t, tolerance, step sizes, omega: FCH takes this path from 16^2 up (its
+# 14 rows of P~ nearly cover the grid there), the others above 64^2
+CASES = [
+    ("fch", 16, 1e-3, 1e-6, 0.58, 0.5, 1.0),
+    ("fch", 64, 1e-3, 5e-6, 0.5, 0.58, 0.9),
+    ("allen_cahn", 128, 1e-3, 1e-8, 0.9, 0.7, 0.8),
+    ("allen_cahn", 1024, 1e-3, 1e-6, 0.9, 0.9, 1.0),
+    ("heat", 256, 1e-3, 1e-8, 0.8, 0.9, 1.0),
+    ("cahn_hilliard", 128, 1e-4, 1e-3, 0.7, 0.6, 0.9),
+    ("cahn_hilliard", 256, 1e-4, 1e-2, 0.7, 0.7, 1.0),
+    ("biharmonic", 128, 1e-4, 1e-3, 0.7, 0.7, 1.0),
+    ("schnakenberg", 128, 1e-3, 1e-5, 0.9, 0.8, 0.9),
+]
+
+
+def state(kind, N, seed):
+    rng = np.random.default_rng(seed)
+    if kind == "fch":
+        x = 2 * np.pi * (np.arange(N) + 0.5) / N
+        X, Y = np.meshgrid(x, x)
+        return 2 * np.exp(np.sin(X) + np.cos(Y) - 2) + 2.1 * np.exp(-np.sin(X) - np.cos(Y) - 2) - 1
+    if kind == "schnakenberg":
+        return np.stack([1.0 + rng.uniform(-0.01, 0.01, (N, N)), 0.9 + rng.uniform(-0.01, 0.01, (N, N))])
+    return rng.uniform(-0.1, 0.1, (N, N))
+
+
+@pytest.mark.parametrize("bc", ["periodic", "neumann"])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "%s-%d" % c[:2])
+def test_step_matches_oracle(case, bc):
+    from paper_2305_03945_amd import rd
+    kind, N, ht, tol, tau_u, tau_p, omega = case
+    diff = {"fch": (0.18 ** 2,), "cahn_hilliard": (4e-4,), "biharmonic": (4e-4,), "schnakenberg": (1.0, 10.0)}.get(
+        kind, (1e-4,))
+    par = dict(L=2 * np.pi if kind == "fch" else 1.0, bc=bc, diff=diff, b=1.0, a=0.1, sb=0.9, kappa=1.0)
+    u = state(kind, N, 7)
+    ref = opdhg.step(oeq.Problem(kind=kind, N=N, **par), u, ht,
+                     opdhg.Options(tol=tol, max_iter=2000, tau_u=tau_u, tau_p=tau_p, omega=omega))
+    assert ref.status == "ok"
+    ctx = rd.Context(0)
+    p = rd.make_problem(kind, N, **par)
+    for prec, bound in (("fp64", 1e-10), ("mixed", 1e-5)):
+        o = rd.make_opts(tol=tol, max_iter=2000, tau_u=tau_u, tau_p=tau_p, omega=omega, precision=prec)
+        out, info = ctx.step(torch.tensor(u, device="cuda"), ht, p, o)
+        assert info["status"] == "ok", (prec, info)
+        if prec == "fp64":
+            assert info["iters"] == ref.iters
+        assert float(np.max(np.abs(out.cpu().numpy() - ref.U))) <= bound
+    ctx.close()
