@@ -200,13 +200,87 @@ __device__ __forceinline__ void rows_pre_inverse(cplx<T> *buf, const cplx<T> *__
     __syncthreads();
 }
 
-// Symbol multiplier 1 / (N^2 g), g = (1 + alpha mu + beta mu^2 + gamma mu^3)^2,
+// Symbol multiplier invNd / g, g = (1 + alpha mu + beta mu^2 + gamma mu^3)^2, invNd a
+// power of two.  The reciprocal of the root a = sqrt(g) >= 1 is the hardware's
+// estimate and two Newton steps (as far as 1 ulp; the full division's scaling and
+// fix-up are for operands that do not occur here), squared; a is bounded so that
+// an overflowing g still gives 0.
+__device__ __forceinline__ double symbol_of(double mu, double alpha, double beta, double gamma, double invNd) {
+    double a = 1.0 + mu * (alpha + mu * (beta + gamma * mu));
+    a = a > 0x1p+1000 ? 0x1p+1000 : a;
+    double r = __builtin_amdgcn_rcp(a);
+    r = __builtin_fma(__builtin_fma(-a, r, 1.0), r, r);
+    r = __builtin_fma(__builtin_fma(-a, r, 1.0), r, r);
+    return invNd * (r * r);
+}
+
 // mu = s_kx + s_ky.
 __device__ __forceinline__ double symbol_mult(const double *__restrict__ eig, int kx, int ky, double alpha,
                                               double beta, double gamma, double invN2) {
-    const double mu = eig[kx] + eig[ky];
-    const double a = 1.0 + mu * (alpha + mu * (beta + gamma * mu));
-    return invN2 / (a * a);
+    return symbol_of(eig[kx] + eig[ky], alpha, beta, gamma, invN2);
+}
+
+// What a pair item of the symbol pass reads besides its two bins: the eigenvalues
+// at its bins l and nl = N - l (l = 0: bins 0 and N/2) and the DCT twiddle w_l.
+template <typename T> struct SymPair {
+    double el, en;
+    cplx<T> w;
+};
+template <typename T, int LOGN, int BC>
+__device__ __forceinline__ SymPair<T> load_sym_pair(const double *__restrict__ eig, const cplx<T> *__restrict__ twd,
+                                                    int l) {
+    constexpr int N = 1 << LOGN;
+    SymPair<T> p;
+    p.el = eig[l];
+    p.en = eig[l == 0 ? N / 2 : N - l];
+    if constexpr (BC == BC_N) p.w = twd[l];
+    return p;
+}
+
+// One pair item (bins zl, zn) of a transformed line that holds one complex sequence
+// (plain; eigenvalue ea of the other directions) or two real ones packed as real and
+// imaginary part (ea, eb; periodic), or two cosine sequences (Neumann).
+template <typename T, int BC>
+__device__ __forceinline__ void apply_symbol_pair(cplx<T> &zlr, cplx<T> &znr, int l, bool plain, double ea, double eb,
+                                                  const SymPair<T> &p, double al, double be, double ga, double invNd) {
+    auto m = [&](double ex, double ey) { return (T)symbol_of(ex + ey, al, be, ga, invNd); };
+    const cplx<T> zl = zlr, zn = znr;
+    if constexpr (BC == BC_P) {
+        if (plain) {
+            const T m1 = m(ea, p.el), m2 = m(ea, p.en);
+            zlr = {zl.re * m1, zl.im * m1};
+            znr = {zn.re * m2, zn.im * m2};
+        } else if (l == 0) {
+            // bins 0 and N/2 of two real sequences: real pairs
+            zlr = {zl.re * m(ea, p.el), zl.im * m(eb, p.el)};
+            znr = {zn.re * m(ea, p.en), zn.im * m(eb, p.en)};
+        } else {
+            const T ma = m(ea, p.el), mb = m(eb, p.el);
+            cplx<T> A = {(zl.re + zn.re) * (T)0.5, (zl.im - zn.im) * (T)0.5};
+            cplx<T> B = {(zl.im + zn.im) * (T)0.5, (zn.re - zl.re) * (T)0.5};
+            A = {A.re * ma, A.im * ma};
+            B = {B.re * mb, B.im * mb};
+            zlr = {A.re - B.im, A.im + B.re};
+            znr = {A.re + B.im, B.re - A.im};
+        }
+    } else {
+        if (l == 0) {
+            zlr = {zl.re * m(ea, p.el), zl.im * m(eb, p.el)};
+            znr = {zn.re * m(ea, p.en), zn.im * m(eb, p.en)};
+        } else {
+            const cplx<T> A = {(zl.re + zn.re) * (T)0.5, (zl.im - zn.im) * (T)0.5};
+            const cplx<T> B = {(zl.im + zn.im) * (T)0.5, (zn.re - zl.re) * (T)0.5};
+            const cplx<T> qa = cmul(A, p.w), qb = cmul(B, p.w);
+            // cosine coefficients at l and N-l, scaled by their symbols
+            const T xal = qa.re * m(ea, p.el), xan = -qa.im * m(ea, p.en);
+            const T xbl = qb.re * m(eb, p.el), xbn = -qb.im * m(eb, p.en);
+            const cplx<T> wc = cconj(p.w);
+            const cplx<T> va = cmul(wc, cplx<T>{xal, -xan});
+            const cplx<T> vb = cmul(wc, cplx<T>{xbl, -xbn});
+            zlr = {va.re - vb.im, va.im + vb.re};
+            znr = {va.re + vb.im, vb.re - va.im};
+        }
+    }
 }
 
 // ---- column pass, between the forward and inverse column FFTs: multiply by the
@@ -215,16 +289,17 @@ __device__ __forceinline__ double symbol_mult(const double *__restrict__ eig, in
 // column 0 packs kx = 0 (real part) and kx = N/2 (imaginary part).  Neumann:
 // column j packs kx = 2j (real) and kx = 2j + 1 (imaginary), both cosine
 // coefficients.  Each item rewrites its own two bins, so no barrier is needed
-// between reading and writing.
+// between reading and writing.  pre: the items' SymPairs, loaded ahead (nullptr:
+// loaded here).
 template <typename T, int LOGN, int BC, int NREG, int NTH>
 __device__ __forceinline__ void cols_apply_symbol(cplx<T> *buf, int job0, int njobs, SlotRef s,
-                                                  const cplx<T> *__restrict__ twd) {
+                                                  const cplx<T> *__restrict__ twd, const SymPair<T> *pre) {
     constexpr int N = 1 << LOGN, H = N / 2;
     constexpr int IPT = pair_items_per_thread<LOGN, NREG, NTH>();
     const double invN2 = 1.0 / ((double)N * (double)N);
     // FP32: not unrolled, which keeps the FP32 column pass within 128 registers
     // (no spills) so that two of its workgroups fit on a compute unit
-    constexpr int UNR = sizeof(T) == 4 ? 1 : IPT;
+    constexpr int UNR = sizeof(T) == 4 && IPT > 4 ? 1 : IPT;
 #pragma unroll UNR
     for (int i = 0; i < IPT; ++i) {
         const int it = threadIdx.x + i * NTH;
@@ -235,55 +310,10 @@ __device__ __forceinline__ void cols_apply_symbol(cplx<T> *buf, int job0, int nj
         const int c = job / H, j = job % H;
         const double al = s.alpha[c], be = s.beta[c], ga = s.gamma[c];
         const int nl = (l == 0) ? H : N - l;
-        cplx<T> &zlr = buf[rix<LOGN>(reg, l)];
-        cplx<T> &znr = buf[rix<LOGN>(reg, nl)];
-        const cplx<T> zl = zlr, zn = znr;
-        if constexpr (BC == BC_P) {
-            if (j > 0) {
-                const T m1 = (T)symbol_mult(s.eig, j, l, al, be, ga, invN2);
-                const T m2 = (T)symbol_mult(s.eig, j, nl, al, be, ga, invN2);
-                zlr = {zl.re * m1, zl.im * m1};
-                znr = {zn.re * m2, zn.im * m2};
-            } else if (l == 0) {
-                // bins 0 and N/2 of the packed (kx = 0, kx = N/2) column: real pairs
-                zlr = {zl.re * (T)symbol_mult(s.eig, 0, 0, al, be, ga, invN2),
-                       zl.im * (T)symbol_mult(s.eig, H, 0, al, be, ga, invN2)};
-                znr = {zn.re * (T)symbol_mult(s.eig, 0, H, al, be, ga, invN2),
-                       zn.im * (T)symbol_mult(s.eig, H, H, al, be, ga, invN2)};
-            } else {
-                const T ma = (T)symbol_mult(s.eig, 0, l, al, be, ga, invN2);
-                const T mb = (T)symbol_mult(s.eig, H, l, al, be, ga, invN2);
-                cplx<T> A = {(zl.re + zn.re) * (T)0.5, (zl.im - zn.im) * (T)0.5};
-                cplx<T> B = {(zl.im + zn.im) * (T)0.5, (zn.re - zl.re) * (T)0.5};
-                A = {A.re * ma, A.im * ma};
-                B = {B.re * mb, B.im * mb};
-                zlr = {A.re - B.im, A.im + B.re};
-                znr = {A.re + B.im, B.re - A.im};
-            }
-        } else {
-            const int ka = 2 * j, kb = 2 * j + 1;
-            if (l == 0) {
-                zlr = {zl.re * (T)symbol_mult(s.eig, ka, 0, al, be, ga, invN2),
-                       zl.im * (T)symbol_mult(s.eig, kb, 0, al, be, ga, invN2)};
-                znr = {zn.re * (T)symbol_mult(s.eig, ka, H, al, be, ga, invN2),
-                       zn.im * (T)symbol_mult(s.eig, kb, H, al, be, ga, invN2)};
-            } else {
-                const cplx<T> w = twd[l];
-                const cplx<T> A = {(zl.re + zn.re) * (T)0.5, (zl.im - zn.im) * (T)0.5};
-                const cplx<T> B = {(zl.im + zn.im) * (T)0.5, (zn.re - zl.re) * (T)0.5};
-                const cplx<T> qa = cmul(A, w), qb = cmul(B, w);
-                // cosine coefficients at l and N-l, scaled by their symbols
-                const T xal = qa.re * (T)symbol_mult(s.eig, ka, l, al, be, ga, invN2);
-                const T xan = -qa.im * (T)symbol_mult(s.eig, ka, N - l, al, be, ga, invN2);
-                const T xbl = qb.re * (T)symbol_mult(s.eig, kb, l, al, be, ga, invN2);
-                const T xbn = -qb.im * (T)symbol_mult(s.eig, kb, N - l, al, be, ga, invN2);
-                const cplx<T> wc = cconj(w);
-                const cplx<T> va = cmul(wc, cplx<T>{xal, -xan});
-                const cplx<T> vb = cmul(wc, cplx<T>{xbl, -xbn});
-                zlr = {va.re - vb.im, va.im + vb.re};
-                znr = {va.re + vb.im, vb.re - va.im};
-            }
-        }
+        const SymPair<T> p = pre ? pre[i] : load_sym_pair<T, LOGN, BC>(s.eig, twd, l);
+        const int ka = BC == BC_P ? j : 2 * j, kb = BC == BC_P ? H : 2 * j + 1;
+        apply_symbol_pair<T, BC>(buf[rix<LOGN>(reg, l)], buf[rix<LOGN>(reg, nl)], l, j > 0, s.eig[ka], s.eig[kb], p,
+                                 al, be, ga, invN2);
     }
     __syncthreads();
 }

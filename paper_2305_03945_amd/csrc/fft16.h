@@ -197,24 +197,28 @@ __device__ __forceinline__ void passes16(cplx<T> *x, int t, bool active, const T
 
 // ---- transforms whose first input and last output stay in registers
 //
-// Thread t of a transform holds its 16 values in "stride order": value r is
-// element t + r N/16.  That is what the first radix-16 pass reads (NS = 1,
+// Thread t of a transform holds its V values in "stride order": value r is
+// element t + r N/V.  That is what the first radix-V pass reads (NS = 1,
 // butterfly j = t) and, for the last pass of radix RL (NS = N/RL, butterflies
-// j = t + b N/16 with k = j), output q of butterfly b lands at
-// t + (b + q 16/RL) N/16, again element t + r N/16 with r = b + q 16/RL.  So a
+// j = t + b N/V with k = j), output q of butterfly b lands at
+// t + (b + q V/RL) N/V, again element t + r N/V with r = b + q V/RL.  So a
 // transform can start from values loaded straight from global memory and end
 // with values ready to be stored, with LDS used only between passes.
 
 // Radix of the last pass and the register index of its output (b, q).
-template <int LOGN> constexpr int last_radix() { return pass_radix<LOGN>(npasses16<LOGN>() - 1); }
-template <int LOGN> __host__ __device__ constexpr int last_slot(int b, int q) { return b + q * (16 / last_radix<LOGN>()); }
+template <int LOGN, int V = 16> constexpr int last_radix() {
+    return pass_radix<LOGN, V>(npasses16<LOGN, V>() - 1);
+}
+template <int LOGN, int V = 16> __host__ __device__ constexpr int last_slot(int b, int q) {
+    return b + q * (V / last_radix<LOGN, V>());
+}
 
-// Middle passes q = 1 .. npasses - 2 (all radix 16), each ending with a barrier.
-template <typename T, int LOGN, int DIR, int Q>
-__device__ __forceinline__ void middle_passes(cplx<T> *x, int t, const Tw16<T, LOGN> &w) {
-    if constexpr (Q < npasses16<LOGN>() - 1) {
-        pass16<T, LOGN, 16, (1 << (4 * Q)), DIR>(x, t, true, w.p[Q - 1]);
-        middle_passes<T, LOGN, DIR, Q + 1>(x, t, w);
+// Middle passes q = 1 .. npasses - 2 (all radix V), each ending with a barrier.
+template <typename T, int LOGN, int DIR, int Q, int V>
+__device__ __forceinline__ void middle_passes(cplx<T> *x, int t, const Tw16<T, LOGN, V> &w) {
+    if constexpr (Q < npasses16<LOGN, V>() - 1) {
+        pass16<T, LOGN, V, (1 << (logv<V>() * Q)), DIR, V>(x, t, true, w.p[Q - 1]);
+        middle_passes<T, LOGN, DIR, Q + 1, V>(x, t, w);
     }
 }
 
@@ -222,22 +226,22 @@ __device__ __forceinline__ void middle_passes(cplx<T> *x, int t, const Tw16<T, L
 // output is left in v (stride order).  Needs at least two passes.  Starts by
 // writing x (the caller makes sure no thread still reads it) and ends with the
 // last pass's reads of x (the caller places a barrier before x is rewritten).
-template <typename T, int LOGN, int DIR>
-__device__ __forceinline__ void fft16_regs(cplx<T> *x, int t, const Tw16<T, LOGN> &w, cplx<T> *v) {
-    static_assert(npasses16<LOGN>() >= 2, "register-ended transforms need two passes");
-    constexpr int NP = npasses16<LOGN>();
-    constexpr int RL = last_radix<LOGN>();
-    dft16<T, DIR>(v);
+template <typename T, int LOGN, int DIR, int V>
+__device__ __forceinline__ void fft16_regs(cplx<T> *x, int t, const Tw16<T, LOGN, V> &w, cplx<T> *v) {
+    static_assert(npasses16<LOGN, V>() >= 2, "register-ended transforms need two passes");
+    constexpr int NP = npasses16<LOGN, V>();
+    constexpr int RL = last_radix<LOGN, V>();
+    dftR<T, V, DIR>(v);
 #pragma unroll
-    for (int q = 0; q < 16; ++q) x[lds_pad(16 * t + q)] = v[q];
+    for (int q = 0; q < V; ++q) x[lds_pad(V * t + q)] = v[q];
     __syncthreads();
-    middle_passes<T, LOGN, DIR, 1>(x, t, w);
-    cplx<T> o[16 / RL][RL];
-    pass_in<T, LOGN, RL, (1 << (4 * (NP - 1))), DIR>(x, t, w.p[NP - 2], o);
+    middle_passes<T, LOGN, DIR, 1, V>(x, t, w);
+    cplx<T> o[V / RL][RL];
+    pass_in<T, LOGN, RL, (1 << (logv<V>() * (NP - 1))), DIR, V>(x, t, w.p[NP - 2], o);
 #pragma unroll
-    for (int b = 0; b < 16 / RL; ++b)
+    for (int b = 0; b < V / RL; ++b)
 #pragma unroll
-        for (int q = 0; q < RL; ++q) v[last_slot<LOGN>(b, q)] = o[b][q];
+        for (int q = 0; q < RL; ++q) v[last_slot<LOGN, V>(b, q)] = o[b][q];
 }
 
 // In-place transforms of NREG regions (region i at buf + i * lds_region<LOGN>(),

@@ -986,24 +986,32 @@ __global__ __launch_bounds__(NT) void k_row_forward(Slot *const *slots) {
 constexpr int COL_TEAM_PAD = 8;
 template <int LOGN> constexpr int col_region() { return lds_region<LOGN>() + COL_TEAM_PAD; }
 
+// Values per thread of a column transform: at most 512^2 leaves the chip short of
+// waves (512^2: 256 columns), and a pass takes one wave's serial chain; 8 values
+// per thread halve it.
+template <int LOGN> constexpr int col_values() { return LOGN <= 9 ? 8 : 16; }
+
 template <typename T, int LOGN, int C> constexpr int col_jobs() {
     constexpr int N = 1 << LOGN;
+    constexpr int V = col_values<LOGN>();
     constexpr int R = rows_per_block<T, LOGN, C>();
     constexpr int tile_bytes = R * (int)sizeof(cplx<T>);
     constexpr int by_tile = tile_bytes >= 64 ? 1 : 64 / tile_bytes;
-    constexpr int by_wave = (N / 16 >= 64) ? 1 : 64 / (N / 16);
+    constexpr int by_wave = (N / V >= 64) ? 1 : 64 / (N / V);
     constexpr int want = by_tile > by_wave ? by_tile : by_wave;
     // LDS (<= 156 KB, leaving room for the decision lanes) and threads (<= 1024)
     // bound it from above
     constexpr int by_lds = 159744 / (col_region<LOGN>() * (int)sizeof(cplx<T>));
-    constexpr int by_thr = 1024 / (N / 16 >= 1 ? N / 16 : 1);
+    constexpr int by_thr = 1024 / (N / V);
     constexpr int cap = by_lds < by_thr ? by_lds : by_thr;
     constexpr int cb0 = want < cap ? want : cap;
     constexpr int cb1 = cb0 < 1 ? 1 : (cb0 > N / 2 ? N / 2 : cb0);
     // a power of two, so that it divides N/2
     return cb1 >= 16 ? 16 : cb1 >= 8 ? 8 : cb1 >= 4 ? 4 : cb1 >= 2 ? 2 : 1;
 }
-template <typename T, int LOGN, int C> constexpr int col_threads() { return col_jobs<T, LOGN, C>() * ((1 << LOGN) / 16); }
+template <typename T, int LOGN, int C> constexpr int col_threads() {
+    return col_jobs<T, LOGN, C>() * ((1 << LOGN) / col_values<LOGN>());
+}
 // Register budget: two column workgroups must fit on one CU (four SIMDs), so that
 // the extra decision workgroup of a launch that fills every CU starts at once --
 // where their LDS fits twice in the CU's 160 KB; otherwise one.
@@ -1026,64 +1034,75 @@ template <typename T, int LOGN, int C> constexpr int col_waves_per_eu() {
 // region size (64 bytes in FP32: 16 banks).  At N = 2048 the column pass takes
 // 21 instead of 26 us (FP64) and 17.1 instead of 18.2 us (FP32).
 template <typename T, int LOGN, int C> constexpr bool cols_in_regs() {
-    constexpr int TPF = (1 << LOGN) / 16;
+    constexpr int V = col_values<LOGN>();
+    constexpr int TPF = (1 << LOGN) / V;
     constexpr int R = rows_per_block<T, LOGN, C>();
-    return npasses16<LOGN>() >= 2 && TPF >= R && TPF % R == 0;
+    return npasses16<LOGN, V>() >= 2 && TPF >= R && TPF % R == 0;
 }
 
 template <typename T, int LOGN, int C, int CB>
 __device__ __forceinline__ void cols_regs(SlotRef s, int c, int kx0, const cplx<T> *S, cplx<T> *S2, cplx<T> *buf) {
-    constexpr int N = 1 << LOGN, H = N / 2, TPF = N / 16;
+    constexpr int V = col_values<LOGN>();
+    constexpr int N = 1 << LOGN, H = N / 2, TPF = N / V;
     constexpr int R = rows_per_block<T, LOGN, C>();
+    // with 8 values there is room to keep the twiddles and to read the eigenvalues
+    // ahead; with 16 they are read again where they are used
+    constexpr bool KEEP = V == 8;
     typedef T v2_t __attribute__((ext_vector_type(2)));
     const int idx = threadIdx.x;
     const int team = (idx / R) % CB;
     const int t = (idx / (R * CB)) * R + idx % R;
     const int kx = kx0 + team;
     cplx<T> *x = buf + team * col_region<LOGN>();
-    // element t + r N/16 of the column sits r * (N/16) * (N/2) slots after element t
+    // element t + r N/V of the column sits r * (N/V) * (N/2) slots after element t
     const int o0 = (int)spec_off<R>(c, t, kx, N);
     constexpr int STRIDE = TPF * H;
-    cplx<T> v[16];
+    cplx<T> v[V];
     {
         const auto Sg = gp((const v2_t *)S);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
+        for (int r = 0; r < V; ++r) {
             const v2_t a = Sg[o0 + r * STRIDE];
             v[r] = {a[0], a[1]};
         }
     }
-    {
-        Tw16<T, LOGN> twr;
-        load_tw16<T, LOGN>(twr, (const cplx<T> *)s.tw, t);
-        fft16_regs<T, LOGN, -1>(x, t, twr, v);
+    const double ex = s.eig[kx];
+    double ey[V];
+    if constexpr (KEEP) {
+#pragma unroll
+        for (int r = 0; r < V; ++r) ey[r] = s.eig[t + r * TPF];
     }
+    Tw16<T, LOGN, V> twr;
+    load_tw16<T, LOGN, V>(twr, (const cplx<T> *)s.tw, t);
+    fft16_regs<T, LOGN, -1, V>(x, t, twr, v);
     {
         const double al = s.alpha[c], be = s.beta[c], ga = s.gamma[c];
         const double invN2 = 1.0 / ((double)N * (double)N);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const T m = (T)symbol_mult(s.eig, kx, t + r * TPF, al, be, ga, invN2);
+        for (int r = 0; r < V; ++r) {
+            const T m = (T)symbol_of(ex + (KEEP ? ey[r] : s.eig[t + r * TPF]), al, be, ga, invN2);
             v[r] = {v[r].re * m, v[r].im * m};
         }
     }
     __syncthreads();   // the last forward pass has read x
-    // gather the twiddles again rather than keeping them live across the symbol,
-    // and recompute the LDS addresses of the inverse passes rather than keeping the
-    // forward ones (an empty asm hides that t is unchanged; without it the FP32
-    // pass spills them)
-    __asm__ volatile("" ::: "memory");
-    {
+    if constexpr (KEEP) {
+        fft16_regs<T, LOGN, +1, V>(x, t, twr, v);
+    } else {
+        // gather the twiddles again rather than keeping them live across the symbol,
+        // and recompute the LDS addresses of the inverse passes rather than keeping the
+        // forward ones (an empty asm hides that t is unchanged; without it the FP32
+        // pass spills them)
+        __asm__ volatile("" ::: "memory");
         int t2 = t;
         __asm__ volatile("" : "+v"(t2));
         cplx<T> *x2 = buf + ((threadIdx.x / R) % CB) * col_region<LOGN>();
-        Tw16<T, LOGN> twr;
-        load_tw16<T, LOGN>(twr, (const cplx<T> *)s.tw, t2);
-        fft16_regs<T, LOGN, +1>(x2, t2, twr, v);
+        Tw16<T, LOGN, V> twi;
+        load_tw16<T, LOGN, V>(twi, (const cplx<T> *)s.tw, t2);
+        fft16_regs<T, LOGN, +1, V>(x2, t2, twi, v);
     }
     const auto So = gp((v2_t *)S2);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
+    for (int r = 0; r < V; ++r) {
         v2_t a;
         a[0] = v[r].re;
         a[1] = v[r].im;
@@ -1151,21 +1170,36 @@ __global__ __launch_bounds__((col_threads<T, LOGN, C>()), (col_waves_per_eu<T, L
             }
         }
     }
-    __syncthreads();
     const cplx<T> *twd = (const cplx<T> *)s.twd;
-    {
-        Tw16<T, LOGN> twr;
-        load_tw16<T, LOGN>(twr, (const cplx<T> *)s.tw);
-        wg_fft16<T, LOGN, -1, CB, NTH>(buf, twr);
-    }
-    cols_apply_symbol<T, LOGN, BC, CB, NTH>(buf, c * H + kx0, CB, s, twd);
-    // the inverse transform gathers its twiddles again rather than keeping the
-    // forward ones live across the symbol pass (register budget)
-    __asm__ volatile("" ::: "memory");
-    {
-        Tw16<T, LOGN> twr;
-        load_tw16<T, LOGN>(twr, (const cplx<T> *)s.tw);
-        wg_fft16<T, LOGN, +1, CB, NTH>(buf, twr);
+    constexpr int V = col_values<LOGN>();
+    if constexpr (V == 8) {
+        // everything else the pass reads is loaded beside the spectrum
+        constexpr int IPT = pair_items_per_thread<LOGN, CB, NTH>();
+        Tw16<T, LOGN, V> twr;
+        load_tw16<T, LOGN, V>(twr, (const cplx<T> *)s.tw);
+        SymPair<T> pre[IPT];
+#pragma unroll
+        for (int i = 0; i < IPT; ++i) pre[i] = load_sym_pair<T, LOGN, BC>(s.eig, twd, (threadIdx.x + i * NTH) % H);
+        __syncthreads();
+        wg_fft16<T, LOGN, -1, CB, NTH, V>(buf, twr);
+        cols_apply_symbol<T, LOGN, BC, CB, NTH>(buf, c * H + kx0, CB, s, twd, pre);
+        wg_fft16<T, LOGN, +1, CB, NTH, V>(buf, twr);
+    } else {
+        __syncthreads();
+        {
+            Tw16<T, LOGN> twr;
+            load_tw16<T, LOGN>(twr, (const cplx<T> *)s.tw);
+            wg_fft16<T, LOGN, -1, CB, NTH>(buf, twr);
+        }
+        cols_apply_symbol<T, LOGN, BC, CB, NTH>(buf, c * H + kx0, CB, s, twd, nullptr);
+        // the inverse transform gathers its twiddles again rather than keeping the
+        // forward ones live across the symbol pass (register budget)
+        __asm__ volatile("" ::: "memory");
+        {
+            Tw16<T, LOGN> twr;
+            load_tw16<T, LOGN>(twr, (const cplx<T> *)s.tw);
+            wg_fft16<T, LOGN, +1, CB, NTH>(buf, twr);
+        }
     }
 #pragma unroll
     for (int i = 0; i < (TOT + NTH - 1) / NTH; ++i) {

@@ -532,9 +532,7 @@ template <typename T, int LOGN> constexpr int line_threads() {
 // Symbol of the 3-D preconditioner: 1 / (N^3 g), mu = s_kx + s_ky + s_kz.
 __device__ __forceinline__ double symbol3(const double *__restrict__ eig, int kx, int ky, int kz, double al,
                                           double be, double ga, double invN3) {
-    const double mu = eig[kx] + eig[ky] + eig[kz];
-    const double a = 1.0 + mu * (al + mu * (be + ga * mu));
-    return invN3 / (a * a);
+    return symbol_of(eig[kx] + eig[ky] + eig[kz], al, be, ga, invN3);
 }
 
 // The z-pass between its forward and inverse transforms: multiply every z-line by
@@ -561,7 +559,6 @@ __device__ __forceinline__ void lines_apply_symbol3(cplx<T> *buf, int c, int q, 
         const int nl = (l == 0) ? H : N - l;
         cplx<T> &zlr = buf[rix<LOGN>(reg, l)];
         cplx<T> &znr = buf[rix<LOGN>(reg, nl)];
-        const cplx<T> zl = zlr, zn = znr;
         // (kx, ky) of the re and im sequences; plain: one complex sequence (a only)
         bool plain;
         int kxa, kya, kxb = 0, kyb = 0;
@@ -587,49 +584,8 @@ __device__ __forceinline__ void lines_apply_symbol3(cplx<T> *buf, int c, int q, 
             kya = 2 * qq;
             kyb = 2 * qq + 1;
         }
-        if constexpr (BC == BC_P) {
-            if (plain) {
-                const T m1 = (T)symbol3(s.eig, kxa, kya, l, al, be, ga, invN3);
-                const T m2 = (T)symbol3(s.eig, kxa, kya, nl, al, be, ga, invN3);
-                zlr = {zl.re * m1, zl.im * m1};
-                znr = {zn.re * m2, zn.im * m2};
-            } else if (l == 0) {
-                zlr = {zl.re * (T)symbol3(s.eig, kxa, kya, 0, al, be, ga, invN3),
-                       zl.im * (T)symbol3(s.eig, kxb, kyb, 0, al, be, ga, invN3)};
-                znr = {zn.re * (T)symbol3(s.eig, kxa, kya, H, al, be, ga, invN3),
-                       zn.im * (T)symbol3(s.eig, kxb, kyb, H, al, be, ga, invN3)};
-            } else {
-                const T ma = (T)symbol3(s.eig, kxa, kya, l, al, be, ga, invN3);
-                const T mb = (T)symbol3(s.eig, kxb, kyb, l, al, be, ga, invN3);
-                cplx<T> A = {(zl.re + zn.re) * (T)0.5, (zl.im - zn.im) * (T)0.5};
-                cplx<T> B = {(zl.im + zn.im) * (T)0.5, (zn.re - zl.re) * (T)0.5};
-                A = {A.re * ma, A.im * ma};
-                B = {B.re * mb, B.im * mb};
-                zlr = {A.re - B.im, A.im + B.re};
-                znr = {A.re + B.im, B.re - A.im};
-            }
-        } else {
-            if (l == 0) {
-                zlr = {zl.re * (T)symbol3(s.eig, kxa, kya, 0, al, be, ga, invN3),
-                       zl.im * (T)symbol3(s.eig, kxb, kyb, 0, al, be, ga, invN3)};
-                znr = {zn.re * (T)symbol3(s.eig, kxa, kya, H, al, be, ga, invN3),
-                       zn.im * (T)symbol3(s.eig, kxb, kyb, H, al, be, ga, invN3)};
-            } else {
-                const cplx<T> w = twd[l];
-                const cplx<T> A = {(zl.re + zn.re) * (T)0.5, (zl.im - zn.im) * (T)0.5};
-                const cplx<T> B = {(zl.im + zn.im) * (T)0.5, (zn.re - zl.re) * (T)0.5};
-                const cplx<T> qa = cmul(A, w), qb = cmul(B, w);
-                const T xal = qa.re * (T)symbol3(s.eig, kxa, kya, l, al, be, ga, invN3);
-                const T xan = -qa.im * (T)symbol3(s.eig, kxa, kya, N - l, al, be, ga, invN3);
-                const T xbl = qb.re * (T)symbol3(s.eig, kxb, kyb, l, al, be, ga, invN3);
-                const T xbn = -qb.im * (T)symbol3(s.eig, kxb, kyb, N - l, al, be, ga, invN3);
-                const cplx<T> wc = cconj(w);
-                const cplx<T> va = cmul(wc, cplx<T>{xal, -xan});
-                const cplx<T> vb = cmul(wc, cplx<T>{xbl, -xbn});
-                zlr = {va.re - vb.im, va.im + vb.re};
-                znr = {va.re + vb.im, vb.re - va.im};
-            }
-        }
+        apply_symbol_pair<T, BC>(zlr, znr, l, plain, s.eig[kxa] + s.eig[kya], s.eig[kxb] + s.eig[kyb],
+                                 load_sym_pair<T, LOGN, BC>(s.eig, twd, l), al, be, ga, invN3);
     }
     __syncthreads();
 }

@@ -211,51 +211,9 @@ __device__ __forceinline__ void cols_symbol_mapped(cplx<T> *buf, SlotRef s, cons
         const int nl = (l == 0) ? H : N - l;
         cplx<T> &zlr = buf[M::at(reg, l)];
         cplx<T> &znr = buf[M::at(reg, nl)];
-        const cplx<T> zl = zlr, zn = znr;
-        if constexpr (BC == BC_P) {
-            if (j > 0) {
-                const T m1 = (T)symbol_mult(eig, j, l, al, be, ga, invN2);
-                const T m2 = (T)symbol_mult(eig, j, nl, al, be, ga, invN2);
-                zlr = {zl.re * m1, zl.im * m1};
-                znr = {zn.re * m2, zn.im * m2};
-            } else if (l == 0) {
-                zlr = {zl.re * (T)symbol_mult(eig, 0, 0, al, be, ga, invN2),
-                       zl.im * (T)symbol_mult(eig, H, 0, al, be, ga, invN2)};
-                znr = {zn.re * (T)symbol_mult(eig, 0, H, al, be, ga, invN2),
-                       zn.im * (T)symbol_mult(eig, H, H, al, be, ga, invN2)};
-            } else {
-                const T ma = (T)symbol_mult(eig, 0, l, al, be, ga, invN2);
-                const T mb = (T)symbol_mult(eig, H, l, al, be, ga, invN2);
-                cplx<T> A = {(zl.re + zn.re) * (T)0.5, (zl.im - zn.im) * (T)0.5};
-                cplx<T> B = {(zl.im + zn.im) * (T)0.5, (zn.re - zl.re) * (T)0.5};
-                A = {A.re * ma, A.im * ma};
-                B = {B.re * mb, B.im * mb};
-                zlr = {A.re - B.im, A.im + B.re};
-                znr = {A.re + B.im, B.re - A.im};
-            }
-        } else {
-            const int ka = 2 * j, kb = 2 * j + 1;
-            if (l == 0) {
-                zlr = {zl.re * (T)symbol_mult(eig, ka, 0, al, be, ga, invN2),
-                       zl.im * (T)symbol_mult(eig, kb, 0, al, be, ga, invN2)};
-                znr = {zn.re * (T)symbol_mult(eig, ka, H, al, be, ga, invN2),
-                       zn.im * (T)symbol_mult(eig, kb, H, al, be, ga, invN2)};
-            } else {
-                const cplx<T> w = twd[l];
-                const cplx<T> A = {(zl.re + zn.re) * (T)0.5, (zl.im - zn.im) * (T)0.5};
-                const cplx<T> B = {(zl.im + zn.im) * (T)0.5, (zn.re - zl.re) * (T)0.5};
-                const cplx<T> qa = cmul(A, w), qb = cmul(B, w);
-                const T xal = qa.re * (T)symbol_mult(eig, ka, l, al, be, ga, invN2);
-                const T xan = -qa.im * (T)symbol_mult(eig, ka, N - l, al, be, ga, invN2);
-                const T xbl = qb.re * (T)symbol_mult(eig, kb, l, al, be, ga, invN2);
-                const T xbn = -qb.im * (T)symbol_mult(eig, kb, N - l, al, be, ga, invN2);
-                const cplx<T> wc = cconj(w);
-                const cplx<T> va = cmul(wc, cplx<T>{xal, -xan});
-                const cplx<T> vb = cmul(wc, cplx<T>{xbl, -xbn});
-                zlr = {va.re - vb.im, va.im + vb.re};
-                znr = {va.re + vb.im, vb.re - va.im};
-            }
-        }
+        const int ka = BC == BC_P ? j : 2 * j, kb = BC == BC_P ? H : 2 * j + 1;
+        apply_symbol_pair<T, BC>(zlr, znr, l, j > 0, eig[ka], eig[kb], load_sym_pair<T, LOGN, BC>(eig, twd, l), al,
+                                 be, ga, invN2);
     }
     __syncthreads();
 }
