@@ -355,11 +355,17 @@ template <typename T, int LOGN, int EQ> struct RowsPlan {
     static constexpr int RP = R + 4 * HY;        // rows of P~
     static constexpr int NRI = C * RP / 2;       // inverse transforms (row pairs)
     static constexpr int NRF = C * R / 2;        // forward transforms
-    static constexpr int V = LOGN <= 9 ? 8 : 16; // values per thread of a transform
+    // values per thread of a transform: 8 while 512 threads then run every inverse
+    // transform at once (1024^2 mixed Allen-Cahn step 647 -> 605 us), 16 above
+    // (2048^2 mixed: 1.39 against 1.43 ms with 8)
+    static constexpr int V = NRI * N / 8 <= 512 ? 8 : 16;
     static constexpr int TPF = N / V;
-    static constexpr int want = NRI * TPF;
-    static constexpr int NTH = want <= 256 ? 256 : 512;
+    static constexpr int NTH = NRI * TPF <= 256 ? 256 : 512;
     static constexpr size_t lds = (size_t)NRI * lds_region<LOGN>() * sizeof(cplx<T>);
+    // FP32 2048^2, 5-point stencil: 128 registers, so that two workgroups share a CU and
+    // one's loads run beside the other's transforms (k_rows 39.7 -> 35 us); the others
+    // would spill, or have one workgroup per CU by their LDS
+    static constexpr int WPE = sizeof(T) == 4 && LOGN == 11 && C == 1 && HY == 1 ? 4 : 1;
     // points per thread of the primal update and of the residual
     static constexpr int QU = RU * N / 4 >= NTH ? 4 : RU * N / 2 >= NTH ? 2 : 1;
     static constexpr int QW = R / 2 * N / 4 >= NTH ? 4 : R / 2 * N / 2 >= NTH ? 2 : 1;
@@ -367,7 +373,8 @@ template <typename T, int LOGN, int EQ> struct RowsPlan {
 
 // Whether the fused row pass serves (T, N, equation): its LDS fits.
 template <typename T, int LOGN, int EQ> constexpr bool rows_fused() {
-    return RowsPlan<T, LOGN, EQ>::lds + 1024 <= 163840 && RowsPlan<T, LOGN, EQ>::N >= RowsPlan<T, LOGN, EQ>::RP;
+    return RowsPlan<T, LOGN, EQ>::lds + 1024 <= 163840 && RowsPlan<T, LOGN, EQ>::N >= RowsPlan<T, LOGN, EQ>::RP &&
+           !(EQ == EQ_FCH && LOGN > 10);
 }
 
 // ---------------------------------------------------------------- deterministic block sums

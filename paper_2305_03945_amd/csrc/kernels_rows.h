@@ -350,7 +350,7 @@ __device__ __forceinline__ void rows_iteration(SlotRef s, StateRef sst, cplx<T> 
 // One iteration's row-parallel steps; mixed: the FP64 outer update instead once
 // the inner loop has stopped (K_MIXED of k_row_forward).
 template <typename T, int LOGN, int BC, int EQ>
-__global__ __launch_bounds__((RowsPlan<T, LOGN, EQ>::NTH)) void k_rows(Slot *const *slots) {
+__global__ __launch_bounds__((RowsPlan<T, LOGN, EQ>::NTH), (RowsPlan<T, LOGN, EQ>::WPE)) void k_rows(Slot *const *slots) {
     using Pl = RowsPlan<T, LOGN, EQ>;
     __shared__ cplx<T> buf[Pl::NRI * lds_region<LOGN>()];
     __shared__ double scratch[2 * Pl::C * (Pl::NTH / 64)];

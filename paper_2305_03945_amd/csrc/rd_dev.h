@@ -42,18 +42,15 @@ template <typename X> __device__ __forceinline__ X ld_agent(const X *p) {
 struct StateV {
     int done, iters, outer, outer_done;
 };
-// The four fields that select what a launch does, read once per workgroup (two
-// 8-byte loads by thread 0; one request per workgroup rather than per wave keeps
+// The four fields that select what a launch does, read once per workgroup (one
+// 8-byte load by each of two threads; one request per workgroup rather than per wave keeps
 // the thousands of workgroups of a launch from queueing on the one line) and
 // handed to every thread through LDS.  Called by every thread of the workgroup,
 // before any thread leaves the kernel.
 __device__ __forceinline__ StateV state_of(SlotRef s) {
     __shared__ unsigned long long sh_state[2];
-    if (threadIdx.x == 0) {
-        const unsigned long long *p = (const unsigned long long *)s.st;
-        sh_state[0] = ld_agent(p);
-        sh_state[1] = ld_agent(p + 1);
-    }
+    // one lane per word: one latency (a lane's second load would wait for its first)
+    if (threadIdx.x < 2) sh_state[threadIdx.x] = ld_agent((const unsigned long long *)s.st + threadIdx.x);
     __syncthreads();
     const unsigned long long a = sh_state[0], b = sh_state[1];
     StateV v;
