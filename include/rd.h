@@ -290,9 +290,12 @@ rd_status rd_poll(rd_ctx *ctx, uint64_t ticket, rd_info *info);
  * that ended RD_OK by the end of any serving round in flight, which the copy waits for
  * (the initial state if none has).  Synchronises.                                       */
 rd_status rd_traj_read(rd_traj *traj, double *u_out, void *hip_stream);
-/* Close a trajectory: waits for the device, releases its workspace (returning its bytes
- * to the budget), its resident state and its tickets: rd_poll then returns RD_E_INVALID
- * for every ticket of it, finished or not (unfinished steps are dropped).                */
+/* Close a trajectory: waits for its group's round in flight, releases its workspace
+ * (returning its bytes to the budget), its resident state and its tickets: rd_poll then
+ * returns RD_E_INVALID for every ticket of it, finished or not (unfinished steps are
+ * dropped).  The context keeps released memory for later trajectories of the same shape,
+ * at most 256 MiB and, with a budget, at most what the budget leaves beside the admitted
+ * workspaces; rd_destroy frees it.                                                        */
 rd_status rd_traj_close(rd_traj *traj);
 
 typedef struct {

@@ -15,6 +15,8 @@
 #include <mutex>
 #include <thread>
 #include <tuple>
+#include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "../../include/rd.h"
@@ -130,11 +132,11 @@ struct Workspace {
     int N = 0, C = 0, mode = 0, logN = 0, nblk = 0, dim = 2;
     size_t pts = 0;
     size_t bytes = 0;
-    std::vector<void *> allocs;
+    void *slab = nullptr;         // one device allocation, every buffer below carved from it
     Slot *slot_dev = nullptr;     // device copy of the slot
     Slot **slot_list_dev = nullptr; // device array {slot_dev}
-    Slot *slot_host = nullptr;    // pinned staging
-    State *st_host = nullptr;     // pinned readback
+    Slot *slot_host = nullptr;    // pinned staging, and in the same allocation
+    State *st_host = nullptr;     // the pinned readback
     Slot proto{};                 // pointers filled at allocation
     // iteration launches the last two steps on this workspace used (FP64: their
     // iterations; mixed: their inner iterations plus one per outer update)
@@ -180,6 +182,7 @@ size_t workspace_bytes(size_t pts, int rows, int C, int mode, int rows_per_block
         b += 2 * field_bytes(N, C, 4);   // r32, Ub32
         b += 3 * field_bytes(N, C, 8);   // U64[2], Uk
     }
+    // the small buffers, and each buffer's rounding up to 256 bytes
     b += nblk * 2 * C * sizeof(double) + sizeof(State) + sizeof(Slot) + sizeof(Slot *) + 4096;
     return b;
 }
@@ -237,6 +240,10 @@ struct Ctx {
     std::deque<Traj *> admit_queue;
     std::map<std::pair<GroupKey, int>, BatchBuffers> batch;
     std::map<GroupKey, GroupRound> rounds;
+    // memory of closed trajectories, kept for later ones (see SPARE_LIMIT)
+    std::vector<std::unique_ptr<Workspace>> spare_ws;
+    std::vector<std::pair<size_t, double *>> spare_states;
+    size_t spare_bytes = 0;
 };
 
 struct PendingStep {
@@ -259,22 +266,19 @@ struct Traj {
     bool queued_for_admission = false;
 };
 
-rd_status dmalloc(Workspace &w, void **p, size_t bytes) {
-    if (hipMalloc(p, bytes) != hipSuccess) return RD_E_NOMEM;
-    w.allocs.push_back(*p);
-    return RD_OK;
-}
-
 void free_workspace(Workspace *w) {
     if (!w) return;
-    for (void *p : w->allocs) (void)hipFree(p);
-    w->allocs.clear();
+    if (w->slab) (void)hipFree(w->slab);
     if (w->slot_host) (void)hipHostFree(w->slot_host);
-    if (w->st_host) (void)hipHostFree(w->st_host);
+    w->slab = nullptr;
     w->slot_host = nullptr;
     w->st_host = nullptr;
 }
 
+constexpr size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// One device and one pinned allocation per workspace: an allocation costs tens of
+// microseconds, and a served trajectory pays for its workspace before its first step.
 rd_status make_workspace(const Desc &d, int mode, std::unique_ptr<Workspace> &out) {
     auto w = std::make_unique<Workspace>();
     const int C = d.C;
@@ -291,39 +295,43 @@ rd_status make_workspace(const Desc &d, int mode, std::unique_ptr<Workspace> &ou
     w->bytes = workspace_bytes(d.pts, d.rows, C, mode, k.rows_per_block);
     Slot &s = w->proto;
     std::memset(&s, 0, sizeof(Slot));
-    rd_status r;
-    const size_t te = mode == MODE_F64 ? 8 : 4;
-#define ALLOC(ptr, bytes)                                          \
-    do {                                                           \
-        void *p_ = nullptr;                                        \
-        if ((r = dmalloc(*w, &p_, (bytes))) != RD_OK) {            \
-            free_workspace(w.get());                               \
-            return r;                                              \
-        }                                                          \
-        ptr = decltype(ptr)(p_);                                   \
-    } while (0)
-    ALLOC(s.U[0], field_bytes(N, C, te));
-    ALLOC(s.U[1], field_bytes(N, C, te));
-    ALLOC(s.P, field_bytes(N, C, te));
-    ALLOC(s.Pt, field_bytes(N, C, te));
-    ALLOC(s.S, field_bytes(N, C, te));
-    ALLOC(s.Uk, field_bytes(N, C, 8));
-    if (mode == MODE_MIXED) {
-        ALLOC(s.U64[0], field_bytes(N, C, 8));
-        ALLOC(s.U64[1], field_bytes(N, C, 8));
-        ALLOC(s.r32, field_bytes(N, C, 4));
-        ALLOC(s.Ub32, field_bytes(N, C, 4));
+    if (hipMalloc(&w->slab, w->bytes) != hipSuccess) {
+        w->slab = nullptr;
+        return RD_E_NOMEM;
     }
-    ALLOC(s.partials, (size_t)w->nblk * 2 * C * sizeof(double));
-    ALLOC(s.st, sizeof(State));
-    ALLOC(w->slot_dev, sizeof(Slot));
-    ALLOC(w->slot_list_dev, sizeof(Slot *));
-#undef ALLOC
-    if (hipHostMalloc((void **)&w->slot_host, sizeof(Slot), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void **)&w->st_host, sizeof(State), hipHostMallocDefault) != hipSuccess) {
+    size_t off = 0;
+    auto take = [&](auto *&ptr, size_t bytes) {
+        ptr = (std::remove_reference_t<decltype(ptr)>)((char *)w->slab + off);
+        off = align256(off + bytes);
+    };
+    const size_t te = mode == MODE_F64 ? 8 : 4;
+    take(s.U[0], field_bytes(N, C, te));
+    take(s.U[1], field_bytes(N, C, te));
+    take(s.P, field_bytes(N, C, te));
+    take(s.Pt, field_bytes(N, C, te));
+    take(s.S, field_bytes(N, C, te));
+    take(s.Uk, field_bytes(N, C, 8));
+    if (mode == MODE_MIXED) {
+        take(s.U64[0], field_bytes(N, C, 8));
+        take(s.U64[1], field_bytes(N, C, 8));
+        take(s.r32, field_bytes(N, C, 4));
+        take(s.Ub32, field_bytes(N, C, 4));
+    }
+    take(s.partials, (size_t)w->nblk * 2 * C * sizeof(double));
+    take(s.st, sizeof(State));
+    take(w->slot_dev, sizeof(Slot));
+    take(w->slot_list_dev, sizeof(Slot *));
+    if (off > w->bytes) {   // workspace_bytes counts every buffer above
+        free_workspace(w.get());
+        return RD_E_DEVICE;
+    }
+    const size_t st_off = align256(sizeof(Slot));
+    if (hipHostMalloc((void **)&w->slot_host, st_off + sizeof(State), hipHostMallocDefault) != hipSuccess) {
+        w->slot_host = nullptr;
         free_workspace(w.get());
         return RD_E_NOMEM;
     }
+    w->st_host = (State *)((char *)w->slot_host + st_off);
     if (hipMemset(s.st, 0, sizeof(State)) != hipSuccess ||
         hipMemcpy(w->slot_list_dev, &w->slot_dev, sizeof(Slot *), hipMemcpyHostToDevice) != hipSuccess) {
         free_workspace(w.get());
@@ -331,6 +339,85 @@ rd_status make_workspace(const Desc &d, int mode, std::unique_ptr<Workspace> &ou
     }
     out = std::move(w);
     return RD_OK;
+}
+
+// ---------------------------------------------------------------- spare memory of closed trajectories
+// Short-lived trajectories come and go in a serving stream; a context keeps the
+// workspaces and resident states of closed ones for later ones of the same shape, up to
+// SPARE_LIMIT bytes (with a budget, only what the budget leaves beside the admitted
+// workspaces), and gives them back when memory runs short and when it is destroyed.
+// Whoever gives memory here has waited for the work that used it.
+constexpr size_t SPARE_LIMIT = (size_t)256 << 20;
+
+void trim_spares(Ctx *c, size_t limit) {
+    while (c->spare_bytes > limit && !c->spare_ws.empty()) {
+        Workspace *w = c->spare_ws.front().get();
+        c->spare_bytes -= w->bytes;
+        free_workspace(w);
+        c->spare_ws.erase(c->spare_ws.begin());
+    }
+    while (c->spare_bytes > limit && !c->spare_states.empty()) {
+        c->spare_bytes -= c->spare_states.front().first;
+        (void)hipFree(c->spare_states.front().second);
+        c->spare_states.erase(c->spare_states.begin());
+    }
+}
+
+size_t spare_limit(const Ctx *c) {
+    if (!c->budget) return SPARE_LIMIT;
+    return std::min(SPARE_LIMIT, c->budget > c->resident ? c->budget - c->resident : 0);
+}
+
+rd_status take_workspace(Ctx *c, const Desc &d, int mode, std::unique_ptr<Workspace> &out) {
+    for (auto it = c->spare_ws.begin(); it != c->spare_ws.end(); ++it) {
+        Workspace &w = **it;
+        if (w.N != d.N || w.C != d.C || w.mode != mode || w.dim != d.dim) continue;
+        // another trajectory's lengths say nothing about this one
+        w.last_iters = w.prev_iters = 0;
+        w.last_parity = -1;
+        c->spare_bytes -= w.bytes;
+        out = std::move(*it);
+        c->spare_ws.erase(it);
+        return RD_OK;
+    }
+    rd_status r = make_workspace(d, mode, out);
+    if (r == RD_E_NOMEM && c->spare_bytes > 0) {
+        trim_spares(c, 0);
+        r = make_workspace(d, mode, out);
+    }
+    return r;
+}
+
+void give_workspace(Ctx *c, std::unique_ptr<Workspace> w) {
+    if (c->spare_bytes + w->bytes > spare_limit(c)) {
+        free_workspace(w.get());
+        return;
+    }
+    c->spare_bytes += w->bytes;
+    c->spare_ws.push_back(std::move(w));
+}
+
+double *take_state(Ctx *c, size_t bytes) {
+    for (auto it = c->spare_states.begin(); it != c->spare_states.end(); ++it) {
+        if (it->first != bytes) continue;
+        double *u = it->second;
+        c->spare_bytes -= bytes;
+        c->spare_states.erase(it);
+        return u;
+    }
+    double *u = nullptr;
+    if (hipMalloc((void **)&u, bytes) == hipSuccess) return u;
+    trim_spares(c, 0);
+    return hipMalloc((void **)&u, bytes) == hipSuccess ? u : nullptr;
+}
+
+void give_state(Ctx *c, double *u, size_t bytes) {
+    if (c->spare_bytes + bytes > spare_limit(c)) {
+        (void)hipFree(u);
+        return;
+    }
+    c->spare_bytes += bytes;
+    c->spare_states.emplace_back(bytes, u);
 }
 
 // eig: N doubles; tw, twd: 2N doubles (complex, re/im interleaved).
@@ -602,8 +689,6 @@ rd_status noalloc_setup(int device) {
     return RD_OK;
 }
 
-size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
-
 }  // namespace
 
 // ====================================================================== C ABI
@@ -668,6 +753,7 @@ rd_status rd_destroy(rd_ctx *ctx) {
         if (t->u) (void)hipFree(t->u);
         delete t;
     }
+    trim_spares(c, 0);
     for (auto &kv : c->step_ws) free_workspace(kv.second.get());
     for (auto &kv : c->tables) {
         (void)hipFree(kv.second.eig);
@@ -1150,7 +1236,10 @@ rd_status rd_prox(rd_ctx *ctx, const rd_problem *prob, double h_t, const double 
 // ---------------------------------------------------------------- serving
 rd_status rd_serve_set_budget(rd_ctx *ctx, size_t bytes) {
     if (!ctx) return RD_E_INVALID;
-    ((Ctx *)ctx)->budget = bytes;
+    Ctx *c = (Ctx *)ctx;
+    RD_CHECK(hipSetDevice(c->device));
+    c->budget = bytes;
+    trim_spares(c, spare_limit(c));
     return RD_OK;
 }
 
@@ -1174,7 +1263,7 @@ rd_status rd_traj_open(rd_ctx *ctx, const rd_problem *prob, const rd_opts *opts,
         return RD_E_INVALID;
     }
     const size_t fb = field_bytes(d.pts, d.C, 8);
-    if (hipMalloc((void **)&t->u, fb) != hipSuccess) {
+    if (!(t->u = take_state(c, fb))) {
         delete t;
         return RD_E_NOMEM;
     }
@@ -1375,11 +1464,12 @@ rd_status rd_serve_pump(rd_ctx *ctx, int32_t max_wait_us) {
                                             kset(t->d.mode, t->d).rows_per_block);
         if (c->budget && c->resident + need > c->budget && c->resident > 0) break;
         std::unique_ptr<Workspace> w;
-        r = make_workspace(t->d, t->d.mode, w);
+        r = take_workspace(c, t->d, t->d.mode, w);
         if (r == RD_E_NOMEM && c->resident > 0) break;
         if (r != RD_OK) return r;
         t->ws = std::move(w);
         c->resident += need;
+        trim_spares(c, spare_limit(c));
         c->admit_queue.pop_front();
         t->queued_for_admission = false;
     }
@@ -1454,14 +1544,16 @@ rd_status rd_traj_close(rd_traj *traj) {
     Traj *t = (Traj *)traj;
     Ctx *c = t->ctx;
     (void)hipSetDevice(c->device);
-    (void)hipDeviceSynchronize();
-    // every round has completed: retire them, so that none refers to t afterwards
-    for (auto &kv : c->rounds)
-        if (kv.second.in_flight) retire_round(c, kv.second);
+    // everything that uses t's memory is on its group's stream (copies to and from the
+    // caller have been waited for): wait for it, and retire the round it may be in
+    auto g = c->rounds.find(GroupKey{t->d.mode, t->d.logN, t->d.bc, t->d.eq, t->d.dim});
+    if (g != c->rounds.end() && g->second.stream) {
+        (void)hipStreamSynchronize(g->second.stream);
+        if (g->second.in_flight) retire_round(c, g->second);
+    }
     if (t->ws) {
         c->resident -= std::min(c->resident, t->ws->bytes);
-        free_workspace(t->ws.get());
-        t->ws.reset();
+        give_workspace(c, std::move(t->ws));
     }
     for (size_t i = 0; i < c->admit_queue.size(); ++i)
         if (c->admit_queue[i] == t) {
@@ -1476,7 +1568,7 @@ rd_status rd_traj_close(rd_traj *traj) {
     // its tickets, finished or not, become unknown: no poll waits on a step that will
     // never run, and the ticket table holds the open trajectories' steps only
     for (uint64_t id : t->tickets) c->tickets.erase(id);
-    if (t->u) (void)hipFree(t->u);
+    give_state(c, t->u, field_bytes(t->d.pts, t->d.C, 8));
     delete t;
     return RD_OK;
 }
