@@ -31,48 +31,6 @@ template <typename T, int DIR> __device__ __forceinline__ cplx<T> rot90(cplx<T> 
     return DIR < 0 ? cplx<T>{a.im, -a.re} : cplx<T>{-a.im, a.re};
 }
 
-template <typename T, int DIR> __device__ __forceinline__ void dft2(cplx<T> *v) {
-    cplx<T> a = v[0], b = v[1];
-    v[0] = cadd(a, b);
-    v[1] = csub(a, b);
-}
-
-template <typename T, int DIR> __device__ __forceinline__ void dft4(cplx<T> *v) {
-    cplx<T> t0 = cadd(v[0], v[2]), t1 = csub(v[0], v[2]);
-    cplx<T> t2 = cadd(v[1], v[3]), t3 = rot90<T, DIR>(csub(v[1], v[3]));
-    v[0] = cadd(t0, t2);
-    v[2] = csub(t0, t2);
-    v[1] = cadd(t1, t3);
-    v[3] = csub(t1, t3);
-}
-
-template <typename T, int DIR> __device__ __forceinline__ void dft8(cplx<T> *v) {
-    cplx<T> e[4] = {v[0], v[2], v[4], v[6]};
-    cplx<T> o[4] = {v[1], v[3], v[5], v[7]};
-    dft4<T, DIR>(e);
-    dft4<T, DIR>(o);
-    const T s = (T)0.707106781186547524400844362104849039;
-    const T d = (T)DIR;
-    // o_q * exp(DIR i pi q / 4) for q = 1, 2, 3
-    cplx<T> o1 = {s * (o[1].re - d * o[1].im), s * (o[1].im + d * o[1].re)};
-    cplx<T> o2 = rot90<T, DIR>(o[2]);
-    cplx<T> o3 = {s * (-o[3].re - d * o[3].im), s * (-o[3].im + d * o[3].re)};
-    v[0] = cadd(e[0], o[0]);
-    v[4] = csub(e[0], o[0]);
-    v[1] = cadd(e[1], o1);
-    v[5] = csub(e[1], o1);
-    v[2] = cadd(e[2], o2);
-    v[6] = csub(e[2], o2);
-    v[3] = cadd(e[3], o3);
-    v[7] = csub(e[3], o3);
-}
-
-template <typename T, int R, int DIR> __device__ __forceinline__ void dft(cplx<T> *v) {
-    if constexpr (R == 8) dft8<T, DIR>(v);
-    else if constexpr (R == 4) dft4<T, DIR>(v);
-    else dft2<T, DIR>(v);
-}
-
 // LDS regions hold N complex values with one padding slot per 16 (fft16.h):
 // complex element i of region r lives at r * lds_region<LOGN>() + lds_pad(i).
 template <int LOGN> __device__ __forceinline__ int rix(int reg, int i) { return reg * lds_region<LOGN>() + lds_pad(i); }
@@ -200,18 +158,18 @@ __device__ __forceinline__ void rows_pre_inverse(cplx<T> *buf, const cplx<T> *__
     __syncthreads();
 }
 
-// Symbol multiplier invNd / g, g = (1 + alpha mu + beta mu^2 + gamma mu^3)^2, invNd a
-// power of two.  The reciprocal of the root a = sqrt(g) >= 1 is the hardware's
-// estimate and two Newton steps (as far as 1 ulp; the full division's scaling and
-// fix-up are for operands that do not occur here), squared; a is bounded so that
-// an overflowing g still gives 0.
+// Symbol multiplier invNd / g, g = (1 + alpha mu + beta mu^2 + gamma mu^3)^2 >= 1, invNd a
+// power of two.  The reciprocal is the hardware's estimate and two Newton steps, which
+// leave its last rounding; the full division's scaling and fix-up are for operands
+// that do not occur here.  g is bounded so that an overflowing one still gives 0.
 __device__ __forceinline__ double symbol_of(double mu, double alpha, double beta, double gamma, double invNd) {
-    double a = 1.0 + mu * (alpha + mu * (beta + gamma * mu));
-    a = a > 0x1p+1000 ? 0x1p+1000 : a;
-    double r = __builtin_amdgcn_rcp(a);
-    r = __builtin_fma(__builtin_fma(-a, r, 1.0), r, r);
-    r = __builtin_fma(__builtin_fma(-a, r, 1.0), r, r);
-    return invNd * (r * r);
+    const double a = 1.0 + mu * (alpha + mu * (beta + gamma * mu));
+    double g = a * a;
+    g = g > 0x1p+1000 ? 0x1p+1000 : g;
+    double r = __builtin_amdgcn_rcp(g);
+    r = __builtin_fma(__builtin_fma(-g, r, 1.0), r, r);
+    r = __builtin_fma(__builtin_fma(-g, r, 1.0), r, r);
+    return invNd * r;
 }
 
 // mu = s_kx + s_ky.

@@ -117,8 +117,9 @@ template <int LOGN> constexpr int r8_radix(int q) { return LOGN - 3 * q >= 3 ? 8
 template <int LOGN> constexpr int r8_passes() { return (LOGN + 2) / 3; }
 
 template <typename T, int LOGN> struct TwR8 {
-    // pass 1 (the only pass with NS > 1 for N <= 64): butterflies b < 8 / R, inputs 1..R-1
-    cplx<T> w[4][7];
+    // pass 1 (the only pass with NS > 1 for N <= 64): butterflies b < 8 / R, powers
+    // w, w^2, w^4 of the twiddle
+    cplx<T> w[4][3];
 };
 
 template <typename T, int LOGN>
@@ -135,7 +136,8 @@ __device__ __forceinline__ void load_twr8(TwR8<T, LOGN> &tw, const cplx<T> *tabl
             const int k = j & (NS - 1);
             (void)NB;
 #pragma unroll
-            for (int r = 1; r < R; ++r) tw.w[b][r - 1] = table[(r * k * STEP) & (N - 1)];
+            for (int e = 0; e < 3; ++e)
+                if ((1 << e) < R) tw.w[b][e] = table[((k * STEP) << e) & (N - 1)];
         }
     }
 }
@@ -151,14 +153,8 @@ __device__ __forceinline__ void r8_pass(cplx<T> *buf, int reg, int t, bool activ
             const int j = t + b * TPT;
 #pragma unroll
             for (int r = 0; r < R; ++r) v[b][r] = buf[M::at(reg, j + r * NB)];
-            if constexpr (NS > 1) {
-#pragma unroll
-                for (int r = 1; r < R; ++r) {
-                    const cplx<T> w = DIR < 0 ? tw.w[b][r - 1] : cconj(tw.w[b][r - 1]);
-                    v[b][r] = cmul(v[b][r], w);
-                }
-            }
-            dftR<T, R, DIR>(v[b]);
+            if constexpr (NS > 1) twiddled_dft<T, R, DIR>(v[b], tw.w[b]);
+            else dftR<T, R, DIR>(v[b]);
         }
     }
     __syncthreads();
