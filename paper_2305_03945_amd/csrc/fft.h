@@ -23,17 +23,24 @@
 
 namespace rdk {
 
-__host__ __device__ constexpr int lds_pad(int i) { return i + (i >> 4); }
-template <int LOGN> __host__ __device__ constexpr int lds_region() { return (1 << LOGN) + (1 << LOGN) / 16; }
+// Values per thread of the transforms (see fft16.h).
+template <int LOGN> constexpr int fft_values() { return LOGN <= 9 ? 8 : 16; }
+// LDS regions hold N complex values with a padding slot after every 8 (N <= 64) or 16
+// values, which sets a pass's stride-8 or stride-16 writes by neighbouring threads on
+// different banks.  The single-workgroup step (N <= 64), which LDS bounds, needs 8: in
+// FP64 (16-byte values) 16 leaves two lanes of eight on each bank, a third of its LDS
+// cycles.  Above, the step's other LDS accesses make up for it (8: 1-2 % slower).
+template <int LOGN> constexpr int pad_shift() { return LOGN <= 6 ? 3 : 4; }
+template <int LOGN> __host__ __device__ constexpr int lds_pad(int i) { return i + (i >> pad_shift<LOGN>()); }
+template <int LOGN> __host__ __device__ constexpr int lds_region() { return lds_pad<LOGN>(1 << LOGN); }
 
 template <typename T, int DIR> __device__ __forceinline__ cplx<T> rot90(cplx<T> a) {
     // multiply by exp(DIR i pi / 2): -i for the forward transform, +i for the inverse
     return DIR < 0 ? cplx<T>{a.im, -a.re} : cplx<T>{-a.im, a.re};
 }
 
-// LDS regions hold N complex values with one padding slot per 16 (fft16.h):
-// complex element i of region r lives at r * lds_region<LOGN>() + lds_pad(i).
-template <int LOGN> __device__ __forceinline__ int rix(int reg, int i) { return reg * lds_region<LOGN>() + lds_pad(i); }
+// Complex element i of region r.
+template <int LOGN> __device__ __forceinline__ int rix(int reg, int i) { return reg * lds_region<LOGN>() + lds_pad<LOGN>(i); }
 
 // Real element m (< 2N) of a region viewed as 2N reals (re, im interleaved).
 template <typename T, int LOGN> __device__ __forceinline__ T &rreal(cplx<T> *buf, int reg, int m) {

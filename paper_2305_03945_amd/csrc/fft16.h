@@ -2,9 +2,8 @@
 //
 // A length-N transform (N = 2^LOGN, 16 <= N <= 4096) is done by N/16 threads
 // (one wave or less for N <= 1024, several waves above), in an LDS region of
-// N complex values laid out with one padding slot per 16 (index i at
-// i + i/16), which keeps the stride-R writes of a Stockham pass off a single
-// bank group.  Passes are Stockham autosort passes of radix 16, then one pass
+// N complex values with padding (lds_pad), which keeps the stride-R writes of a
+// Stockham pass off a single bank group.  Passes are Stockham autosort passes of radix 16, then one pass
 // of radix 8, 4 or 2 for the remaining bits; each thread runs 16/R butterflies
 // of a radix-R pass.  A butterfly gathers the powers W^{k}, W^{2k}, W^{4k}, W^{8k}
 // of its twiddle and applies them in its radix-2 steps (twiddled_dft).
@@ -200,7 +199,7 @@ __device__ __forceinline__ void pass_in(const cplx<T> *x, int t, const cplx<T> (
     for (int b = 0; b < BPT; ++b) {
         const int j = t + b * TPF;
 #pragma unroll
-        for (int r = 0; r < R; ++r) v[b][r] = x[lds_pad(j + r * NB)];
+        for (int r = 0; r < R; ++r) v[b][r] = x[lds_pad<LOGN>(j + r * NB)];
         if constexpr (NS > 1) twiddled_dft<T, R, DIR>(v[b], pw[b]);
         else dftR<T, R, DIR>(v[b]);
     }
@@ -216,7 +215,7 @@ __device__ __forceinline__ void pass_out(cplx<T> *x, int t, const cplx<T> (*v)[R
         const int k = j & (NS - 1);
         const int base = (j - k) * R + k;
 #pragma unroll
-        for (int q = 0; q < R; ++q) x[lds_pad(base + q * NS)] = v[b][q];
+        for (int q = 0; q < R; ++q) x[lds_pad<LOGN>(base + q * NS)] = v[b][q];
     }
 }
 
@@ -290,7 +289,7 @@ __device__ __forceinline__ void fft16_regs(cplx<T> *x, int t, const Tw16<T, LOGN
     constexpr int RL = last_radix<LOGN, V>();
     dftR<T, V, DIR>(v);
 #pragma unroll
-    for (int q = 0; q < V; ++q) x[lds_pad(V * t + q)] = v[q];
+    for (int q = 0; q < V; ++q) x[lds_pad<LOGN>(V * t + q)] = v[q];
     __syncthreads();
     middle_passes<T, LOGN, DIR, 1, V>(x, t, w);
     cplx<T> o[V / RL][RL];

@@ -996,7 +996,7 @@ template <int LOGN> constexpr int col_region() { return lds_region<LOGN>() + COL
 // Values per thread of a column transform: at most 512^2 leaves the chip short of
 // waves (512^2: 256 columns), and a pass takes one wave's serial chain; 8 values
 // per thread halve it.
-template <int LOGN> constexpr int col_values() { return LOGN <= 9 ? 8 : 16; }
+template <int LOGN> constexpr int col_values() { return fft_values<LOGN>(); }
 
 template <typename T, int LOGN, int C> constexpr int col_jobs() {
     constexpr int N = 1 << LOGN;

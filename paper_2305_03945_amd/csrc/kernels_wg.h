@@ -94,6 +94,7 @@ template <int K> __device__ __forceinline__ void wg_sum(double *v, double *red) 
 // is needed between the row and the column transforms.
 template <int LOGN, int BC> struct ColMap {
     static constexpr int N = 1 << LOGN, H = N / 2;
+    static constexpr bool COLUMNS = true;
     __device__ __forceinline__ static int row_of(int i) {
         if (BC == BC_P) return i;
         return i < H ? 2 * i : 2 * (N - 1 - i) + 1;   // inverse of dct_pos
@@ -123,13 +124,12 @@ template <typename T, int LOGN> struct TwR8 {
 };
 
 template <typename T, int LOGN>
-__device__ __forceinline__ void load_twr8(TwR8<T, LOGN> &tw, const cplx<T> *table) {
+__device__ __forceinline__ void load_twr8(TwR8<T, LOGN> &tw, const cplx<T> *table, int t) {
     static_assert(r8_passes<LOGN>() <= 2, "radix-8 step transforms: N <= 64");
     constexpr int N = 1 << LOGN, TPT = N / 8;
     if constexpr (r8_passes<LOGN>() == 2) {
         constexpr int R = r8_radix<LOGN>(1), NS = 8, NB = N / R, BPT = 8 / R;
         constexpr int STEP = N / (NS * R);
-        const int t = threadIdx.x % TPT;
 #pragma unroll
         for (int b = 0; b < BPT; ++b) {
             const int j = t + b * TPT;
@@ -157,7 +157,7 @@ __device__ __forceinline__ void r8_pass(cplx<T> *buf, int reg, int t, bool activ
             else dftR<T, R, DIR>(v[b]);
         }
     }
-    __syncthreads();
+    pass_sync<true>();
     if (active) {
 #pragma unroll
         for (int b = 0; b < BPT; ++b) {
@@ -168,16 +168,21 @@ __device__ __forceinline__ void r8_pass(cplx<T> *buf, int reg, int t, bool activ
             for (int q = 0; q < R; ++q) buf[M::at(reg, base + q * NS)] = v[b][q];
         }
     }
-    __syncthreads();
+    pass_sync<true>();
 }
 
 // In-place transforms of NREG regions (address map M) by NTH threads; teams of N/8
-// threads take regions round-robin.  Ends with a barrier.
+// threads, each within one wave, take regions round-robin.  Rows: a team is N/8
+// consecutive lanes, whose reads are contiguous.  Columns: consecutive lanes take
+// consecutive columns, which are contiguous in LDS at every row (a team's own rows are
+// region strides apart).  Ends with a barrier.
 template <typename T, int LOGN, int DIR, int NREG, int NTH, class M>
 __device__ __forceinline__ void wg_fft_r8(cplx<T> *buf, const TwR8<T, LOGN> &tw) {
-    constexpr int TPT = (1 << LOGN) / 8;
+    constexpr int TPT = (1 << LOGN) / 8, TPW = 64 / TPT;
     constexpr int NTEAMS = NTH / TPT;
-    const int team = threadIdx.x / TPT, t = threadIdx.x % TPT;
+    const int lane = threadIdx.x & 63;
+    const int t = M::COLUMNS ? lane / TPW : lane % TPT;
+    const int team = (threadIdx.x >> 6) * TPW + (M::COLUMNS ? lane % TPW : lane / TPT);
 #pragma unroll 1
     for (int g = 0; g < NREG; g += NTEAMS) {
         const int reg = g + team;
@@ -185,9 +190,11 @@ __device__ __forceinline__ void wg_fft_r8(cplx<T> *buf, const TwR8<T, LOGN> &tw)
         r8_pass<T, LOGN, 0, DIR, M>(buf, active ? reg : 0, t, active, tw);
         if constexpr (r8_passes<LOGN>() == 2) r8_pass<T, LOGN, 1, DIR, M>(buf, active ? reg : 0, t, active, tw);
     }
+    __syncthreads();
 }
 
 template <int LOGN> struct RowMap {
+    static constexpr bool COLUMNS = false;
     __device__ __forceinline__ static int at(int reg, int i) { return rix<LOGN>(reg, i); }
 };
 
@@ -265,8 +272,9 @@ __global__ __launch_bounds__(NT7) void k_step_wg(Slot *const *slots) {
     const double *src = s.src;     // U^k: the caller's input, read-only for the whole step
     const double *Ukp = Plan::uk_lds ? (const double *)nxt : src;
     double *U64 = s.U64[0];        // mixed: FP64 U (never bound to the caller's input)
-    TwR8<T, LOGN> twr;
-    load_twr8<T, LOGN>(twr, (const cplx<T> *)s.tw);
+    TwR8<T, LOGN> twr, twc;   // of this thread's place in a row team, and in a column team
+    load_twr8<T, LOGN>(twr, (const cplx<T> *)s.tw, (threadIdx.x & 63) % (N / 8));
+    load_twr8<T, LOGN>(twc, (const cplx<T> *)s.tw, (threadIdx.x & 63) / (64 / (N / 8)));
     const StopRule rule{s.tol, s.inner_rtol, s.max_iter, s.max_outer};
     auto pos = [](int x) { return BC == BC_P ? x : dct_pos(x, N); };
     auto at = [](int c, int y, int x) { return c * NN + wrap<BC>(y, N) * N + wrap<BC>(x, N); };
@@ -410,9 +418,9 @@ __global__ __launch_bounds__(NT7) void k_step_wg(Slot *const *slots) {
     auto precond = [&]() {
         wg_fft_r8<T, LOGN, -1, NREG, NT7, RowMap<LOGN>>(S, twr);
         rows_post_forward<T, LOGN, BC, NREG, NT7>(S, twd);
-        wg_fft_r8<T, LOGN, -1, NREG, NT7, ColMap<LOGN, BC>>(S, twr);
+        wg_fft_r8<T, LOGN, -1, NREG, NT7, ColMap<LOGN, BC>>(S, twc);
         cols_symbol_mapped<T, LOGN, BC, NREG, NT7, ColMap<LOGN, BC>>(S, s, eig_l, twd);
-        wg_fft_r8<T, LOGN, +1, NREG, NT7, ColMap<LOGN, BC>>(S, twr);
+        wg_fft_r8<T, LOGN, +1, NREG, NT7, ColMap<LOGN, BC>>(S, twc);
         rows_pre_inverse<T, LOGN, BC, NREG, NT7>(S, twd);
         wg_fft_r8<T, LOGN, +1, NREG, NT7, RowMap<LOGN>>(S, twr);
     };
