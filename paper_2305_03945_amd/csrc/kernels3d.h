@@ -23,6 +23,12 @@
 
 namespace rdk {
 
+// Values per thread of the 3-D transforms: the passes of at most 2 M points (128^3) hold
+// too few waves to hide their serial chains, which 8 values halve (128^3 mixed step
+// 1.25 -> 1.07 ms, 64^3 767 -> 580 us).
+// 256^3 fills the chip (FP64 step 14.4 ms; 15.0 with 8).
+template <int LOGN> constexpr int V3() { return LOGN <= 7 ? 8 : 16; }
+
 // ---------------------------------------------------------------- 3-D stencil windows
 // Four consecutive points (z, y, x0 .. x0+3), x0 a multiple of 4, and their 7-point
 // neighbourhood: the row (z, y) with one value on each side, and the rows (z, y +- 1)
@@ -264,8 +270,8 @@ __device__ __forceinline__ void row3_forward_pass(SlotRef s, StateRef sst, cplx<
     constexpr int NREG = C * R / 2;
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
     const int z = tile / (N / R), y0 = (tile % (N / R)) * R;
-    Tw16<T, LOGN> twr;
-    load_tw16<T, LOGN>(twr, (const cplx<T> *)s.tw);
+    Tw16<T, LOGN, V3<LOGN>()> twr;
+    load_tw16<T, LOGN, V3<LOGN>()>(twr, (const cplx<T> *)s.tw);
     double acc[2 * C];
 #pragma unroll
     for (int k = 0; k < 2 * C; ++k) acc[k] = 0.0;
@@ -325,8 +331,8 @@ __global__ __launch_bounds__(NT) void k3_rowinv(Slot *const *slots) {
     if (skip_launch<K_ITER64>(sst)) return;
     const int tile = blockIdx.x;
     const int z = tile / (N / R), y0 = (tile % (N / R)) * R;
-    Tw16<T, LOGN> twr;
-    load_tw16<T, LOGN>(twr, (const cplx<T> *)s.tw);
+    Tw16<T, LOGN, V3<LOGN>()> twr;
+    load_tw16<T, LOGN, V3<LOGN>()>(twr, (const cplx<T> *)s.tw);
     const cplx<T> *S = (const cplx<T> *)s.S;
     for (int idx = threadIdx.x; idx < C * R * H; idx += NT) {
         const int j = idx % H, rest = idx / H;
@@ -525,7 +531,7 @@ template <typename T, int LOGN> constexpr int line_cb() {
     return want > (1 << LOGN) / 2 ? (1 << LOGN) / 2 : want;
 }
 template <typename T, int LOGN> constexpr int line_threads() {
-    constexpr int t = line_cb<T, LOGN>() * ((1 << LOGN) / 16);
+    constexpr int t = line_cb<T, LOGN>() * ((1 << LOGN) / V3<LOGN>());
     return t < 64 ? 64 : t;
 }
 
@@ -593,17 +599,18 @@ __device__ __forceinline__ void lines_apply_symbol3(cplx<T> *buf, int c, int q, 
 // Periodic lines of slots j > 0 are plain complex sequences: the y passes are
 // bare transforms and the z pass multiplies by the symbol at (kx, ky, kz) =
 // (j, q, l).  Their transforms start from and end in registers (fft16_regs):
-// thread t of team g holds elements t + r N/16 of the line of slot j0 + g, and
+// thread t of team g holds elements t + r N/V of the line of slot j0 + g, and
 // CB consecutive lanes take the CB adjacent slots (one 128-byte run).  FP64 only,
 // as for the 2-D column pass (measured: no gain for FP32).
 template <typename T, int LOGN> constexpr bool lines_in_regs() {
-    return sizeof(T) == 8 && npasses16<LOGN>() >= 2 &&
-           line_threads<T, LOGN>() == line_cb<T, LOGN>() * ((1 << LOGN) / 16);
+    return sizeof(T) == 8 && npasses16<LOGN, V3<LOGN>()>() >= 2 &&
+           line_threads<T, LOGN>() == line_cb<T, LOGN>() * ((1 << LOGN) / V3<LOGN>());
 }
 
 template <typename T, int LOGN, int PASS>
 __device__ __forceinline__ void lines_regs(SlotRef s, int c, int w, int j0, cplx<T> *S, cplx<T> *buf) {
-    constexpr int N = 1 << LOGN, TPF = N / 16;
+    constexpr int V = V3<LOGN>();
+    constexpr int N = 1 << LOGN, TPF = N / V;
     constexpr int CB = line_cb<T, LOGN>();
     typedef T v2_t __attribute__((ext_vector_type(2)));
     const int team = threadIdx.x % CB, t = threadIdx.x / CB;
@@ -613,34 +620,34 @@ __device__ __forceinline__ void lines_regs(SlotRef s, int c, int w, int j0, cplx
     auto off = [&](int p) -> int {
         return PASS == L3_ZSYM ? (int)s3_off<LOGN>(c, p, w, j) : (int)s3_off<LOGN>(c, w, p, j);
     };
-    cplx<T> v[16];
+    cplx<T> v[V];
     {
         const auto Sg = gp((const v2_t *)S);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
+        for (int r = 0; r < V; ++r) {
             const v2_t a = Sg[off(t + r * TPF)];
             v[r] = {a[0], a[1]};
         }
     }
-    Tw16<T, LOGN> twr;
-    load_tw16<T, LOGN>(twr, (const cplx<T> *)s.tw, t);
+    Tw16<T, LOGN, V3<LOGN>()> twr;
+    load_tw16<T, LOGN, V3<LOGN>()>(twr, (const cplx<T> *)s.tw, t);
     if constexpr (PASS == L3_ZSYM) {
-        fft16_regs<T, LOGN, -1>(x, t, twr, v);
+        fft16_regs<T, LOGN, -1, V>(x, t, twr, v);
         const double invN3 = 1.0 / ((double)N * (double)N * (double)N);
         const double al = s.alpha[c], be = s.beta[c], ga = s.gamma[c];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
+        for (int r = 0; r < V; ++r) {
             const T m = (T)symbol3(s.eig, j, w, t + r * TPF, al, be, ga, invN3);
             v[r] = {v[r].re * m, v[r].im * m};
         }
         __syncthreads();   // the last forward pass has read x
-        fft16_regs<T, LOGN, +1>(x, t, twr, v);
+        fft16_regs<T, LOGN, +1, V>(x, t, twr, v);
     } else {
-        fft16_regs<T, LOGN, PASS == L3_YFWD ? -1 : +1>(x, t, twr, v);
+        fft16_regs<T, LOGN, PASS == L3_YFWD ? -1 : +1, V>(x, t, twr, v);
     }
     const auto So = gp((v2_t *)S);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
+    for (int r = 0; r < V; ++r) {
         v2_t a;
         a[0] = v[r].re;
         a[1] = v[r].im;
@@ -688,8 +695,8 @@ __global__ __launch_bounds__((line_threads<T, LOGN>())) void k3_lines(Slot *cons
             return;
         }
     }
-    Tw16<T, LOGN> twr;
-    load_tw16<T, LOGN>(twr, (const cplx<T> *)s.tw);
+    Tw16<T, LOGN, V3<LOGN>()> twr;
+    load_tw16<T, LOGN, V3<LOGN>()>(twr, (const cplx<T> *)s.tw);
     // element p of the line of slot j
     auto off = [&](int p, int j) -> size_t {
         return PASS == L3_ZSYM ? s3_off<LOGN>(c, p, w, j) : s3_off<LOGN>(c, w, p, j);
@@ -733,8 +740,8 @@ __global__ __launch_bounds__(NT) void k3_rows_transform_in(Slot *const *slots, c
     __shared__ cplx<T> buf[NREG * lds_region<LOGN>()];
     SlotRef s = slot_of(slots);
     const int z = blockIdx.x / (N / R), y0 = (blockIdx.x % (N / R)) * R;
-    Tw16<T, LOGN> twr;
-    load_tw16<T, LOGN>(twr, (const cplx<T> *)s.tw);
+    Tw16<T, LOGN, V3<LOGN>()> twr;
+    load_tw16<T, LOGN, V3<LOGN>()>(twr, (const cplx<T> *)s.tw);
     for (int idx = threadIdx.x; idx < C * R * N; idx += NT) {
         const int x = idx & (N - 1), rest = idx >> LOGN;
         const int r = rest % R, c = rest / R;
@@ -761,8 +768,8 @@ __global__ __launch_bounds__(NT) void k3_rows_transform_out(Slot *const *slots, 
     __shared__ cplx<T> buf[NREG * lds_region<LOGN>()];
     SlotRef s = slot_of(slots);
     const int z = blockIdx.x / (N / R), y0 = (blockIdx.x % (N / R)) * R;
-    Tw16<T, LOGN> twr;
-    load_tw16<T, LOGN>(twr, (const cplx<T> *)s.tw);
+    Tw16<T, LOGN, V3<LOGN>()> twr;
+    load_tw16<T, LOGN, V3<LOGN>()>(twr, (const cplx<T> *)s.tw);
     const cplx<T> *S = (const cplx<T> *)s.S;
     for (int idx = threadIdx.x; idx < C * R * H; idx += NT) {
         const int j = idx % H, rest = idx / H;
