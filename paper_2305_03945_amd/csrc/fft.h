@@ -202,50 +202,64 @@ __device__ __forceinline__ SymPair<T> load_sym_pair(const double *__restrict__ e
     return p;
 }
 
-// One pair item (bins zl, zn) of a transformed line that holds one complex sequence
-// (plain; eigenvalue ea of the other directions) or two real ones packed as real and
-// imaginary part (ea, eb; periodic), or two cosine sequences (Neumann).
+// The symbol multipliers of a pair item (bins l and nl of a line that holds one complex
+// sequence -- plain; eigenvalue ea of the other directions -- or two real ones packed
+// as real and imaginary part, ea and eb; Neumann: two cosine sequences).
+template <typename T> struct PairMult {
+    T al, an, bl, bn;
+};
 template <typename T, int BC>
-__device__ __forceinline__ void apply_symbol_pair(cplx<T> &zlr, cplx<T> &znr, int l, bool plain, double ea, double eb,
-                                                  const SymPair<T> &p, double al, double be, double ga, double invNd) {
+__device__ __forceinline__ PairMult<T> pair_mults(int l, bool plain, double ea, double eb, const SymPair<T> &p,
+                                                  double al, double be, double ga, double invNd) {
     auto m = [&](double ex, double ey) { return (T)symbol_of(ex + ey, al, be, ga, invNd); };
+    PairMult<T> r{};
+    r.al = m(ea, p.el);
+    if (BC == BC_N || plain || l == 0) r.an = m(ea, p.en);
+    if (BC == BC_N || !plain) {
+        r.bl = m(eb, p.el);
+        if (BC == BC_N || l == 0) r.bn = m(eb, p.en);
+    }
+    return r;
+}
+
+// Multiply the item's bins.  w: the DCT twiddle w_l (Neumann).
+template <typename T, int BC>
+__device__ __forceinline__ void apply_pair(cplx<T> &zlr, cplx<T> &znr, int l, bool plain, const PairMult<T> &m,
+                                           cplx<T> w) {
     const cplx<T> zl = zlr, zn = znr;
-    if constexpr (BC == BC_P) {
-        if (plain) {
-            const T m1 = m(ea, p.el), m2 = m(ea, p.en);
-            zlr = {zl.re * m1, zl.im * m1};
-            znr = {zn.re * m2, zn.im * m2};
-        } else if (l == 0) {
-            // bins 0 and N/2 of two real sequences: real pairs
-            zlr = {zl.re * m(ea, p.el), zl.im * m(eb, p.el)};
-            znr = {zn.re * m(ea, p.en), zn.im * m(eb, p.en)};
-        } else {
-            const T ma = m(ea, p.el), mb = m(eb, p.el);
-            cplx<T> A = {(zl.re + zn.re) * (T)0.5, (zl.im - zn.im) * (T)0.5};
-            cplx<T> B = {(zl.im + zn.im) * (T)0.5, (zn.re - zl.re) * (T)0.5};
-            A = {A.re * ma, A.im * ma};
-            B = {B.re * mb, B.im * mb};
+    if (BC == BC_P && plain) {
+        zlr = {zl.re * m.al, zl.im * m.al};
+        znr = {zn.re * m.an, zn.im * m.an};
+    } else if (l == 0) {
+        // bins 0 and N/2 of two real sequences: real pairs
+        zlr = {zl.re * m.al, zl.im * m.bl};
+        znr = {zn.re * m.an, zn.im * m.bn};
+    } else {
+        cplx<T> A = {(zl.re + zn.re) * (T)0.5, (zl.im - zn.im) * (T)0.5};
+        cplx<T> B = {(zl.im + zn.im) * (T)0.5, (zn.re - zl.re) * (T)0.5};
+        if constexpr (BC == BC_P) {
+            A = {A.re * m.al, A.im * m.al};
+            B = {B.re * m.bl, B.im * m.bl};
             zlr = {A.re - B.im, A.im + B.re};
             znr = {A.re + B.im, B.re - A.im};
-        }
-    } else {
-        if (l == 0) {
-            zlr = {zl.re * m(ea, p.el), zl.im * m(eb, p.el)};
-            znr = {zn.re * m(ea, p.en), zn.im * m(eb, p.en)};
         } else {
-            const cplx<T> A = {(zl.re + zn.re) * (T)0.5, (zl.im - zn.im) * (T)0.5};
-            const cplx<T> B = {(zl.im + zn.im) * (T)0.5, (zn.re - zl.re) * (T)0.5};
-            const cplx<T> qa = cmul(A, p.w), qb = cmul(B, p.w);
+            const cplx<T> qa = cmul(A, w), qb = cmul(B, w);
             // cosine coefficients at l and N-l, scaled by their symbols
-            const T xal = qa.re * m(ea, p.el), xan = -qa.im * m(ea, p.en);
-            const T xbl = qb.re * m(eb, p.el), xbn = -qb.im * m(eb, p.en);
-            const cplx<T> wc = cconj(p.w);
+            const T xal = qa.re * m.al, xan = -qa.im * m.an;
+            const T xbl = qb.re * m.bl, xbn = -qb.im * m.bn;
+            const cplx<T> wc = cconj(w);
             const cplx<T> va = cmul(wc, cplx<T>{xal, -xan});
             const cplx<T> vb = cmul(wc, cplx<T>{xbl, -xbn});
             zlr = {va.re - vb.im, va.im + vb.re};
             znr = {va.re + vb.im, vb.re - va.im};
         }
     }
+}
+
+template <typename T, int BC>
+__device__ __forceinline__ void apply_symbol_pair(cplx<T> &zl, cplx<T> &zn, int l, bool plain, double ea, double eb,
+                                                  const SymPair<T> &p, double al, double be, double ga, double invNd) {
+    apply_pair<T, BC>(zl, zn, l, plain, pair_mults<T, BC>(l, plain, ea, eb, p, al, be, ga, invNd), p.w);
 }
 
 // ---- column pass, between the forward and inverse column FFTs: multiply by the

@@ -5,18 +5,20 @@
 // cost their launch latency, not their bytes.  Here one workgroup per slot takes
 // the whole step, Algorithm 1 with its stop test, in one launch:
 //
-//   W = F(U_n) (stencil)  -> spectrum S in LDS (row pairs packed as complex rows)
+//   W = F(U_n) (stencil);  Z = Q + (1 + omega) W -> spectrum S in LDS (row pairs
+//   packed as complex rows);  Q += W (registers; the sums of kernels_rows.h)
 //   ||W / h_t|| (fixed-order workgroup sum), stop decision (decide<>, thread 0)
 //   row FFTs, column FFTs (on the row layout), 1 / (N^2 g), inverse column
-//   FFTs, inverse row FFTs                          -> Y = G^-1 W_n in LDS
-//   P_{n+1} = P_n + tau_p Y,  P~ = P_{n+1} + omega tau_p Y (P~ kept in LDS)
+//   FFTs, inverse row FFTs                          -> P~ = tau_p G^-1 Z in LDS
 //   U_{n+1} = U_n - tau_u grad F(U_n)^T P~
 //
 // and, in the mixed precision, the same FP32 inner loop on the correction e with
 // the FP64 outer passes (U += e, r = F(U), stop test) between inner loops.  The
-// spectrum always lives in LDS; the iterate, P and (mixed) the FP32 copies of U
-// and r take LDS in that order while the 160 KB of a gfx950 workgroup allow, and
-// otherwise stay in the slot's HBM buffers (then L2-resident).  The arithmetic
+// spectrum always lives in LDS; the iterate and (mixed) the FP32 copy of U take
+// LDS in that order while the 160 KB of a gfx950 workgroup allow, and otherwise stay
+// in the slot's HBM buffers (then L2-resident).  What a thread alone reads, Q, U^k (FP64)
+// or r (mixed) at its own points and its symbol multipliers, stays in registers for
+// the whole step: LDS, not arithmetic, bounds this kernel.  The arithmetic
 // per point is that of the batched kernels (the same eval_F / eval_Ftilde /
 // eval_adjoint code, the pair / cosine processing and symbol of fft.h); the
 // transforms are radix-8 passes and the norm's sums run in another order.
@@ -39,14 +41,8 @@ template <typename T, int LOGN, int C> struct WgPlan {
     static constexpr size_t room = WG_LDS_BYTES - fixed;
     static constexpr bool ok = spec <= room;
     static constexpr bool u_lds = ok && spec + fieldT <= room;
-    static constexpr bool p_lds = u_lds && spec + 2 * fieldT <= room;
-    static constexpr bool ub_lds = sizeof(T) == 4 && p_lds && spec + 2 * fieldT + field32 <= room;
-    static constexpr bool r_lds = ub_lds && spec + 2 * fieldT + 2 * field32 <= room;
-    // FP64 path: U^k as well, when it fits beside U and P
-    static constexpr size_t field64 = (size_t)C * NN * sizeof(double);
-    static constexpr bool uk_lds = sizeof(T) == 8 && p_lds && spec + 2 * fieldT + field64 <= room;
-    static constexpr size_t bytes = spec + (u_lds ? fieldT : 0) + (p_lds ? fieldT : 0) + (ub_lds ? field32 : 0) +
-                                    (r_lds ? field32 : 0) + (uk_lds ? field64 : 0);
+    static constexpr bool ub_lds = sizeof(T) == 4 && u_lds && spec + fieldT + field32 <= room;
+    static constexpr size_t bytes = spec + (u_lds ? fieldT : 0) + (ub_lds ? field32 : 0);
 };
 
 // Whether the single-workgroup step serves (T, N, equation): N <= 64, the
@@ -201,22 +197,42 @@ template <int LOGN> struct RowMap {
 // 1 / (N^2 g) on the transformed columns (cols_apply_symbol of fft.h on the
 // mapped layout): column job reg of component c = reg / H is kx = reg % H
 // (periodic; column 0 packs kx = 0 and kx = N/2) or the cosine pair kx = 2j, 2j + 1
-// (Neumann).
-template <typename T, int LOGN, int BC, int NREG, int NTH, class M>
-__device__ __forceinline__ void cols_symbol_mapped(cplx<T> *buf, SlotRef s, const double *eig, const cplx<T> *twd) {
+// (Neumann).  Item i of a thread is the pair (reg, l); eight neighbouring lanes take
+// eight neighbouring columns, which are contiguous in LDS.  The multipliers depend on
+// the step only, so a thread forms them once (load_wg_symbol).
+template <int LOGN> __device__ __forceinline__ void wg_symbol_item(int it, int &reg, int &l) {
+    constexpr int H = (1 << LOGN) / 2;
+    reg = (it & 7) + 8 * (it / (8 * H));
+    l = (it >> 3) % H;
+}
+template <int NREG, int LOGN> constexpr int wg_symbol_items() { return (NREG * (1 << LOGN) / 2 + NT7 - 1) / NT7; }
+
+template <typename T, int LOGN, int BC, int NREG>
+__device__ __forceinline__ void load_wg_symbol(PairMult<T> *m, SlotRef s) {
     constexpr int N = 1 << LOGN, H = N / 2;
     const double invN2 = 1.0 / ((double)N * (double)N);
-#pragma unroll 1
-    for (int it = threadIdx.x; it < NREG * H; it += NTH) {
-        const int reg = it / H, l = it % H;
+#pragma unroll
+    for (int i = 0; i < wg_symbol_items<NREG, LOGN>(); ++i) {
+        int reg, l;
+        wg_symbol_item<LOGN>(threadIdx.x + i * NT7, reg, l);
+        if (reg >= NREG) break;
         const int c = reg / H, j = reg % H;
-        const double al = s.alpha[c], be = s.beta[c], ga = s.gamma[c];
-        const int nl = (l == 0) ? H : N - l;
-        cplx<T> &zlr = buf[M::at(reg, l)];
-        cplx<T> &znr = buf[M::at(reg, nl)];
         const int ka = BC == BC_P ? j : 2 * j, kb = BC == BC_P ? H : 2 * j + 1;
-        apply_symbol_pair<T, BC>(zlr, znr, l, j > 0, eig[ka], eig[kb], load_sym_pair<T, LOGN, BC>(eig, twd, l), al,
-                                 be, ga, invN2);
+        const SymPair<T> p{s.eig[l], s.eig[l == 0 ? H : N - l], {}};
+        m[i] = pair_mults<T, BC>(l, j > 0, s.eig[ka], s.eig[kb], p, s.alpha[c], s.beta[c], s.gamma[c], invN2);
+    }
+}
+
+template <typename T, int LOGN, int BC, int NREG, class M>
+__device__ __forceinline__ void cols_symbol_mapped(cplx<T> *buf, const PairMult<T> *m, const cplx<T> *twd) {
+    constexpr int N = 1 << LOGN, H = N / 2;
+#pragma unroll
+    for (int i = 0; i < wg_symbol_items<NREG, LOGN>(); ++i) {
+        int reg, l;
+        wg_symbol_item<LOGN>(threadIdx.x + i * NT7, reg, l);
+        if (reg >= NREG) break;
+        apply_pair<T, BC>(buf[M::at(reg, l)], buf[M::at(reg, l == 0 ? H : N - l)], l, reg % H > 0, m[i],
+                          BC == BC_N ? twd[l] : cplx<T>{});
     }
     __syncthreads();
 }
@@ -253,8 +269,7 @@ __global__ __launch_bounds__(NT7) void k_step_wg(Slot *const *slots) {
     __shared__ __align__(16) unsigned char lds[Plan::bytes];
     __shared__ double red[2 * C * (NT7 / 64)];
     __shared__ State stl;
-    __shared__ double eig_l[N];        // s_k, and the DCT twiddles: read in LDS phases,
-    __shared__ cplx<T> twd_l[N];       // so staged once rather than fetched from L2
+    __shared__ cplx<T> twd_l[N];       // the DCT twiddles, staged once rather than fetched from L2
 
     SlotRef s = slot_of(slots);
     const int tid = threadIdx.x;
@@ -263,14 +278,8 @@ __global__ __launch_bounds__(NT7) void k_step_wg(Slot *const *slots) {
     // iterate: FP64 U, or the mixed path's correction e
     T *U = Plan::u_lds ? (T *)nxt : (T *)s.U[0];
     nxt += Plan::u_lds ? Plan::fieldT : 0;
-    T *P = Plan::p_lds ? (T *)nxt : (T *)s.P;
-    nxt += Plan::p_lds ? Plan::fieldT : 0;
     float *Ub = Plan::ub_lds ? (float *)nxt : s.Ub32;
-    nxt += Plan::ub_lds ? Plan::field32 : 0;
-    float *Rr = Plan::r_lds ? (float *)nxt : s.r32;
-    nxt += Plan::r_lds ? Plan::field32 : 0;
     const double *src = s.src;     // U^k: the caller's input, read-only for the whole step
-    const double *Ukp = Plan::uk_lds ? (const double *)nxt : src;
     double *U64 = s.U64[0];        // mixed: FP64 U (never bound to the caller's input)
     TwR8<T, LOGN> twr, twc;   // of this thread's place in a row team, and in a column team
     load_twr8<T, LOGN>(twr, (const cplx<T> *)s.tw, (threadIdx.x & 63) % (N / 8));
@@ -293,23 +302,32 @@ __global__ __launch_bounds__(NT7) void k_step_wg(Slot *const *slots) {
         }
     };
     if (tid == 0) stl = State{};
-    for (int i = tid; i < N; i += NT7) {
-        eig_l[i] = s.eig[i];
-        twd_l[i] = ((const cplx<T> *)s.twd)[i];
-    }
-    if constexpr (Plan::uk_lds)
-        for (int g = tid; g < C * NN; g += NT7) ((double *)Ukp)[g] = src[g];
+    for (int i = tid; i < N; i += NT7) twd_l[i] = ((const cplx<T> *)s.twd)[i];
     const cplx<T> *twd = twd_l;
+    PairMult<T> sym[wg_symbol_items<NREG, LOGN>()];
+    load_wg_symbol<T, LOGN, BC, NREG>(sym, s);
+    // at this thread's strip: Q, and U^k (FP64) or the outer residual r (mixed)
+    T q[C][L], own[C][L];
+    const T om1 = (T)1 + (T)s.omega;
+    if constexpr (MODE == MODE_F64) {
+        if (tid < STRIP_THREADS) {
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+#pragma unroll
+                for (int i = 0; i < L; ++i) own[c][i] = src[c * NN + ((tid / N) * L + i) * N + tid % N];
+        }
+    }
 
     // ---- the residual of an FP64 state (U_0, or the mixed outer U) into S; its
     // norm and sum(U - U^k) decided by thread 0
-    auto residual64 = [&](const double *Uf, auto decide_fn) {
+    // (start: an initial or outer pass, which begins an iteration loop: S = W, Q = W)
+    auto residual64 = [&](const double *Uf, bool start, auto decide_fn) {
         double acc[2 * C];
 #pragma unroll
         for (int k = 0; k < 2 * C; ++k) acc[k] = 0.0;
         if (tid < STRIP_THREADS) {
             const int x = tid % N, y0 = (tid / N) * L;
-#pragma unroll 1
+#pragma unroll
             for (int s0 = 0; s0 < L; s0 += LS) {
                 const int ys = y0 + s0;
                 double v[C][LS + 2 * HY][2 * HY + 1], uk[C][LS];
@@ -321,7 +339,8 @@ __global__ __launch_bounds__(NT7) void k_step_wg(Slot *const *slots) {
                         for (int dx = -HY; dx <= HY; ++dx)
                             if (wg_needed<HY, LS>(r, dx)) v[c][r + HY][dx + HY] = Uf[at(c, ys + r, x + dx)];
 #pragma unroll
-                    for (int i = 0; i < LS; ++i) uk[c][i] = Ukp[c * NN + (ys + i) * N + x];
+                    for (int i = 0; i < LS; ++i)
+                        uk[c][i] = MODE == MODE_F64 ? (double)own[c][s0 + i] : src[c * NN + (ys + i) * N + x];
                 }
                 double W[C][LS];
 #pragma unroll
@@ -333,11 +352,17 @@ __global__ __launch_bounds__(NT7) void k_step_wg(Slot *const *slots) {
                                        Uc);
 #pragma unroll
                     for (int c = 0; c < C; ++c) {
-                        W[c][i] = Wi[c];
                         acc[c] += Wi[c] * Wi[c];
                         acc[C + c] += Uc[c] - ukc[c];
+                        if (start) {
+                            q[c][s0 + i] = (T)Wi[c];
+                            W[c][i] = Wi[c];
+                        } else {
+                            W[c][i] = q[c][s0 + i] + om1 * (T)Wi[c];
+                            q[c][s0 + i] += (T)Wi[c];
+                        }
                         if constexpr (MODE == MODE_MIXED) {
-                            Rr[c * NN + (ys + i) * N + x] = (float)Wi[c];
+                            own[c][s0 + i] = (T)Wi[c];
                             Ub[c * NN + (ys + i) * N + x] = (float)Uc[c];
                         }
                     }
@@ -366,10 +391,10 @@ __global__ __launch_bounds__(NT7) void k_step_wg(Slot *const *slots) {
         for (int c = 0; c < C; ++c) acc[c] = 0.0;
         if (tid < STRIP_THREADS) {
             const int x = tid % N, y0 = (tid / N) * L;
-#pragma unroll 1
+#pragma unroll
             for (int s0 = 0; s0 < L; s0 += LS) {
                 const int ys = y0 + s0;
-                float ve[C][LS + 2 * HY][2 * HY + 1], vu[C][LS + 2 * HU][2 * HU + 1], rc[C][LS];
+                float ve[C][LS + 2 * HY][2 * HY + 1], vu[C][LS + 2 * HU][2 * HU + 1];
 #pragma unroll
                 for (int c = 0; c < C; ++c) {
 #pragma unroll
@@ -382,20 +407,19 @@ __global__ __launch_bounds__(NT7) void k_step_wg(Slot *const *slots) {
 #pragma unroll
                         for (int dx = -HU; dx <= HU; ++dx)
                             if (wg_needed<HU, LS>(r, dx)) vu[c][r + HU][dx + HU] = Ub[at(c, ys + r, x + dx)];
-#pragma unroll
-                    for (int i = 0; i < LS; ++i) rc[c][i] = Rr[c * NN + (ys + i) * N + x];
                 }
                 double W[C][LS];
 #pragma unroll
                 for (int i = 0; i < LS; ++i) {
                     float Wi[C], r[C];
 #pragma unroll
-                    for (int c = 0; c < C; ++c) r[c] = rc[c][i];
+                    for (int c = 0; c < C; ++c) r[c] = (float)own[c][s0 + i];
                     eval_Ftilde<EQ>(s, [&](int c, int dy, int dx) { return ve[c][i + dy + HY][dx + HY]; },
                                     [&](int c, int dy, int dx) { return vu[c][i + dy + HU][dx + HU]; }, r, Wi);
 #pragma unroll
                     for (int c = 0; c < C; ++c) {
-                        W[c][i] = Wi[c];
+                        W[c][i] = q[c][s0 + i] + om1 * (T)Wi[c];
+                        q[c][s0 + i] += (T)Wi[c];
                         acc[c] += (double)Wi[c] * (double)Wi[c];
                     }
                 }
@@ -413,59 +437,43 @@ __global__ __launch_bounds__(NT7) void k_step_wg(Slot *const *slots) {
         __syncthreads();
     };
 
-    // ---- Y = G^-1 W in place (W in S as packed row pairs on entry; on exit the
-    // complex slot pos(x) of region c H + y / 2 holds Y of rows y, y + 1 as re, im)
+    // ---- G^-1 Z in place (Z in S as packed row pairs on entry; on exit the complex
+    // slot pos(x) of region c H + y / 2 holds G^-1 Z of rows y, y + 1 as re, im)
     auto precond = [&]() {
         wg_fft_r8<T, LOGN, -1, NREG, NT7, RowMap<LOGN>>(S, twr);
         rows_post_forward<T, LOGN, BC, NREG, NT7>(S, twd);
         wg_fft_r8<T, LOGN, -1, NREG, NT7, ColMap<LOGN, BC>>(S, twc);
-        cols_symbol_mapped<T, LOGN, BC, NREG, NT7, ColMap<LOGN, BC>>(S, s, eig_l, twd);
+        cols_symbol_mapped<T, LOGN, BC, NREG, ColMap<LOGN, BC>>(S, sym, twd);
         wg_fft_r8<T, LOGN, +1, NREG, NT7, ColMap<LOGN, BC>>(S, twc);
         rows_pre_inverse<T, LOGN, BC, NREG, NT7>(S, twd);
         wg_fft_r8<T, LOGN, +1, NREG, NT7, RowMap<LOGN>>(S, twr);
     };
-    auto Yat = [&](int c, int y, int x) -> T {
-        const cplx<T> zv = S[rix<LOGN>(c * H + (y >> 1), pos(x))];
-        return (y & 1) ? zv.im : zv.re;
-    };
-
-    // ---- primal descent U_{n+1} = U_n - tau_u grad F(U_n)^T P~ with
-    // P~ = P_{n+1} + omega (P_{n+1} - P_n), P_{n+1} = P_n + tau_p Y, formed in the
-    // registers of the strip that reads it, in place on U (the adjoint reads U only
-    // at its own point); mixed: on e, with f' at U_b + e.  Then the dual ascent:
-    // P_{n+1} of the strip's own points, stored once every thread has read the P_n
-    // it needs.
-    auto primal_dual = [&](bool first) {
-        const T tu = (T)s.tau_u, tp = (T)s.tau_p, om = (T)s.omega;
-        T pnew[C][L];
+    // ---- primal descent U_{n+1} = U_n - tau_u grad F(U_n)^T P~, P~ = tau_p G^-1 Z
+    // (the first iteration: (1 + omega) tau_p G^-1 W_0), in place on U (the adjoint
+    // reads U only at its own point); mixed: on e, with f' at U_b + e.
+    auto primal = [&](bool first) {
+        const T tu = (T)s.tau_u * (T)s.tau_p * (first ? om1 : (T)1);
         if (tid < STRIP_THREADS) {
             const int x = tid % N, y0 = (tid / N) * L;
 #pragma unroll
             for (int s0 = 0; s0 < L; s0 += LS) {
                 const int ys = y0 + s0;
                 T pt[C][LS + 2 * HY][2 * HY + 1];
-                auto cell = [&](int c, int r, int dx, int yy, int xx, T Y) {
-                    const T pn = first ? (T)0 : P[c * NN + yy * N + xx];
-                    const T pn1 = pn + tp * Y;
-                    pt[c][r + HY][dx + HY] = pn1 + om * (pn1 - pn);
-                    if (dx == 0 && r >= 0 && r < LS) pnew[c][s0 + r] = pn1;
-                };
 #pragma unroll
                 for (int c = 0; c < C; ++c)
 #pragma unroll
                     for (int dx = -HY; dx <= HY; ++dx) {
-                        const int xx = wrap<BC>(x + dx, N), px = pos(xx);
+                        const int px = pos(wrap<BC>(x + dx, N));
                         if constexpr (LS >= 2) {
                             // the strip's own rows, two per complex slot
 #pragma unroll
-                            for (int q = 0; q < LS / 2; ++q) {
-                                const cplx<T> z = S[rix<LOGN>(c * H + (ys >> 1) + q, px)];
-                                cell(c, 2 * q, dx, ys + 2 * q, xx, z.re);
-                                cell(c, 2 * q + 1, dx, ys + 2 * q + 1, xx, z.im);
+                            for (int h = 0; h < LS / 2; ++h) {
+                                const cplx<T> z = S[rix<LOGN>(c * H + (ys >> 1) + h, px)];
+                                pt[c][2 * h + HY][dx + HY] = z.re;
+                                pt[c][2 * h + 1 + HY][dx + HY] = z.im;
                             }
                         } else {
-                            const cplx<T> z = S[rix<LOGN>(c * H + (ys >> 1), px)];
-                            cell(c, 0, dx, ys, xx, (ys & 1) ? z.im : z.re);
+                            pt[c][HY][dx + HY] = rreal<T, LOGN>(S, c * H + (ys >> 1), 2 * px + (ys & 1));
                         }
                         // halo rows, through the boundary map
 #pragma unroll
@@ -473,8 +481,7 @@ __global__ __launch_bounds__(NT7) void k_step_wg(Slot *const *slots) {
                             if (r >= 0 && r < LS) continue;
                             if (!wg_needed<HY, LS>(r, dx)) continue;
                             const int yy = wrap<BC>(ys + r, N);
-                            const cplx<T> z = S[rix<LOGN>(c * H + (yy >> 1), px)];
-                            cell(c, r, dx, yy, xx, (yy & 1) ? z.im : z.re);
+                            pt[c][r + HY][dx + HY] = rreal<T, LOGN>(S, c * H + (yy >> 1), 2 * px + (yy & 1));
                         }
                     }
 #pragma unroll
@@ -499,14 +506,6 @@ __global__ __launch_bounds__(NT7) void k_step_wg(Slot *const *slots) {
             }
         }
         __syncthreads();
-        if (tid < STRIP_THREADS) {
-            const int x = tid % N, y0 = (tid / N) * L;
-#pragma unroll
-            for (int c = 0; c < C; ++c)
-#pragma unroll
-                for (int i = 0; i < L; ++i) P[c * NN + (y0 + i) * N + x] = pnew[c][i];
-        }
-        // the next reader of P is the next primal step, several barriers later
     };
 
     // ---- the initial state U_0 = U^k (or the pointwise reaction prox of U^k)
@@ -526,12 +525,12 @@ __global__ __launch_bounds__(NT7) void k_step_wg(Slot *const *slots) {
 
     if constexpr (MODE == MODE_F64) {
         initial(U);
-        residual64(U, [&](double res, double m) { stl = decide<K_INIT64>(stl, rule, res, m); });
+        residual64(U, true, [&](double res, double m) { stl = decide<K_INIT64>(stl, rule, res, m); });
         while (!stl.done) {
             const bool first = stl.iters == 0;
             precond();
-            primal_dual(first);
-            residual64(U, [&](double res, double m) { stl = decide<K_ITER64>(stl, rule, res, m); });
+            primal(first);
+            residual64(U, false, [&](double res, double m) { stl = decide<K_ITER64>(stl, rule, res, m); });
         }
         // the result where the batched path leaves it: U[iters & 1]
         double *out = (double *)s.U[stl.iters & 1];
@@ -540,13 +539,13 @@ __global__ __launch_bounds__(NT7) void k_step_wg(Slot *const *slots) {
     } else {
         // outer initial pass: U = U^k (or its prox) in FP64
         initial(U64);
-        residual64(U64, [&](double res, double m) { stl = decide<K_OUTER_INIT>(stl, rule, res, m); });
+        residual64(U64, true, [&](double res, double m) { stl = decide<K_OUTER_INIT>(stl, rule, res, m); });
         while (!stl.outer_done) {
             // inner FP32 loop on the correction e (e_0 = 0, P_0 = 0) from W = r
             while (!stl.done) {
                 const bool first = stl.iters == 0;
                 precond();
-                primal_dual(first);
+                primal(first);
                 residual32();
             }
             // outer update U += e, then r = F(U) in FP64 and the outer decision
@@ -554,7 +553,7 @@ __global__ __launch_bounds__(NT7) void k_step_wg(Slot *const *slots) {
                 for (int g = tid; g < C * NN; g += NT7) U64[g] += (double)U[g];
                 __syncthreads();
             }
-            residual64(U64, [&](double res, double m) { stl = decide<K_OUTER_UPD>(stl, rule, res, m); });
+            residual64(U64, true, [&](double res, double m) { stl = decide<K_OUTER_UPD>(stl, rule, res, m); });
         }
         double *out = s.U64[stl.outer & 1];
         if (out != U64)
