@@ -378,19 +378,33 @@ template <typename T, int LOGN, int EQ> constexpr bool rows_fused() {
 }
 
 // ---------------------------------------------------------------- deterministic block sums
-// Workgroup sum of K values per thread, in a fixed order (wave butterflies, then
-// the waves in order); the totals are valid in thread 0 only.
+// x plus the value that a lane-permuting move (DPP control CTRL) brings: lanes whose
+// source is outside the move's reach add 0.
+template <int CTRL> __device__ __forceinline__ double dpp_add(double x) {
+    const long long b = __builtin_bit_cast(long long, x);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return x + __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
+}
+// Sum over a wave in a fixed order, valid in lane 63: running sums within rows of 16
+// lanes (row_shr 1, 2, 4, 8), then across rows (row_bcast 15 and 31).  Six moves in the
+// VALU instead of six round trips through LDS, which cost a row pass about 0.5 us.
+__device__ __forceinline__ double wave_sum(double x) {
+    x = dpp_add<0x111>(x);
+    x = dpp_add<0x112>(x);
+    x = dpp_add<0x114>(x);
+    x = dpp_add<0x118>(x);
+    x = dpp_add<0x142>(x);
+    return dpp_add<0x143>(x);
+}
+// Workgroup sum of K values per thread, in a fixed order (wave sums, then the waves in
+// order); the totals are valid in thread 0 only.
 template <int K, int NTH = NT>
 __device__ __forceinline__ void block_sum(double *v, double *scratch /* K * NTH/64 */) {
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        double x = v[k];
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
-        v[k] = x;
-    }
+    for (int k = 0; k < K; ++k) v[k] = wave_sum(v[k]);
     const int wave = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
+    if ((threadIdx.x & 63) == 63) {
 #pragma unroll
         for (int k = 0; k < K; ++k) scratch[k * (NTH / 64) + wave] = v[k];
     }

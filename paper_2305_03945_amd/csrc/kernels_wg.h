@@ -55,32 +55,6 @@ template <typename T, int LOGN, int EQ> constexpr bool wg_step_available() {
     return LOGN <= WG_MAX_LOGN && EQ != EQ_FCH && WgPlan<T, LOGN, EQ == EQ_SCHNAK ? 2 : 1>::ok;
 }
 
-// Workgroup sum of K values per thread in a fixed order (wave butterflies, then
-// the waves in order); the totals are valid in thread 0.  red: K * NT7/64 doubles.
-template <int K> __device__ __forceinline__ void wg_sum(double *v, double *red) {
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        double x = v[k];
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
-        v[k] = x;
-    }
-    const int wave = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-        for (int k = 0; k < K; ++k) red[k * (NT7 / 64) + wave] = v[k];
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            double x = 0.0;
-            for (int w = 0; w < NT7 / 64; ++w) x += red[k * (NT7 / 64) + w];
-            v[k] = x;
-        }
-    }
-}
-
 // ---------------------------------------------------------------- column transforms in place
 // The column transforms run on the spectrum where the row pass left it (row pairs
 // packed per LDS region): element i of column job reg (component c = reg / H,
@@ -371,7 +345,7 @@ __global__ __launch_bounds__(NT7) void k_step_wg(Slot *const *slots) {
                 for (int c = 0; c < C; ++c) store_w(c, ys, x, W[c]);
             }
         }
-        wg_sum<2 * C>(acc, red);
+        block_sum<2 * C, NT7>(acc, red);
         if (tid == 0) {
             double res = 0.0, m = 0.0;
 #pragma unroll
@@ -427,7 +401,7 @@ __global__ __launch_bounds__(NT7) void k_step_wg(Slot *const *slots) {
                 for (int c = 0; c < C; ++c) store_w(c, ys, x, W[c]);
             }
         }
-        wg_sum<C>(acc, red);
+        block_sum<C, NT7>(acc, red);
         if (tid == 0) {
             double res = 0.0;
 #pragma unroll
