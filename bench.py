@@ -58,9 +58,13 @@ def iteration_hbm(kernels, alg_bytes_per_point, pts):
 #   rowfwd : read U_{n+1} and U^k (mixed: e, U_b, r), write the spectrum
 #   rows   : rowinv, upd and rowfwd in one launch: read the spectrum, U_n, U^k and Q,
 #            write U_{n+1}, Q and the spectrum (mixed: e, U_b, r and Q read)
+#   planeinv, planefwd : 3-D, rowinv with the inverse y pass, rowfwd with the forward one
+#            (the spectrum between them stays in LDS)
 BYTES_PER_POINT = {
-    "fp64": {"cols": 16, "rows": 56, "rowinv": 32, "upd": 24, "rowfwd": 24, "yfwd": 16, "zsym": 16, "yinv": 16},
-    "mixed": {"cols": 8, "rows": 32, "rowinv": 16, "upd": 16, "rowfwd": 16, "yfwd": 8, "zsym": 8, "yinv": 8},
+    "fp64": {"cols": 16, "rows": 56, "rowinv": 32, "upd": 24, "rowfwd": 24, "yfwd": 16, "zsym": 16, "yinv": 16,
+             "planeinv": 32, "planefwd": 24},
+    "mixed": {"cols": 8, "rows": 32, "rowinv": 16, "upd": 16, "rowfwd": 16, "yfwd": 8, "zsym": 8, "yinv": 8,
+              "planeinv": 16, "planefwd": 16},
 }
 
 
@@ -69,10 +73,15 @@ def log(*a):
 
 
 def launch_ms(ms):
-    """profile_iteration's durations by launch: "rows" where one launch makes the three
-    row-parallel steps."""
-    if ms.get("upd") == 0.0:
-        return {"cols": ms["cols"], "rows": ms["rowinv"]}
+    """profile_iteration's durations by launch: a launch that makes several steps has
+    given each of them an equal share (one row launch: "rows"; 3-D plane passes)."""
+    if "zsym" not in ms and ms["rowinv"] == ms["upd"] == ms["rowfwd"]:
+        return {"cols": ms["cols"], "rows": 3 * ms["rowinv"]}
+    if "zsym" in ms and ms["yinv"] == ms["rowinv"]:
+        out = {"zsym": ms["zsym"], "planeinv": 2 * ms["yinv"], "upd": ms["upd"]}
+        if ms["yfwd"] == ms["rowfwd"]:
+            return dict(out, planefwd=2 * ms["yfwd"])
+        return dict(out, yfwd=ms["yfwd"], rowfwd=ms["rowfwd"])
     return ms
 
 

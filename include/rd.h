@@ -243,11 +243,14 @@ rd_status rd_prox(rd_ctx *ctx, const rd_problem *prob, double h_t, const double 
  * on that stream), so each kernel runs in the cache state the real loop leaves.  ms_out
  * (HOST, 4 doubles on a 2-D grid, 6 on a 3-D one) receives the mean duration per launch
  * in milliseconds of, 2-D: column pass (with the stop decision of the preceding row
- * pass), inverse row pass + dual update, primal update, residual + forward row pass
- * (where one launch makes the last three, the second value is its duration and the
- * last two are 0);  3-D: forward y-line pass (with the stop decision of the preceding row pass), z-line
+ * pass), inverse row pass + dual update, primal update, residual + forward row pass;
+ * 3-D: forward y-line pass (with the stop decision of the preceding row pass), z-line
  * pass (forward, symbol, inverse), inverse y-line pass, inverse x-row pass + dual
- * update, primal update, residual + forward x-row pass.  Synchronises.                 */
+ * update, primal update, residual + forward x-row pass.  Where one launch makes several
+ * of these steps (2-D grids but the largest: the last three; 3-D up to 64^3: the
+ * inverse y and x passes, and the forward ones, with the stop decision in the z pass;
+ * 128^3 mixed: the inverse ones), its duration is shared equally among them.
+ * Synchronises.                                                                        */
 rd_status rd_profile_iteration(rd_ctx *ctx, const rd_problem *prob, const rd_opts *opts, double h_t,
                                const double *u_n, int32_t reps, void *hip_stream, double *ms_out);
 

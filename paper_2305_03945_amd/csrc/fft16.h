@@ -188,9 +188,16 @@ __device__ __forceinline__ void load_tw16(Tw16<T, LOGN, V> &w, const cplx<T> *__
 // gathered powers for this pass (unused when NS = 1).  Thread t of a transform
 // runs butterflies j = t + b N/V, b < V/R.
 //
+// x: accessor of the transform's elements (x(i): element i in LDS); a region is
+// Region<T, LOGN>{pointer}.
+template <typename T, int LOGN> struct Region {
+    cplx<T> *p;
+    __device__ __forceinline__ cplx<T> &operator()(int i) const { return p[lds_pad<LOGN>(i)]; }
+};
+
 // pass_in: the reads, twiddles and butterflies of the thread (outputs in v).
-template <typename T, int LOGN, int R, int NS, int DIR, int V = 16>
-__device__ __forceinline__ void pass_in(const cplx<T> *x, int t, const cplx<T> (*pw)[logv<V>()], cplx<T> (*v)[R]) {
+template <typename T, int LOGN, int R, int NS, int DIR, int V = 16, class X>
+__device__ __forceinline__ void pass_in(X x, int t, const cplx<T> (*pw)[logv<V>()], cplx<T> (*v)[R]) {
     constexpr int N = 1 << LOGN;
     constexpr int TPF = N / V;       // threads per transform
     constexpr int NB = N / R;        // butterflies
@@ -199,15 +206,15 @@ __device__ __forceinline__ void pass_in(const cplx<T> *x, int t, const cplx<T> (
     for (int b = 0; b < BPT; ++b) {
         const int j = t + b * TPF;
 #pragma unroll
-        for (int r = 0; r < R; ++r) v[b][r] = x[lds_pad<LOGN>(j + r * NB)];
+        for (int r = 0; r < R; ++r) v[b][r] = x(j + r * NB);
         if constexpr (NS > 1) twiddled_dft<T, R, DIR>(v[b], pw[b]);
         else dftR<T, R, DIR>(v[b]);
     }
 }
 
 // pass_out: the Stockham writes of the thread's butterfly outputs.
-template <typename T, int LOGN, int R, int NS, int V = 16>
-__device__ __forceinline__ void pass_out(cplx<T> *x, int t, const cplx<T> (*v)[R]) {
+template <typename T, int LOGN, int R, int NS, int V = 16, class X>
+__device__ __forceinline__ void pass_out(X x, int t, const cplx<T> (*v)[R]) {
     constexpr int TPF = (1 << LOGN) / V;
 #pragma unroll
     for (int b = 0; b < V / R; ++b) {
@@ -215,7 +222,7 @@ __device__ __forceinline__ void pass_out(cplx<T> *x, int t, const cplx<T> (*v)[R
         const int k = j & (NS - 1);
         const int base = (j - k) * R + k;
 #pragma unroll
-        for (int q = 0; q < R; ++q) x[lds_pad<LOGN>(base + q * NS)] = v[b][q];
+        for (int q = 0; q < R; ++q) x(base + q * NS) = v[b][q];
     }
 }
 
@@ -231,8 +238,8 @@ template <bool WAVE> __device__ __forceinline__ void pass_sync() {
     }
 }
 
-template <typename T, int LOGN, int R, int NS, int DIR, int V = 16, bool WAVE = false>
-__device__ __forceinline__ void pass16(cplx<T> *x, int t, bool active, const cplx<T> (*pw)[logv<V>()]) {
+template <typename T, int LOGN, int R, int NS, int DIR, int V = 16, bool WAVE = false, class X>
+__device__ __forceinline__ void pass16(X x, int t, bool active, const cplx<T> (*pw)[logv<V>()]) {
     cplx<T> v[V / R][R];
     if (active) pass_in<T, LOGN, R, NS, DIR, V>(x, t, pw, v);
     pass_sync<WAVE>();
@@ -240,8 +247,8 @@ __device__ __forceinline__ void pass16(cplx<T> *x, int t, bool active, const cpl
     pass_sync<WAVE>();
 }
 
-template <typename T, int LOGN, int DIR, int DONE, int V, bool WAVE>
-__device__ __forceinline__ void passes16(cplx<T> *x, int t, bool active, const Tw16<T, LOGN, V> &w) {
+template <typename T, int LOGN, int DIR, int DONE, int V, bool WAVE, class X>
+__device__ __forceinline__ void passes16(X x, int t, bool active, const Tw16<T, LOGN, V> &w) {
     if constexpr (DONE < LOGN) {
         constexpr int q = DONE / logv<V>();
         constexpr int R = pass_radix<LOGN, V>(q);
@@ -270,26 +277,27 @@ template <int LOGN, int V = 16> __host__ __device__ constexpr int last_slot(int 
 }
 
 // Middle passes q = 1 .. npasses - 2 (all radix V), each ending with a barrier.
-template <typename T, int LOGN, int DIR, int Q, int V>
-__device__ __forceinline__ void middle_passes(cplx<T> *x, int t, const Tw16<T, LOGN, V> &w) {
+template <typename T, int LOGN, int DIR, int Q, int V, class X>
+__device__ __forceinline__ void middle_passes(X x, int t, const Tw16<T, LOGN, V> &w) {
     if constexpr (Q < npasses16<LOGN, V>() - 1) {
         pass16<T, LOGN, V, (1 << (logv<V>() * Q)), DIR, V>(x, t, true, w.p[Q - 1]);
         middle_passes<T, LOGN, DIR, Q + 1, V>(x, t, w);
     }
 }
 
-// Transform of one region x whose input v (stride order) is in registers; the
+// Transform of one region whose input v (stride order) is in registers; the
 // output is left in v (stride order).  Needs at least two passes.  Starts by
-// writing x (the caller makes sure no thread still reads it) and ends with the
-// last pass's reads of x (the caller places a barrier before x is rewritten).
+// writing the region (the caller makes sure no thread still reads it) and ends with the
+// last pass's reads of it (the caller places a barrier before it is rewritten).
 template <typename T, int LOGN, int DIR, int V>
-__device__ __forceinline__ void fft16_regs(cplx<T> *x, int t, const Tw16<T, LOGN, V> &w, cplx<T> *v) {
+__device__ __forceinline__ void fft16_regs(cplx<T> *region, int t, const Tw16<T, LOGN, V> &w, cplx<T> *v) {
+    const Region<T, LOGN> x{region};
     static_assert(npasses16<LOGN, V>() >= 2, "register-ended transforms need two passes");
     constexpr int NP = npasses16<LOGN, V>();
     constexpr int RL = last_radix<LOGN, V>();
     dftR<T, V, DIR>(v);
 #pragma unroll
-    for (int q = 0; q < V; ++q) x[lds_pad<LOGN>(V * t + q)] = v[q];
+    for (int q = 0; q < V; ++q) x(V * t + q) = v[q];
     __syncthreads();
     middle_passes<T, LOGN, DIR, 1, V>(x, t, w);
     cplx<T> o[V / RL][RL];
@@ -315,7 +323,8 @@ __device__ __forceinline__ void wg_fft16(cplx<T> *buf, const Tw16<T, LOGN, V> &w
     for (int g = 0; g < NREG; g += NTEAMS) {
         const int reg = g + team;
         const bool active = reg < NREG;
-        passes16<T, LOGN, DIR, 0, V, WAVE>(buf + (active ? reg : 0) * lds_region<LOGN>(), t, active, w);
+        const Region<T, LOGN> x{buf + (active ? reg : 0) * lds_region<LOGN>()};
+        passes16<T, LOGN, DIR, 0, V, WAVE>(x, t, active, w);
     }
     if constexpr (WAVE) __syncthreads();
 }

@@ -5,7 +5,7 @@
 //
 // Fields are [c][z][y][x], x fastest.  The spectrum S3 holds, for every
 // component and (z, y) row, N/2 complex slots, row-major: S3[c][z][y][j].
-// One iteration is six launches:
+// One iteration is six launches (fewer where planes fit in LDS: "plane passes" below):
 //   k3_rowinv      inverse x-transforms of Y -> P_{n+1}, P~ (eqs. 21-22)
 //   k3_upd         U_{n+1} = U_n - tau_u grad F(U_n)^T P~ (eq. 23)
 //   k3_row_forward W = F(U_{n+1}) (or F~(e), or the mixed outer update), partial
@@ -657,14 +657,15 @@ __device__ __forceinline__ void lines_regs(SlotRef s, int c, int w, int j0, cplx
 
 // Lines of CB adjacent slots.  YFWD / YINV: the lines along y of plane (c, z);
 // ZSYM: the lines along z of row q (the y-transformed index) of component c.
-// FIN >= 0 (forward y pass only): one extra workgroup, block 0, takes the stop
-// decision of the preceding row pass of kind FIN, as in the 2-D column pass.
-template <typename T, int LOGN, int BC, int C, int PASS, int FIN>
+// FIN >= 0 (the first pass of an iteration only): one extra workgroup, block 0, takes
+// the stop decision of the preceding row pass of kind FIN, as in the 2-D column pass.
+// HEAD: the pass is the first of an iteration.
+template <typename T, int LOGN, int BC, int C, int PASS, int FIN, bool HEAD>
 __global__ __launch_bounds__((line_threads<T, LOGN>())) void k3_lines(Slot *const *slots) {
     constexpr int N = 1 << LOGN, H = N / 2;
     constexpr int CB = line_cb<T, LOGN>();
     constexpr int NTH = line_threads<T, LOGN>();
-    static_assert(FIN == FIN_NONE || PASS == L3_YFWD, "only the forward y pass takes a decision");
+    static_assert(FIN == FIN_NONE || HEAD, "only the first pass of an iteration takes a decision");
     __shared__ cplx<T> buf[CB * lds_region<LOGN>()];
     __shared__ double lanes[FIN == FIN_NONE ? 1 : 64 * 2 * C];
     SlotRef s = slot_of(slots);
@@ -675,10 +676,10 @@ __global__ __launch_bounds__((line_threads<T, LOGN>())) void k3_lines(Slot *cons
             return;
         }
     }
-    // The forward y pass transforms unless the step is finished (after a mixed
-    // outer update it is the first iteration of the next inner loop, while its
-    // decision workgroup runs); the later line passes see a decided State.
-    if (PASS == L3_YFWD ? sst.outer_done != 0 : sst.done != 0) return;
+    // The first pass transforms unless the step is finished (after a mixed outer
+    // update it is the first iteration of the next inner loop, while its decision
+    // workgroup runs); the later line passes see a decided State.
+    if (HEAD ? sst.outer_done != 0 : sst.done != 0) return;
     // blockIdx.x -> (component, plane or row, first slot); CB divides N/2
     // 256^3: consecutive blocks (adjacent slot groups, then lines) on one XCD
     // (FP64 line passes 20-25 % faster there; at 128^3 the round-robin order is
@@ -727,6 +728,244 @@ __global__ __launch_bounds__((line_threads<T, LOGN>())) void k3_lines(Slot *cons
         const int reg = idx % CB, p = idx / CB;
         const int pos = (PASS == L3_YFWD || BC == BC_P) ? p : dct_pos(p, N);
         S[off(p, j0 + reg)] = buf[rix<LOGN>(reg, pos)];
+    }
+}
+
+// ---------------------------------------------------------------- plane passes
+// A whole plane of one component fits in a workgroup's LDS (128^2 FP64: 139 KB), so its
+// x and y transforms can be one pass: the inverse y pass goes on to the rows and the
+// dual update, the row pass to the y transforms.  A plane's rows are packed in pairs,
+// one region of N complex values per pair (row 2p's slots, then row 2p + 1's), and the y
+// transforms run on that layout through an address map.  With both passes an iteration is
+// four launches (z lines, inverse plane, primal update, forward plane) instead of six,
+// and the spectrum makes two round trips fewer.
+//
+// There are N workgroups per component, so this trades bandwidth (128^3: half the CUs)
+// for launches and serial latency.  Steps, us, six launches -> plane passes, mixed: 64^3
+// 578 -> 513, 32^3 459 -> 334, 16^3 306 -> 228; FP64 64^3 671 -> 602.  128^3, mixed: 1077
+// with neither, 1031 with the inverse pass, 1125 with both (its FP64 outer updates take 52
+// instead of 20 us on 128 workgroups); FP64 2152 with neither, 2159 with the inverse one.
+template <typename T, int LOGN> constexpr int plane_threads() {
+    constexpr int t = (1 << LOGN) / 2 * ((1 << LOGN) / 8);
+    return t < 256 ? 256 : t;
+}
+// Which sides of an iteration take plane passes (the forward one only with the inverse).
+template <typename T, int LOGN> constexpr bool plane_inverse() { return LOGN <= 6 || (LOGN == 7 && sizeof(T) == 4); }
+template <int LOGN> constexpr bool plane_forward() { return LOGN <= 6; }
+
+// Element i of slot kx's y line.  NATURAL: row i; else in transform order (Neumann: the
+// row whose Makhoul position is i).
+template <typename T, int LOGN, int BC, bool NATURAL> struct PlaneLine {
+    cplx<T> *buf;
+    int kx;
+    __device__ __forceinline__ cplx<T> &operator()(int i) const {
+        constexpr int N = 1 << LOGN, H = N / 2;
+        const int y = (NATURAL || BC == BC_P) ? i : i < H ? 2 * i : 2 * (N - 1 - i) + 1;
+        return buf[rix<LOGN>(y >> 1, (y & 1) * H + kx)];
+    }
+};
+
+// The y transforms of every slot of a plane; consecutive lanes take consecutive slots
+// (contiguous in LDS).  Ends with a barrier.
+template <typename T, int LOGN, int BC, int DIR, int NTH>
+__device__ __forceinline__ void plane_fft_y(cplx<T> *buf, const Tw16<T, LOGN, 8> &w) {
+    constexpr int N = 1 << LOGN, H = N / 2;
+    const bool active = threadIdx.x < H * (N / 8);
+    const PlaneLine<T, LOGN, BC, false> x{buf, (int)threadIdx.x % H};
+    passes16<T, LOGN, DIR, 0, 8, false>(x, active ? threadIdx.x / H : 0, active, w);
+}
+
+// The two real sequences packed in a line (periodic: slot 0 only), as rows_post_forward
+// and rows_pre_inverse do for a pair of rows, on the lines of a plane.
+template <typename T, int LOGN, int BC, int NTH, bool INVERSE>
+__device__ __forceinline__ void plane_pairs_y(cplx<T> *buf, const cplx<T> *__restrict__ twd) {
+    constexpr int N = 1 << LOGN, H = N / 2;
+    constexpr int LINES = BC == BC_P ? 1 : H;
+    constexpr int IPT = (LINES * H + NTH - 1) / NTH;
+    cplx<T> oa[IPT], ob[IPT];
+    auto real_at = [&](int kx, int m) -> T & {
+        return reinterpret_cast<T *>(&PlaneLine<T, LOGN, BC, true>{buf, kx}(m >> 1))[m & 1];
+    };
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) {
+        const int it = threadIdx.x + i * NTH;
+        if (it >= LINES * H) break;
+        const int kx = it % LINES, l = it / LINES;
+        const PlaneLine<T, LOGN, BC, false> z{buf, kx};
+        if constexpr (!INVERSE) {
+            const cplx<T> zl = z(l), zn = z(l == 0 ? H : N - l);
+            if (l == 0) {
+                const T s = BC == BC_P ? (T)1 : (T)0.707106781186547524400844362104849039;
+                oa[i] = {zl.re, s * zn.re};
+                ob[i] = {zl.im, s * zn.im};
+            } else {
+                const cplx<T> A = {(zl.re + zn.re) * (T)0.5, (zl.im - zn.im) * (T)0.5};
+                const cplx<T> B = {(zl.im + zn.im) * (T)0.5, (zn.re - zl.re) * (T)0.5};
+                if constexpr (BC == BC_P) {
+                    oa[i] = A;
+                    ob[i] = B;
+                } else {
+                    const cplx<T> w = twd[l];
+                    const cplx<T> qa = cmul(A, w), qb = cmul(B, w);
+                    oa[i] = {qa.re, -qa.im};
+                    ob[i] = {qb.re, -qb.im};
+                }
+            }
+        } else if constexpr (BC == BC_P) {
+            const cplx<T> a = z(l), b = z(H + l);
+            oa[i] = l == 0 ? cplx<T>{a.re, b.re} : cplx<T>{a.re - b.im, a.im + b.re};
+            ob[i] = l == 0 ? cplx<T>{a.im, b.im} : cplx<T>{a.re + b.im, b.re - a.im};
+        } else {
+            if (l == 0) {
+                const T r2 = (T)1.41421356237309504880168872420969808;
+                oa[i] = {real_at(kx, 0), real_at(kx, N)};
+                ob[i] = {r2 * real_at(kx, H), r2 * real_at(kx, N + H)};
+            } else {
+                const cplx<T> wc = cconj(twd[l]);
+                const cplx<T> va = cmul(wc, cplx<T>{real_at(kx, l), -real_at(kx, N - l)});
+                const cplx<T> vb = cmul(wc, cplx<T>{real_at(kx, N + l), -real_at(kx, 2 * N - l)});
+                oa[i] = {va.re - vb.im, va.im + vb.re};
+                ob[i] = {va.re + vb.im, vb.re - va.im};
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) {
+        const int it = threadIdx.x + i * NTH;
+        if (it >= LINES * H) break;
+        const int kx = it % LINES, l = it / LINES;
+        const PlaneLine<T, LOGN, BC, false> z{buf, kx};
+        if constexpr (INVERSE) {
+            z(l) = oa[i];
+            z(l == 0 ? H : N - l) = ob[i];
+        } else if constexpr (BC == BC_P) {
+            z(l) = oa[i];
+            z(H + l) = ob[i];
+        } else {
+            real_at(kx, l) = oa[i].re;
+            real_at(kx, l == 0 ? H : N - l) = oa[i].im;
+            real_at(kx, N + l) = ob[i].re;
+            real_at(kx, l == 0 ? N + H : 2 * N - l) = ob[i].im;
+        }
+    }
+    __syncthreads();
+}
+
+// Forward plane pass: the row-forward quantity of plane z (all kinds of produce3_W4),
+// partial norms, x and y transforms of component c's plane.  Workgroup = (c, z); with
+// two components both workgroups of a plane evaluate both (and store the same side
+// results), and each sums and transforms its own.
+template <typename T, int LOGN, int BC, int EQ, int KIND>
+__device__ __forceinline__ void plane_forward_pass(SlotRef s, StateRef sst, cplx<T> *buf, double *scratch) {
+    constexpr int N = 1 << LOGN, H = N / 2;
+    constexpr int C = EQ == EQ_SCHNAK ? 2 : 1;
+    constexpr int NTH = plane_threads<T, LOGN>();
+    const int tile = xcd_tile(blockIdx.x, gridDim.x);
+    const int z = tile / C, c = tile % C;
+    Tw16<T, LOGN, 8> twx, twy;
+    load_tw16<T, LOGN, 8>(twx, (const cplx<T> *)s.tw);
+    load_tw16<T, LOGN, 8>(twy, (const cplx<T> *)s.tw, (int)threadIdx.x / H % (N / 8));
+    double acc[2 * C];
+#pragma unroll
+    for (int k = 0; k < 2 * C; ++k) acc[k] = 0.0;
+#pragma unroll 2
+    for (int idx = threadIdx.x; idx < N * N / 4; idx += NTH) {
+        const int y = idx >> (LOGN - 2), x0 = (idx & (N / 4 - 1)) * 4;
+        T wv[4][C];
+        produce3_W4<T, LOGN, BC, EQ, KIND>(s, sst, z, y, x0, wv, acc);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int pos = (BC == BC_P) ? x0 + k : dct_pos(x0 + k, N);
+            rreal<T, LOGN>(buf, y / 2, 2 * pos + (y & 1)) = C == 2 && c == 1 ? wv[k][C - 1] : wv[k][0];
+        }
+    }
+    __syncthreads();
+    const cplx<T> *twd = (const cplx<T> *)s.twd;
+    wg_fft16<T, LOGN, -1, H, NTH>(buf, twx);
+    rows_post_forward<T, LOGN, BC, H, NTH>(buf, twd);
+    plane_fft_y<T, LOGN, BC, -1, NTH>(buf, twy);
+    plane_pairs_y<T, LOGN, BC, NTH, false>(buf, twd);
+    cplx<T> *S = (cplx<T> *)s.S;
+    for (int idx = threadIdx.x; idx < N * H; idx += NTH) {
+        const int j = idx % H, y = idx / H;
+        S[s3_off<LOGN>(c, z, y, j)] = PlaneLine<T, LOGN, BC, true>{buf, j}(y);
+    }
+    block_sum<2 * C, NTH>(acc, scratch);
+    if (threadIdx.x == 0) {
+        s.partials[z * (2 * C) + c] = c == 0 ? acc[0] : acc[C - 1];
+        s.partials[z * (2 * C) + C + c] = c == 0 ? acc[C] : acc[2 * C - 1];
+    }
+}
+
+template <typename T, int LOGN, int BC, int EQ, int KIND>
+__global__ __launch_bounds__((plane_threads<T, LOGN>())) void k3_plane_forward(Slot *const *slots) {
+    constexpr int C = EQ == EQ_SCHNAK ? 2 : 1;
+    __shared__ cplx<T> buf[(1 << LOGN) / 2 * lds_region<LOGN>()];
+    __shared__ double scratch[2 * C * (plane_threads<T, LOGN>() / 64)];
+    SlotRef s = slot_of(slots);
+    StateRef sst = state_of(s);
+    if (skip_launch<KIND>(sst)) return;
+    if constexpr (KIND == K_MIXED) {
+        if (sst.done) plane_forward_pass<T, LOGN, BC, EQ, K_OUTER_UPD>(s, sst, buf, scratch);
+        else plane_forward_pass<T, LOGN, BC, EQ, K_INNER32>(s, sst, buf, scratch);
+    } else {
+        plane_forward_pass<T, LOGN, BC, EQ, KIND>(s, sst, buf, scratch);
+    }
+}
+
+// Inverse plane pass: inverse y and x transforms of component c's plane z, and the dual
+// update (as k3_rowinv).
+template <typename T, int LOGN, int BC, int C>
+__global__ __launch_bounds__((plane_threads<T, LOGN>())) void k3_plane_inverse(Slot *const *slots) {
+    constexpr int N = 1 << LOGN, H = N / 2;
+    constexpr int NTH = plane_threads<T, LOGN>();
+    constexpr size_t NN = (size_t)N * N * N;
+    __shared__ cplx<T> buf[H * lds_region<LOGN>()];
+    SlotRef s = slot_of(slots);
+    StateRef sst = state_of(s);
+    if (skip_launch<K_ITER64>(sst)) return;
+    const int z = blockIdx.x / C, c = blockIdx.x % C;
+    const cplx<T> *S = (const cplx<T> *)s.S;
+    Tw16<T, LOGN, 8> twx, twy;
+    load_tw16<T, LOGN, 8>(twx, (const cplx<T> *)s.tw);
+    load_tw16<T, LOGN, 8>(twy, (const cplx<T> *)s.tw, (int)threadIdx.x / H % (N / 8));
+#pragma unroll 8
+    for (int idx = threadIdx.x; idx < N * H; idx += NTH) {
+        const int j = idx % H, y = idx / H;
+        PlaneLine<T, LOGN, BC, true>{buf, j}(y) = S[s3_off<LOGN>(c, z, y, j)];
+    }
+    __syncthreads();
+    const cplx<T> *twd = (const cplx<T> *)s.twd;
+    plane_pairs_y<T, LOGN, BC, NTH, true>(buf, twd);
+    plane_fft_y<T, LOGN, BC, +1, NTH>(buf, twy);
+    rows_pre_inverse<T, LOGN, BC, H, NTH>(buf, twd);
+    wg_fft16<T, LOGN, +1, H, NTH>(buf, twx);
+    const auto P = gp((T *)s.P);
+    const auto Pt = gp((T *)s.Pt);
+    const T tp = (T)s.tau_p, om = (T)s.omega;
+    const bool first = sst.iters == 0;
+#pragma unroll 4
+    for (int idx = threadIdx.x; idx < N * N / 4; idx += NTH) {
+        const int x0 = (idx & (N / 4 - 1)) * 4, y = idx >> (LOGN - 2);
+        const size_t g = c * NN + ((size_t)z * N + y) * N + x0;
+        vec4_t<T> Pn;
+        if (first) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) Pn[k] = (T)0;
+        } else {
+            Pn = load4<T>(P + g);
+        }
+        vec4_t<T> Pn1, Ptl;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int pos = (BC == BC_P) ? x0 + k : dct_pos(x0 + k, N);
+            const T Y = rreal<T, LOGN>(buf, y / 2, 2 * pos + (y & 1));
+            Pn1[k] = Pn[k] + tp * Y;
+            Ptl[k] = Pn1[k] + om * (Pn1[k] - Pn[k]);
+        }
+        store4<T>(P + g, Pn1);
+        store4<T>(Pt + g, Ptl);
     }
 }
 

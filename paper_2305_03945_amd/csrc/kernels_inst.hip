@@ -155,13 +155,13 @@ void launch3_rowfwd_fin(Slot *const *slots, int nslots, hipStream_t st, hipEvent
                           slots);
 }
 
-template <typename T, int BC, int EQ, int PASS, int FIN>
+template <typename T, int BC, int EQ, int PASS, int FIN, bool HEAD = PASS == L3_YFWD>
 void launch3_lines(Slot *const *slots, int nslots, hipStream_t st, hipEvent_t *ev) {
     constexpr int N = 1 << L;
     constexpr int CB = line_cb<T, L>();
     static_assert((N / 2) % CB == 0, "line blocks must tile the slots");
     constexpr int extra = FIN == FIN_NONE ? 0 : 1;
-    hipExtLaunchKernelGGL((k3_lines<T, L, BC, ncomp<EQ>(), PASS, FIN>),
+    hipExtLaunchKernelGGL((k3_lines<T, L, BC, ncomp<EQ>(), PASS, FIN, HEAD>),
                           dim3(ncomp<EQ>() * N * ((N / 2) / CB) + extra, nslots), dim3(line_threads<T, L>()), 0, st,
                           ev_start(ev), ev_stop(ev), 0, slots);
 }
@@ -188,6 +188,26 @@ void launch3_upd(Slot *const *slots, int nslots, hipStream_t st, hipEvent_t *ev)
                           ev_start(ev), ev_stop(ev), 0, slots);
 }
 
+template <typename T, int BC, int EQ, int KIND>
+void launch3_plane_fwd(Slot *const *slots, int nslots, hipStream_t st, hipEvent_t *ev) {
+    hipExtLaunchKernelGGL((k3_plane_forward<T, L, BC, EQ, KIND>), dim3(ncomp<EQ>() * (1 << L), nslots),
+                          dim3(plane_threads<T, L>()), 0, st, ev_start(ev), ev_stop(ev), 0, slots);
+}
+
+// Initial pass: plane kernel, then its decision at once.
+template <typename T, int BC, int EQ, int KIND>
+void launch3_plane_init(Slot *const *slots, int nslots, hipStream_t st, hipEvent_t *ev) {
+    hipEvent_t e0[2] = {ev_start(ev), nullptr}, e1[2] = {nullptr, ev_stop(ev)};
+    launch3_plane_fwd<T, BC, EQ, KIND>(slots, nslots, st, e0);
+    launch_fin<KIND, EQ>(slots, nslots, st, e1);
+}
+
+template <typename T, int BC, int EQ>
+void launch3_plane_inv(Slot *const *slots, int nslots, hipStream_t st, hipEvent_t *ev) {
+    hipExtLaunchKernelGGL((k3_plane_inverse<T, L, BC, ncomp<EQ>()>), dim3(ncomp<EQ>() * (1 << L), nslots),
+                          dim3(plane_threads<T, L>()), 0, st, ev_start(ev), ev_stop(ev), 0, slots);
+}
+
 template <typename T, int BC, int EQ>
 void launch3_tin(Slot *const *slots, int nslots, const double *in, double *, hipStream_t st) {
     constexpr int R = row_block3<T, EQ>();
@@ -208,18 +228,28 @@ template <typename T, int BC, int EQ, int MODE> void fill3_mode(KSet &k) {
     constexpr bool f64 = MODE == MODE_F64;
     // mixed: the row pass makes the outer update itself (as in 2-D)
     constexpr int KIT = f64 ? K_ITER64 : K_MIXED;
-    k.init = launch3_rowfwd_fin<T, BC, EQ, f64 ? K_INIT64 : K_OUTER_INIT>;
-    k.rowfwd = launch3_rowfwd<T, BC, EQ, KIT>;
     k.fin = launch_fin<KIT, EQ>;
+    // the line passes serve the preconditioner alone on every grid
     k.yfwd = launch3_lines<T, BC, EQ, L3_YFWD, FIN_NONE>;
-    k.yfwd_fin = launch3_lines<T, BC, EQ, L3_YFWD, KIT>;
     k.zsym = launch3_lines<T, BC, EQ, L3_ZSYM, FIN_NONE>;
     k.yinv = launch3_lines<T, BC, EQ, L3_YINV, FIN_NONE>;
-    k.rowinv = launch3_rowinv<T, BC, EQ>;
+    if constexpr (plane_inverse<T, L>()) k.plane_inv = launch3_plane_inv<T, BC, EQ>;
+    else k.rowinv = launch3_rowinv<T, BC, EQ>;
+    if constexpr (plane_forward<L>()) {
+        k.init = launch3_plane_init<T, BC, EQ, f64 ? K_INIT64 : K_OUTER_INIT>;
+        k.zsym_head = launch3_lines<T, BC, EQ, L3_ZSYM, FIN_NONE, true>;
+        k.zsym_fin = launch3_lines<T, BC, EQ, L3_ZSYM, KIT, true>;
+        k.plane_fwd = launch3_plane_fwd<T, BC, EQ, KIT>;
+    } else {
+        k.init = launch3_rowfwd_fin<T, BC, EQ, f64 ? K_INIT64 : K_OUTER_INIT>;
+        k.rowfwd = launch3_rowfwd<T, BC, EQ, KIT>;
+        k.yfwd_fin = launch3_lines<T, BC, EQ, L3_YFWD, KIT>;
+    }
     k.upd = launch3_upd<T, BC, EQ, MODE>;
     k.tin = launch3_tin<T, BC, EQ>;
     k.tout = launch3_tout<T, BC, EQ>;
-    k.rows_per_block = row_block3<T, EQ>();
+    // rows behind one partial norm
+    k.rows_per_block = plane_forward<L>() ? 1 << L : row_block3<T, EQ>();
     k.dim = 3;
 }
 

@@ -25,6 +25,10 @@ struct KSet {
     launch_fn step_wg = nullptr;    // small grids: the whole step, one workgroup per slot (k_step_wg)
     launch_fn yfwd = nullptr;       // 3-D: forward y-transforms
     launch_fn yfwd_fin = nullptr;   // 3-D: the same, plus the stop decision of the preceding row pass
+    launch_fn plane_inv = nullptr;  // 3-D, where set: yinv and rowinv in one launch
+    launch_fn plane_fwd = nullptr;  // 3-D, where set: rowfwd and the next yfwd in one launch
+    launch_fn zsym_head = nullptr;  // 3-D plane passes: zsym as the first pass of an iteration
+    launch_fn zsym_fin = nullptr;   // the same, plus the stop decision of the preceding plane pass
     launch_fn zsym = nullptr;       // 3-D: forward z-transform, symbol, inverse z-transform
     launch_fn yinv = nullptr;       // 3-D: inverse y-transforms
     launch_io_fn tin = nullptr;     // precond-only: FP64 W -> row transforms into S

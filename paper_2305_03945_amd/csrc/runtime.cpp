@@ -551,12 +551,20 @@ void bind_workspace(Slot &s, const Workspace &w, const Tables &t, const KSet &k)
 void enqueue_round(const KSet &k, Slot *const *slots, int nslots, int iters, hipStream_t st) {
     if (k.dim == 3) {
         for (int i = 0; i < iters; ++i) {
-            (i == 0 ? k.yfwd : k.yfwd_fin)(slots, nslots, st, nullptr);
-            k.zsym(slots, nslots, st, nullptr);
-            k.yinv(slots, nslots, st, nullptr);
-            k.rowinv(slots, nslots, st, nullptr);
+            if (k.plane_fwd) {
+                (i == 0 ? k.zsym_head : k.zsym_fin)(slots, nslots, st, nullptr);
+            } else {
+                (i == 0 ? k.yfwd : k.yfwd_fin)(slots, nslots, st, nullptr);
+                k.zsym(slots, nslots, st, nullptr);
+            }
+            if (k.plane_inv) {
+                k.plane_inv(slots, nslots, st, nullptr);
+            } else {
+                k.yinv(slots, nslots, st, nullptr);
+                k.rowinv(slots, nslots, st, nullptr);
+            }
             k.upd(slots, nslots, st, nullptr);
-            k.rowfwd(slots, nslots, st, nullptr);
+            (k.plane_fwd ? k.plane_fwd : k.rowfwd)(slots, nslots, st, nullptr);
         }
         k.fin(slots, nslots, st, nullptr);
         return;
@@ -985,7 +993,11 @@ rd_status rd_profile_iteration(rd_ctx *ctx, const rd_problem *prob, const rd_opt
     // The solver's launch order of one iteration (the stop decision of a row pass is
     // taken by the next column pass, 2-D, or forward y pass, 3-D).
     std::vector<launch_fn> fns;
-    if (d.dim == 3)
+    if (k.plane_fwd)   // with it, always the inverse plane pass too
+        fns = {k.zsym_fin, k.plane_inv, k.upd, k.plane_fwd};
+    else if (k.plane_inv)
+        fns = {k.yfwd_fin, k.zsym, k.plane_inv, k.upd, k.rowfwd};
+    else if (d.dim == 3)
         fns = {k.yfwd_fin, k.zsym, k.yinv, k.rowinv, k.upd, k.rowfwd};
     else if (k.rows)
         fns = {k.cols_fin, k.rows};
@@ -995,7 +1007,8 @@ rd_status rd_profile_iteration(rd_ctx *ctx, const rd_problem *prob, const rd_opt
     // One untimed iteration from the initial state (whose decision the initial
     // pass has taken).
     for (int kk = 0; kk < nk; ++kk)
-        (kk == 0 ? (d.dim == 3 ? k.yfwd : k.cols) : fns[kk])(w->slot_list_dev, 1, st, nullptr);
+        (kk == 0 ? (k.plane_fwd ? k.zsym_head : d.dim == 3 ? k.yfwd : k.cols) : fns[kk])(w->slot_list_dev, 1, st,
+                                                                                         nullptr);
     RD_CHECK(hipGetLastError());
     RD_CHECK(hipStreamSynchronize(st));
     // No stop rule may end the timed iterations: tolerance 0 and max_iter 2^30 are
@@ -1020,7 +1033,7 @@ rd_status rd_profile_iteration(rd_ctx *ctx, const rd_problem *prob, const rd_opt
         for (int kk = 0; kk < nk; ++kk) fns[kk](w->slot_list_dev, 1, st, &ev[2 * (nk * i + kk)]);
     RD_CHECK(hipGetLastError());
     RD_CHECK(hipStreamSynchronize(st));
-    for (int kk = nk; kk < 4; ++kk) ms_out[kk] = 0.0;   // steps that the one row launch covers
+    std::vector<double> ms_of(nk);
     for (int kk = 0; kk < nk; ++kk) {
         double tot = 0.0;
         for (int i = 0; i < reps; ++i) {
@@ -1028,9 +1041,27 @@ rd_status rd_profile_iteration(rd_ctx *ctx, const rd_problem *prob, const rd_opt
             RD_CHECK(hipEventElapsedTime(&ms, ev[2 * (nk * i + kk)], ev[2 * (nk * i + kk) + 1]));
             tot += ms;
         }
-        ms_out[kk] = tot / reps;
+        ms_of[kk] = tot / reps;
     }
     for (auto &e : ev) (void)hipEventDestroy(e);
+    // a launch that makes several of the documented steps is shared equally among them
+    if (k.plane_fwd) {
+        ms_out[0] = ms_out[5] = ms_of[3] / 2;
+        ms_out[1] = ms_of[0];
+        ms_out[2] = ms_out[3] = ms_of[1] / 2;
+        ms_out[4] = ms_of[2];
+    } else if (k.plane_inv) {
+        ms_out[0] = ms_of[0];
+        ms_out[1] = ms_of[1];
+        ms_out[2] = ms_out[3] = ms_of[2] / 2;
+        ms_out[4] = ms_of[3];
+        ms_out[5] = ms_of[4];
+    } else if (d.dim == 2 && k.rows) {
+        ms_out[0] = ms_of[0];
+        ms_out[1] = ms_out[2] = ms_out[3] = ms_of[1] / 3;
+    } else {
+        for (int kk = 0; kk < nk; ++kk) ms_out[kk] = ms_of[kk];
+    }
     return RD_OK;
 }
 

@@ -292,8 +292,7 @@ class Context:
 
     def profile_iteration(self, u, ht, problem, opts, reps=20, stream=None):
         """Mean launch duration (ms) of each kernel of one iteration, HIP events on `stream`.
-        Where one launch makes the row-parallel steps (2-D grids but the largest), its
-        duration is "rowinv" and "upd" and "rowfwd" are 0."""
+        A launch that makes several of the steps is shared equally among them."""
         out = (ctypes.c_double * 6)()
         _check(_lib.rd_profile_iteration(self._h, ctypes.byref(problem), ctypes.byref(opts), float(ht), _dptr(u, problem),
                                          int(reps), _stream_ptr(stream), out), "rd_profile_iteration")
