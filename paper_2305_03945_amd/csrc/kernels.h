@@ -1007,14 +1007,18 @@ __global__ __launch_bounds__(NT) void k_row_forward(Slot *const *slots) {
 constexpr int COL_TEAM_PAD = 8;
 template <int LOGN> constexpr int col_region() { return lds_region<LOGN>() + COL_TEAM_PAD; }
 
-// Values per thread of a column transform: at most 512^2 leaves the chip short of
-// waves (512^2: 256 columns), and a pass takes one wave's serial chain; 8 values
-// per thread halve it.
-template <int LOGN> constexpr int col_values() { return fft_values<LOGN>(); }
+// Values per thread of a column transform: up to 512^2 the chip is short of waves (512^2:
+// 256 columns) and a pass takes one wave's serial chain; 8 values per thread halve it.
+// 1024^2 still gains (steps, 16 -> 8 values: mixed Allen-Cahn 602 -> 553 us, FP64
+// Cahn-Hilliard 3.40 -> 3.26 ms, mixed Schnakenberg 990 -> 972 us) except with two FP64
+// components (1557 -> 1595); 2048^2 and 4096^2 lose (mixed 1.25 -> 1.31, 6.0 -> 8.3 ms).
+template <typename T, int LOGN, int C> constexpr int col_values() {
+    return LOGN <= 9 || (LOGN == 10 && (C == 1 || sizeof(T) == 4)) ? 8 : 16;
+}
 
 template <typename T, int LOGN, int C> constexpr int col_jobs() {
     constexpr int N = 1 << LOGN;
-    constexpr int V = col_values<LOGN>();
+    constexpr int V = col_values<T, LOGN, C>();
     constexpr int R = rows_per_block<T, LOGN, C>();
     constexpr int tile_bytes = R * (int)sizeof(cplx<T>);
     constexpr int by_tile = tile_bytes >= 64 ? 1 : 64 / tile_bytes;
@@ -1031,7 +1035,7 @@ template <typename T, int LOGN, int C> constexpr int col_jobs() {
     return cb1 >= 16 ? 16 : cb1 >= 8 ? 8 : cb1 >= 4 ? 4 : cb1 >= 2 ? 2 : 1;
 }
 template <typename T, int LOGN, int C> constexpr int col_threads() {
-    return col_jobs<T, LOGN, C>() * ((1 << LOGN) / col_values<LOGN>());
+    return col_jobs<T, LOGN, C>() * ((1 << LOGN) / col_values<T, LOGN, C>());
 }
 // Register budget: two column workgroups must fit on one CU (four SIMDs), so that
 // the extra decision workgroup of a launch that fills every CU starts at once --
@@ -1055,7 +1059,7 @@ template <typename T, int LOGN, int C> constexpr int col_waves_per_eu() {
 // region size (64 bytes in FP32: 16 banks).  At N = 2048 the column pass takes
 // 21 instead of 26 us (FP64) and 17.1 instead of 18.2 us (FP32).
 template <typename T, int LOGN, int C> constexpr bool cols_in_regs() {
-    constexpr int V = col_values<LOGN>();
+    constexpr int V = col_values<T, LOGN, C>();
     constexpr int TPF = (1 << LOGN) / V;
     constexpr int R = rows_per_block<T, LOGN, C>();
     return npasses16<LOGN, V>() >= 2 && TPF >= R && TPF % R == 0;
@@ -1063,7 +1067,7 @@ template <typename T, int LOGN, int C> constexpr bool cols_in_regs() {
 
 template <typename T, int LOGN, int C, int CB>
 __device__ __forceinline__ void cols_regs(SlotRef s, int c, int kx0, const cplx<T> *S, cplx<T> *S2, cplx<T> *buf) {
-    constexpr int V = col_values<LOGN>();
+    constexpr int V = col_values<T, LOGN, C>();
     constexpr int N = 1 << LOGN, H = N / 2, TPF = N / V;
     constexpr int R = rows_per_block<T, LOGN, C>();
     // with 8 values there is room to keep the twiddles and to read the eigenvalues
@@ -1192,7 +1196,7 @@ __global__ __launch_bounds__((col_threads<T, LOGN, C>()), (col_waves_per_eu<T, L
         }
     }
     const cplx<T> *twd = (const cplx<T> *)s.twd;
-    constexpr int V = col_values<LOGN>();
+    constexpr int V = col_values<T, LOGN, C>();
     if constexpr (V == 8) {
         // everything else the pass reads is loaded beside the spectrum
         constexpr int IPT = pair_items_per_thread<LOGN, CB, NTH>();
