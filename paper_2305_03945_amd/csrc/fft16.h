@@ -1,11 +1,11 @@
-// Workgroup FFT with radix-16 passes, 16 values per thread.
+// Workgroup FFT, V = 8 or 16 values per thread.
 //
-// A length-N transform (N = 2^LOGN, 16 <= N <= 4096) is done by N/16 threads
-// (one wave or less for N <= 1024, several waves above), in an LDS region of
-// N complex values with padding (lds_pad), which keeps the stride-R writes of a
-// Stockham pass off a single bank group.  Passes are Stockham autosort passes of radix 16, then one pass
-// of radix 8, 4 or 2 for the remaining bits; each thread runs 16/R butterflies
-// of a radix-R pass.  A butterfly gathers the powers W^{k}, W^{2k}, W^{4k}, W^{8k}
+// A length-N transform (N = 2^LOGN, 16 <= N <= 4096) is done by N/V threads, in an
+// LDS region of N complex values with padding (lds_pad), which keeps the stride-R
+// writes of a Stockham pass off a single bank group.  Threads of one wave synchronise
+// within it, a transform over several waves by the workgroup's barrier.  Passes are
+// Stockham autosort passes of radix V, then one pass of a smaller radix for the
+// remaining bits; each thread runs V/R butterflies of a radix-R pass.  A butterfly gathers the powers W^{k}, W^{2k}, W^{4k}, W^{8k}
 // of its twiddle and applies them in its radix-2 steps (twiddled_dft).
 #pragma once
 #include "fft.h"

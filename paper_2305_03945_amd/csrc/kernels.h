@@ -5,9 +5,9 @@
 // active slot.  The row-parallel steps are one launch, k_rows (kernels_rows.h),
 // where its rows fit in LDS, and k_rowinv, k_upd and k_row_forward elsewhere (FP64
 // on 4096^2, wide stencils and two components on 2048^2 and 4096^2):
-//   k_cols       column pass of Y = G^-1 W_n: forward column FFT, multiply by
-//                1 / (N^2 g), inverse column FFT, in place on the spectrum S
-//                (the row pass before it left S = row transforms of W_n).
+//   k_cols       column pass of G^-1: forward column FFT, multiply by 1 / (N^2 g),
+//                inverse column FFT, from the spectrum S that the row pass before
+//                it left into S2 (k_rows) or in place on S (the separate kernels).
 //   k_rowinv     inverse row transform -> Y_n;  P_{n+1} = P_n + tau_p Y_n,
 //                P~ = P_{n+1} + omega (P_{n+1} - P_n)   (eqs. 21-22)
 //   k_upd        U_{n+1} = U_n - tau_u grad F(U_n)^T P~ (eq. 23 / 32 / Sec. 3.4.1),

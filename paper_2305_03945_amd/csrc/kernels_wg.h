@@ -1,8 +1,7 @@
 // Small grids: one workgroup runs a whole implicit step.
 //
-// On N <= 128 grids an iteration moves a few hundred KB, and the four launches of
-// the batched iteration (column pass, inverse rows, primal update, forward rows)
-// cost their launch latency, not their bytes.  Here one workgroup per slot takes
+// On N <= 64 grids an iteration moves a few hundred KB, and the launches of the
+// batched iteration (column pass, row pass) cost their latency, not their bytes.  Here one workgroup per slot takes
 // the whole step, Algorithm 1 with its stop test, in one launch:
 //
 //   W = F(U_n) (stencil);  Z = Q + (1 + omega) W -> spectrum S in LDS (row pairs

@@ -7,9 +7,11 @@
 and prints a per-kernel table.  Launches that found their slot finished return
 at once (the host enqueues iterations speculatively); the "working" columns
 keep only launches longer than half the kernel's median duration.  The mixed
-row pass (last template argument 5) makes either the FP32 inner iteration or,
-once an inner loop has stopped, the FP64 outer update: its launches above 1.6x
-the median (duration, or counter value) are listed apart as ``<kernel>:outer``.
+row pass (``k_rows<float,...>``, or a ``row_forward`` with last template argument 5)
+makes either the FP32 inner iteration or, once an inner loop has stopped, the FP64
+outer update: its launches above 1.6x the median (duration, or counter value) are
+listed apart as ``<kernel>:outer`` (at 2048^2 that splits the bytes written by
+``k_rows``; its outer updates take 1.3x the time and read as many bytes).
 
 ``counters`` reads the ``<prefix>_counter_collection.csv`` of one ``--pmc`` run
 and prints, per kernel, the average of every listed counter over the working
@@ -50,7 +52,7 @@ def _working(values):
     return [v for v in values if v >= 0.5 * med]
 
 
-MIXED_ROW = re.compile(r"row_forward<.*,5>$")
+MIXED_ROW = re.compile(r"row_forward<.*,5>$|k_rows<float,")
 
 
 def _split_outer(by):
