@@ -1,4 +1,4 @@
-// Workgroup FFT, V = 8 or 16 values per thread.
+// Workgroup FFT, V = 4, 8 or 16 values per thread.
 //
 // A length-N transform (N = 2^LOGN, 16 <= N <= 4096) is done by N/V threads, in an
 // LDS region of N complex values with padding (lds_pad), which keeps the stride-R
@@ -136,8 +136,8 @@ template <typename T, int R, int DIR> __device__ __forceinline__ void dftR(cplx<
     for (int q = 0; q < R; ++q) v[q] = out[q];
 }
 
-// Values per thread of a transform, V: 16 where the chip is full of transforms, 8
-// where it is not (short serial chains; see row_values).  Radix of pass q of a
+// Values per thread of a transform, V: 16 where the chip is full of transforms, 8 or 4
+// where it is not (short serial chains; see RowsPlan and col_values).  Radix of pass q of a
 // length-2^LOGN transform: radix V while that many bits remain, then one pass of
 // what is left.
 template <int V> constexpr int logv() { return V == 16 ? 4 : V == 8 ? 3 : 2; }

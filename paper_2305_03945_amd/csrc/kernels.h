@@ -357,8 +357,11 @@ template <typename T, int LOGN, int EQ> struct RowsPlan {
     static constexpr int NRF = C * R / 2;        // forward transforms
     // values per thread of a transform: 8 while 512 threads then run every inverse
     // transform at once (1024^2 mixed Allen-Cahn step 647 -> 605 us), 16 above
-    // (2048^2 mixed: 1.39 against 1.43 ms with 8)
-    static constexpr int V = NRI * N / 8 <= 512 ? 8 : 16;
+    // (2048^2 mixed: 1.39 against 1.43 ms with 8); in FP64 4 up to 256^2, where the
+    // workgroup has threads to spare (256^2 Allen-Cahn 527 -> 512 us, Cahn-Hilliard
+    // 1190 -> 1155, FCH 3143 -> 3020, 128^2 458 -> 445; FP32 gains nothing there, and
+    // 512^2 loses: 685 -> 726)
+    static constexpr int V = sizeof(T) == 8 && LOGN <= 8 ? 4 : NRI * N / 8 <= 512 ? 8 : 16;
     static constexpr int TPF = N / V;
     static constexpr int NTH = NRI * TPF <= 256 ? 256 : 512;
     static constexpr size_t lds = (size_t)NRI * lds_region<LOGN>() * sizeof(cplx<T>);

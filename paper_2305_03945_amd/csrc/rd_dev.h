@@ -172,9 +172,12 @@ template <typename T, int LOGN, int C> constexpr int rows_per_block3() {
 // faster on every grid measured (steps, ms: 128^2 FCH 7.9 -> 6.6, 256^2
 // Allen-Cahn 0.84 -> 0.63, 256^2 Neumann Cahn-Hilliard 1.04 -> 0.69, 512^2
 // 1.07 -> 0.82, 1024^2 1.39 -> 1.25; N/32, N/64 and N/128 rows measured in
-// between).  2048^2 and 4096^2 keep 4 rows.  The 3-D row passes keep theirs:
-// there the stop decision reduces one partial sum per workgroup of N^2 / R,
-// and more of them slowed the y pass that takes it.
+// between).  The one-launch row pass, whose halo rows favour tall tiles, keeps the
+// rule (steps, us, half the rows / these / twice: 1024^2 Allen-Cahn FP64 1097 / 937 /
+// 1060, mixed 631 / 550 / 618; 512^2 Neumann Cahn-Hilliard - / 1532 / 1600, 256^2
+// Allen-Cahn - / 528 / 565).  2048^2 and 4096^2 keep 4 rows.  The 3-D row passes
+// keep theirs: there the stop decision reduces one partial sum per workgroup of
+// N^2 / R, and more of them slowed the y pass that takes it.
 template <typename T, int LOGN, int C> constexpr int rows_per_block() {
     constexpr int N = 1 << LOGN;
     constexpr int r3 = rows_per_block3<T, LOGN, C>();

@@ -14,6 +14,7 @@ torch = pytest.importorskip("torch")
 # 14 rows of P~ nearly cover the grid there), the others above 64^2
 CASES = [
     ("fch", 16, 1e-3, 1e-6, 0.58, 0.5, 1.0),
+    ("fch", 32, 1e-3, 1e-6, 0.58, 0.58, 1.0),
     ("fch", 64, 1e-3, 5e-6, 0.5, 0.58, 0.9),
     ("allen_cahn", 128, 1e-3, 1e-8, 0.9, 0.7, 0.8),
     ("allen_cahn", 1024, 1e-3, 1e-6, 0.9, 0.9, 1.0),
