@@ -600,10 +600,16 @@ __device__ __forceinline__ void lines_apply_symbol3(cplx<T> *buf, int c, int q, 
 // bare transforms and the z pass multiplies by the symbol at (kx, ky, kz) =
 // (j, q, l).  Their transforms start from and end in registers (fft16_regs):
 // thread t of team g holds elements t + r N/V of the line of slot j0 + g, and
-// CB consecutive lanes take the CB adjacent slots (one 128-byte run).  FP64 only,
-// as for the 2-D column pass (measured: no gain for FP32).
+// CB consecutive lanes take the CB adjacent slots (one 128-byte run).  Those lanes hit
+// the teams' regions at equal offsets: without LINE_PAD more the regions' stride (136
+// values at 128^3, 272 at 256^3) puts every second or fourth team on the same banks.
+// Steps, ms, padded against not: 128^3 FP64 2.14 -> 2.01; with FP32 in registers too
+// (slower than through LDS unpadded, 1.07): 128^3 mixed 1.024 -> 0.988, 256^3 mixed
+// 6.57 -> 6.25, FP64 14.54 -> 14.20.  2, 4 and 10 values measured the same or less.
+constexpr int LINE_PAD = 9;
+template <int LOGN> constexpr int line_region() { return lds_region<LOGN>() + LINE_PAD; }
 template <typename T, int LOGN> constexpr bool lines_in_regs() {
-    return sizeof(T) == 8 && npasses16<LOGN, V3<LOGN>()>() >= 2 &&
+    return npasses16<LOGN, V3<LOGN>()>() >= 2 &&
            line_threads<T, LOGN>() == line_cb<T, LOGN>() * ((1 << LOGN) / V3<LOGN>());
 }
 
@@ -615,7 +621,7 @@ __device__ __forceinline__ void lines_regs(SlotRef s, int c, int w, int j0, cplx
     typedef T v2_t __attribute__((ext_vector_type(2)));
     const int team = threadIdx.x % CB, t = threadIdx.x / CB;
     const int j = j0 + team;
-    cplx<T> *x = buf + team * lds_region<LOGN>();
+    cplx<T> *x = buf + team * line_region<LOGN>();
     // element p of the line: y lines of plane (c, w), or z lines of row w
     auto off = [&](int p) -> int {
         return PASS == L3_ZSYM ? (int)s3_off<LOGN>(c, p, w, j) : (int)s3_off<LOGN>(c, w, p, j);
@@ -666,7 +672,7 @@ __global__ __launch_bounds__((line_threads<T, LOGN>())) void k3_lines(Slot *cons
     constexpr int CB = line_cb<T, LOGN>();
     constexpr int NTH = line_threads<T, LOGN>();
     static_assert(FIN == FIN_NONE || HEAD, "only the first pass of an iteration takes a decision");
-    __shared__ cplx<T> buf[CB * lds_region<LOGN>()];
+    __shared__ cplx<T> buf[CB * line_region<LOGN>()];
     __shared__ double lanes[FIN == FIN_NONE ? 1 : 64 * 2 * C];
     SlotRef s = slot_of(slots);
     StateRef sst = state_of(s);
@@ -742,9 +748,10 @@ __global__ __launch_bounds__((line_threads<T, LOGN>())) void k3_lines(Slot *cons
 //
 // There are N workgroups per component, so this trades bandwidth (128^3: half the CUs)
 // for launches and serial latency.  Steps, us, six launches -> plane passes, mixed: 64^3
-// 578 -> 513, 32^3 459 -> 334, 16^3 306 -> 228; FP64 64^3 671 -> 602.  128^3, mixed: 1077
-// with neither, 1031 with the inverse pass, 1125 with both (its FP64 outer updates take 52
-// instead of 20 us on 128 workgroups); FP64 2152 with neither, 2159 with the inverse one.
+// 578 -> 513, 32^3 459 -> 334, 16^3 306 -> 228; FP64 64^3 671 -> 602.  128^3, mixed: 1012
+// with neither, 985 with the inverse pass; with both, before LINE_PAD, 1125 against 1031
+// (its FP64 outer updates take 52 instead of 20 us on 128 workgroups); FP64 then 2152 with
+// neither, 2159 with the inverse one.
 template <typename T, int LOGN> constexpr int plane_threads() {
     constexpr int t = (1 << LOGN) / 2 * ((1 << LOGN) / 8);
     return t < 256 ? 256 : t;
