@@ -601,13 +601,14 @@ __device__ __forceinline__ void lines_apply_symbol3(cplx<T> *buf, int c, int q, 
 // (j, q, l).  Their transforms start from and end in registers (fft16_regs):
 // thread t of team g holds elements t + r N/V of the line of slot j0 + g, and
 // CB consecutive lanes take the CB adjacent slots (one 128-byte run).  Those lanes hit
-// the teams' regions at equal offsets: without LINE_PAD more the regions' stride (136
-// values at 128^3, 272 at 256^3) puts every second or fourth team on the same banks.
-// Steps, ms, padded against not: 128^3 FP64 2.14 -> 2.01; with FP32 in registers too
-// (slower than through LDS unpadded, 1.07): 128^3 mixed 1.024 -> 0.988, 256^3 mixed
-// 6.57 -> 6.25, FP64 14.54 -> 14.20.  2, 4 and 10 values measured the same or less.
+// the teams' regions at equal offsets, and a stride of the padded transform alone (136
+// values at 128^3, 272 at 256^3) puts every second or fourth team on the same banks:
+// LINE_PAD more spreads them.  Steps, ms, padded against not: 128^3 FP64 2.14 -> 2.01;
+// with FP32 in registers too (slower than through LDS unpadded, 1.07): 128^3 mixed
+// 1.024 -> 0.988, 256^3 mixed 6.57 -> 6.25, FP64 14.54 -> 14.20.  2, 4 and 10 values
+// measured the same or less.
 constexpr int LINE_PAD = 9;
-template <int LOGN> constexpr int line_region() { return lds_region<LOGN>() + LINE_PAD; }
+template <int LOGN> constexpr int line_region() { return lds_pad<LOGN>(1 << LOGN) + LINE_PAD; }
 template <typename T, int LOGN> constexpr bool lines_in_regs() {
     return npasses16<LOGN, V3<LOGN>()>() >= 2 &&
            line_threads<T, LOGN>() == line_cb<T, LOGN>() * ((1 << LOGN) / V3<LOGN>());
