@@ -12,168 +12,239 @@
 
 namespace rdk {
 
-// ---- twiddled DFT of one butterfly, in multiply-adds
+// ---- twiddled DFT of one butterfly
 //
-// V_q = sum_r v_r w^r W_R^{qr}, W_R = exp(DIR 2 pi i / R), by radix-2 steps on the
-// even and odd inputs: with E, O the DFTs (of R/2 points, for w^2) of the two halves
-// and t = w W_R^q,
-//     V_q = E_q + t O_q,   V_{q+R/2} = 2 E_q - V_q:
-// six multiply-adds for a complex butterfly and its twiddle together.  Only w, w^2,
-// w^4, ... are needed (one per step); t for q >= R/4 is t for q - R/4 turned by 90
-// degrees.  A radix-16 butterfly takes 208 operations, against 272 when its 15
-// twiddles are formed and applied first.
+// V_q = sum_r v_r w^r W_R^{qr}, W_R = exp(DIR 2 pi i / R), by decimation in time: radix-2
+// steps on the DFTs E, O (of R/2 points, for w^2) of the even and odd inputs,
+//     V_q = E_q + t O_q,   V_{q+R/2} = E_q - t O_q,   t = w W_R^q,
+// in eight multiply-adds, so that only w, w^2, w^4, ... are needed; t for q >= R/4 is t
+// for q - R/4 turned by 90 degrees.  A radix-16 butterfly takes 256 operations, against 272
+// when its 15 twiddles are formed and applied first.
+//
+// The rounding error is to be no larger than with twiddles formed and applied first.  G^-1
+// at 512^2 against 80-bit transforms: 4.3e-16 (FP64) and 2.5e-7 (FP32), 4.5e-16 and 2.7e-7
+// that way, 5.2e-16 and 2.8e-7 with the cheaper butterfly of the next lines, against which
+// this one costs 2 % of a step (2048^2 1240 -> 1268 us mixed, 2640 -> 2702 FP64).  Of a
+// 512-point FP64 transform and its inverse, in units of the rounding (FP32): 2.57 (2.80)
+// that way; 2.45 (2.56) this with 8 values per thread, 2.45 (2.70) with 16.  What was
+// found to cost accuracy:
+//  - V_{q+R/2} as 2 E_q - V_q, which saves two operations but takes over V_q's rounding
+//    (one transform: 2.01 against 1.80 formed first);
+//  - w W_8 as a product, which puts the error of the rounded sqrt(1/2) into every value
+//    with the same sign (2.60, 16 values).  It is gathered (tw_has_w8) but for FP32
+//    transforms of 2048 points by 16 values, whose kernels have no register left (3.13,
+//    formed first 3.19);
+//  - radix-2 steps down to two points on short transforms, whose error is small (32
+//    points, 8 values: 1.69, formed first 1.65).  Up to 64 points the DFTs of four multiply
+//    their twiddles in first (1.61); above, the third twiddle would cost registers.
 template <typename T> __device__ __forceinline__ T fma_(T a, T b, T c) { return __builtin_elementwise_fma(a, b, c); }
 
-// cos and sin of 2 pi m / R for R = 16 (m = 1..3) and R = 8 (m = 1)
-template <typename T, int R, int M> __device__ __forceinline__ cplx<T> root_of_one() {
-    static_assert((R == 16 && M >= 1 && M <= 3) || (R == 8 && M == 1), "first-octant roots");
-    constexpr int m = M * 16 / R;
-    if constexpr (m == 1) return {(T)0.923879532511286756128183189396788934, (T)0.382683432365089771728459984030398867};
-    else if constexpr (m == 2) return {(T)0.707106781186547524400844362104849039, (T)0.707106781186547524400844362104849039};
-    else return {(T)0.382683432365089771728459984030398867, (T)0.923879532511286756128183189396788934};
+// exp(DIR 2 pi i m / 16), m = 1, 2, 3
+template <typename T, int DIR, int M> __device__ __forceinline__ cplx<T> root16() {
+    static_assert(M >= 1 && M <= 3, "first-quadrant roots");
+    constexpr T c[4] = {(T)1, (T)0.923879532511286756128183189396788934, (T)0.707106781186547524400844362104849039,
+                        (T)0.382683432365089771728459984030398867};
+    return {c[M], (T)DIR * c[4 - M]};
 }
 
-// the butterfly: lo = a + t b, hi = a - t b.  QUARTER: t is to be turned by DIR 90
-// degrees.  ONE: t = 1.
-template <typename T, int DIR, bool ONE, bool QUARTER>
+// a + t b and a - t b.  QUARTER: t is to be turned by DIR 90 degrees.
+template <typename T, int DIR, bool QUARTER>
 __device__ __forceinline__ void bfly(cplx<T> a, cplx<T> b, cplx<T> t, cplx<T> &lo, cplx<T> &hi) {
-    if constexpr (ONE) {
-        const cplx<T> c = QUARTER ? rot90<T, DIR>(b) : b;
-        lo = cadd(a, c);
-        hi = csub(a, c);
-    } else {
-        if constexpr (QUARTER) b = rot90<T, DIR>(b);
-        lo.re = fma_(-t.im, b.im, fma_(t.re, b.re, a.re));
-        lo.im = fma_(t.im, b.re, fma_(t.re, b.im, a.im));
-        hi.re = fma_((T)2, a.re, -lo.re);
-        hi.im = fma_((T)2, a.im, -lo.im);
+    if constexpr (QUARTER) b = rot90<T, DIR>(b);
+    lo.re = fma_(-t.im, b.im, fma_(t.re, b.re, a.re));
+    lo.im = fma_(t.im, b.re, fma_(t.re, b.im, a.im));
+    hi.re = fma_(t.im, b.im, fma_(-t.re, b.re, a.re));
+    hi.im = fma_(-t.im, b.re, fma_(-t.re, b.im, a.im));
+}
+
+// The radix-2 step of R points; t: the R / 4 twiddles.
+template <typename T, int R, int DIR>
+__device__ __forceinline__ void radix2_step(const cplx<T> *e, const cplx<T> *o, const cplx<T> *t, cplx<T> *out) {
+    constexpr int QT = R / 4;
+#pragma unroll
+    for (int q = 0; q < QT; ++q) {
+        bfly<T, DIR, false>(e[q], o[q], t[q], out[q], out[q + R / 2]);
+        bfly<T, DIR, true>(e[q + QT], o[q + QT], t[q], out[q + QT], out[q + QT + R / 2]);
     }
 }
 
-// t_q = w W_R^q for 0 <= q < max(1, R/4)
-template <typename T, int R, int DIR, bool TW, int Q = 0> __device__ __forceinline__ void step_twiddles(cplx<T> w, cplx<T> *t) {
-    if constexpr (Q < (R >= 8 ? R / 4 : 1)) {
-        if constexpr (Q == 0) {
-            t[0] = w;
-        } else {
-            cplx<T> c = root_of_one<T, R, Q>();
-            c.im *= (T)DIR;
-            t[Q] = TW ? cmul(w, c) : c;
-        }
-        step_twiddles<T, R, DIR, TW, Q + 1>(w, t);
+template <typename T> __device__ __forceinline__ void dft2(cplx<T> *v) {
+    const cplx<T> a = v[0], b = v[1];
+    v[0] = cadd(a, b);
+    v[1] = csub(a, b);
+}
+
+template <typename T, int DIR> __device__ __forceinline__ void dft4(cplx<T> *v) {
+    const cplx<T> e0 = cadd(v[0], v[2]), e1 = csub(v[0], v[2]);
+    const cplx<T> o0 = cadd(v[1], v[3]), o1 = rot90<T, DIR>(csub(v[1], v[3]));
+    v[0] = cadd(e0, o0);
+    v[1] = cadd(e1, o1);
+    v[2] = csub(e0, o0);
+    v[3] = csub(e1, o1);
+}
+
+// Two DFTs of four, and the radix-2 step with W_8 = sqrt(1/2) (1 + DIR i).
+template <typename T, int DIR> __device__ __forceinline__ void dft8(cplx<T> *v) {
+    cplx<T> e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]};
+    dft4<T, DIR>(e);
+    dft4<T, DIR>(o);
+    o[2] = rot90<T, DIR>(o[2]);
+    o[3] = rot90<T, DIR>(o[3]);
+    const T s = root16<T, DIR, 2>().re;
+#pragma unroll
+    for (int q = 0; q < 4; q += 2) {
+        v[q] = cadd(e[q], o[q]);
+        v[q + 4] = csub(e[q], o[q]);
+    }
+#pragma unroll
+    for (int q = 1; q < 4; q += 2) {
+        const cplx<T> r = rot90<T, DIR>(o[q]), c = cadd(o[q], r);
+        v[q] = {fma_(s, c.re, e[q].re), fma_(s, c.im, e[q].im)};
+        v[q + 4] = {fma_(-s, c.re, e[q].re), fma_(-s, c.im, e[q].im)};
     }
 }
 
-// The twiddles of every step of a radix-R butterfly: steps of 16, 8, 4, 2 points.
-template <typename T, int R, int DIR, bool TW> struct StepTw {
-    cplx<T> t[R >= 8 ? R / 4 : 1];
-    StepTw<T, R / 2, DIR, TW> next;
-    __device__ __forceinline__ void set(const cplx<T> *p) {
-        step_twiddles<T, R, DIR, TW>(TW ? p[0] : cplx<T>{(T)1, (T)0}, t);
-        next.set(p + 1);
+// DFTs of four over inputs four apart, W_16^{s q}, DFTs of four over s.
+template <typename T, int DIR> __device__ __forceinline__ void dft16(cplx<T> *v) {
+    cplx<T> a[4][4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) a[s][r] = v[s + 4 * r];
+        dft4<T, DIR>(a[s]);
     }
-};
-template <typename T, int DIR, bool TW> struct StepTw<T, 1, DIR, TW> {
-    __device__ __forceinline__ void set(const cplx<T> *) {}
-};
-
-// in: R inputs at stride S; out: R outputs in natural order.
-template <typename T, int R, int DIR, bool TW, int S>
-__device__ __forceinline__ void dit(const cplx<T> *in, cplx<T> *out, const StepTw<T, R, DIR, TW> &w) {
-    if constexpr (R == 1) {
-        out[0] = in[0];
-    } else {
-        cplx<T> e[R / 2], o[R / 2];
-        dit<T, R / 2, DIR, TW, 2 * S>(in, e, w.next);
-        dit<T, R / 2, DIR, TW, 2 * S>(in + S, o, w.next);
-        constexpr int QT = R >= 4 ? R / 4 : 1;   // q >= QT: turned by 90 degrees
+    a[1][1] = cmul(a[1][1], root16<T, DIR, 1>());
+    a[1][2] = cmul(a[1][2], root16<T, DIR, 2>());
+    a[1][3] = cmul(a[1][3], root16<T, DIR, 3>());
+    a[2][1] = cmul(a[2][1], root16<T, DIR, 2>());
+    a[2][2] = rot90<T, DIR>(a[2][2]);
+    a[2][3] = rot90<T, DIR>(cmul(a[2][3], root16<T, DIR, 2>()));
+    a[3][1] = cmul(a[3][1], root16<T, DIR, 3>());
+    a[3][2] = rot90<T, DIR>(cmul(a[3][2], root16<T, DIR, 2>()));
+    a[3][3] = cmul(a[3][3], root16<T, DIR, 1>());   // W_16^9 = -W_16
+    a[3][3] = {-a[3][3].re, -a[3][3].im};
 #pragma unroll
-        for (int q = 0; q < QT; ++q) {
-            if constexpr (!TW) {
-                if (q == 0) bfly<T, DIR, true, false>(e[0], o[0], w.t[0], out[0], out[R / 2]);
-                else bfly<T, DIR, false, false>(e[q], o[q], w.t[q], out[q], out[q + R / 2]);
-            } else {
-                bfly<T, DIR, false, false>(e[q], o[q], w.t[q], out[q], out[q + R / 2]);
-            }
-        }
-        if constexpr (R >= 4) {
+    for (int q = 0; q < 4; ++q) {
+        cplx<T> b[4] = {a[0][q], a[1][q], a[2][q], a[3][q]};
+        dft4<T, DIR>(b);
 #pragma unroll
-            for (int q = 0; q < QT; ++q) {
-                if constexpr (!TW) {
-                    if (q == 0) bfly<T, DIR, true, true>(e[QT], o[QT], w.t[0], out[QT], out[QT + R / 2]);
-                    else bfly<T, DIR, false, true>(e[q + QT], o[q + QT], w.t[q], out[q + QT], out[q + QT + R / 2]);
-                } else {
-                    bfly<T, DIR, false, true>(e[q + QT], o[q + QT], w.t[q], out[q + QT], out[q + QT + R / 2]);
-                }
-            }
-        }
+        for (int r = 0; r < 4; ++r) v[q + 4 * r] = b[r];
     }
-}
-
-// DFT_R of v in place, input r multiplied by w^r first; p: w, w^2, w^4, ... (forward
-// sign, conjugated here for the inverse).
-template <typename T, int R, int DIR> __device__ __forceinline__ void twiddled_dft(cplx<T> *v, const cplx<T> *p) {
-    cplx<T> pd[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-        if ((1 << e) < R) pd[e] = DIR > 0 ? cconj(p[e]) : p[e];
-    // step sizes R, R/2, ..., 2 take w, w^2, ...
-    StepTw<T, R, DIR, true> w;
-    w.set(pd);
-    cplx<T> out[R];
-    dit<T, R, DIR, true, 1>(v, out, w);
-#pragma unroll
-    for (int q = 0; q < R; ++q) v[q] = out[q];
 }
 
 // DFT_R of v in place.
 template <typename T, int R, int DIR> __device__ __forceinline__ void dftR(cplx<T> *v) {
-    StepTw<T, R, DIR, false> w;
-    w.set(nullptr);
-    cplx<T> out[R];
-    dit<T, R, DIR, false, 1>(v, out, w);
+    if constexpr (R == 16) dft16<T, DIR>(v);
+    else if constexpr (R == 8) dft8<T, DIR>(v);
+    else if constexpr (R == 4) dft4<T, DIR>(v);
+    else dft2<T>(v);
+}
+
+// Twiddles kept per butterfly of an N-point transform by V values per thread: the powers
+// w, w^2, w^4, ..., then (tw_has_w3) w^{3R/4}, the last input's in a DFT of four, then
+// (tw_has_w8) the 8-point step's power times W_8.
+template <int V> constexpr int logv() { return V == 16 ? 4 : V == 8 ? 3 : 2; }
+template <int LOGN> constexpr bool twiddles_first() { return LOGN <= 6; }
+template <int LOGN, int V> constexpr bool tw_has_w3() { return twiddles_first<LOGN>() && V <= 8; }
+template <typename T, int LOGN, int V> constexpr bool tw_has_w8() {
+    return V == 8 || (V == 16 && !(sizeof(T) == 4 && LOGN == 11));
+}
+template <typename T, int LOGN, int V> constexpr int tw_count() {
+    return logv<V>() + (tw_has_w3<LOGN, V>() ? 1 : 0) + (tw_has_w8<T, LOGN, V>() ? 1 : 0);
+}
+
+// Gather a radix-R butterfly's twiddles: w = W_N^i, table tw of W_N (forward sign).
+template <typename T, int LOGN, int V, int R, class TAB>
+__device__ __forceinline__ void gather_twiddles(cplx<T> *p, TAB tw, int i) {
+    constexpr int N = 1 << LOGN;
+    auto at = [&](int m) { return cplx<T>{tw[m & (N - 1)].re, tw[m & (N - 1)].im}; };
 #pragma unroll
-    for (int q = 0; q < R; ++q) v[q] = out[q];
+    for (int e = 0; e < logv<V>(); ++e)
+        if ((1 << e) < R) p[e] = at(i << e);
+    if constexpr (tw_has_w3<LOGN, V>() && R >= 4) p[logv<V>()] = at(i * (3 * R / 4));
+    if constexpr (tw_has_w8<T, LOGN, V>() && R >= 8) p[tw_count<T, LOGN, V>() - 1] = at(i * (R / 8) + N / 8);
+}
+
+// DFT_R of v in place, input r multiplied by w^r first; p: gather_twiddles (forward sign,
+// conjugated here for the inverse).
+template <typename T, int LOGN, int V, int R, int DIR>
+__device__ __forceinline__ void twiddled_dft(cplx<T> *v, const cplx<T> *p) {
+    auto tw = [&](int e) { return DIR > 0 ? cconj(p[e]) : p[e]; };
+    if constexpr (R == 2) {
+        bfly<T, DIR, false>(v[0], v[1], tw(0), v[0], v[1]);
+    } else {
+        constexpr int NL = R / 4;                                // DFTs of four
+        constexpr int E = R == 16 ? 2 : R == 8 ? 1 : 0;          // their twiddle is w^{R/4}
+        const cplx<T> l1 = tw(E), l2 = tw(E + 1);
+        cplx<T> a[NL][4];
+        if constexpr (twiddles_first<LOGN>()) {
+            cplx<T> l3;
+            if constexpr (tw_has_w3<LOGN, V>()) l3 = tw(logv<V>());
+            else l3 = cmul(l1, l2);
+#pragma unroll
+            for (int s = 0; s < NL; ++s) {
+                a[s][0] = v[s];
+                a[s][1] = cmul(v[s + NL], l1);
+                a[s][2] = cmul(v[s + 2 * NL], l2);
+                a[s][3] = cmul(v[s + 3 * NL], l3);
+                dft4<T, DIR>(a[s]);
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < NL; ++s) {
+                cplx<T> e[2], o[2];
+                bfly<T, DIR, false>(v[s], v[s + 2 * NL], l2, e[0], e[1]);
+                bfly<T, DIR, false>(v[s + NL], v[s + 3 * NL], l2, o[0], o[1]);
+                radix2_step<T, 4, DIR>(e, o, &l1, a[s]);
+            }
+        }
+        if constexpr (R == 4) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = a[0][q];
+        } else {
+            cplx<T> t8[2] = {tw(E - 1)};
+            if constexpr (tw_has_w8<T, LOGN, V>()) t8[1] = tw(tw_count<T, LOGN, V>() - 1);
+            else t8[1] = cmul(t8[0], root16<T, DIR, 2>());
+            if constexpr (R == 8) {
+                radix2_step<T, 8, DIR>(a[0], a[1], t8, v);
+            } else {
+                cplx<T> e[8], o[8];
+                radix2_step<T, 8, DIR>(a[0], a[2], t8, e);
+                radix2_step<T, 8, DIR>(a[1], a[3], t8, o);
+                const cplx<T> w = tw(0);
+                const cplx<T> t16[4] = {w, cmul(w, root16<T, DIR, 1>()), cmul(w, root16<T, DIR, 2>()),
+                                        cmul(w, root16<T, DIR, 3>())};
+                radix2_step<T, 16, DIR>(e, o, t16, v);
+            }
+        }
+    }
 }
 
 // Values per thread of a transform, V: 16 where the chip is full of transforms, 8 or 4
 // where it is not (short serial chains; see RowsPlan and col_values).  Radix of pass q of a
 // length-2^LOGN transform: radix V while that many bits remain, then one pass of
 // what is left.
-template <int V> constexpr int logv() { return V == 16 ? 4 : V == 8 ? 3 : 2; }
 template <int LOGN, int V = 16> constexpr int npasses16() { return (LOGN + logv<V>() - 1) / logv<V>(); }
 template <int LOGN, int V = 16> constexpr int pass_radix(int q) {
     return LOGN - logv<V>() * q >= logv<V>() ? V : (1 << (LOGN - logv<V>() * q));
 }
 
-// The twiddles of one thread for every pass after the first: for butterfly b of
-// pass q, the gathered powers W^{k}, W^{2k}, W^{4k}, W^{8k} (forward sign) of
-// W = exp(-2 pi i / (NS R)), k = j mod NS.  They depend only on the thread's
+// The twiddles of one thread for every pass after the first: those of butterfly b of
+// pass q for w = exp(-2 pi i k / (NS R)), k = j mod NS.  They depend only on the thread's
 // index in its transform team, so a kernel loads them once, at its start, and
 // every transform (forward and inverse) of the kernel reuses them.
 template <typename T, int LOGN, int V = 16> struct Tw16 {
-    cplx<T> p[npasses16<LOGN, V>() > 1 ? npasses16<LOGN, V>() - 1 : 1][V / 2][logv<V>()];
+    cplx<T> p[npasses16<LOGN, V>() > 1 ? npasses16<LOGN, V>() - 1 : 1][V / 2][tw_count<T, LOGN, V>()];
 };
 
-template <typename T, int LOGN, int V>
+template <typename T, int LOGN, int V, int Q = 1>
 __device__ __forceinline__ void load_tw16(Tw16<T, LOGN, V> &w, const cplx<T> *__restrict__ tw, int t) {
-    constexpr int N = 1 << LOGN;
-    constexpr int TPF = N / V;
-    const auto tg = gp(tw);
+    if constexpr (Q < npasses16<LOGN, V>()) {
+        constexpr int R = pass_radix<LOGN, V>(Q), NS = 1 << (logv<V>() * Q), N = 1 << LOGN;
 #pragma unroll
-    for (int q = 1; q < npasses16<LOGN, V>(); ++q) {
-        const int R = pass_radix<LOGN, V>(q), NS = 1 << (logv<V>() * q);
-        const int TWSTEP = N / (NS * R);
-#pragma unroll
-        for (int b = 0; b < V / R; ++b) {
-            const int k = (t + b * TPF) & (NS - 1);
-#pragma unroll
-            for (int e = 0; e < logv<V>(); ++e)
-                if ((1 << e) < R) {
-                    const int i = ((k * TWSTEP) << e) & (N - 1);
-                    w.p[q - 1][b][e] = {tg[i].re, tg[i].im};
-                }
-        }
+        for (int b = 0; b < V / R; ++b)
+            gather_twiddles<T, LOGN, V, R>(w.p[Q - 1][b], gp(tw), ((t + b * (N / V)) & (NS - 1)) * (N / (NS * R)));
+        load_tw16<T, LOGN, V, Q + 1>(w, tw, t);
     }
 }
 
@@ -197,7 +268,7 @@ template <typename T, int LOGN> struct Region {
 
 // pass_in: the reads, twiddles and butterflies of the thread (outputs in v).
 template <typename T, int LOGN, int R, int NS, int DIR, int V = 16, class X>
-__device__ __forceinline__ void pass_in(X x, int t, const cplx<T> (*pw)[logv<V>()], cplx<T> (*v)[R]) {
+__device__ __forceinline__ void pass_in(X x, int t, const cplx<T> (*pw)[tw_count<T, LOGN, V>()], cplx<T> (*v)[R]) {
     constexpr int N = 1 << LOGN;
     constexpr int TPF = N / V;       // threads per transform
     constexpr int NB = N / R;        // butterflies
@@ -207,7 +278,7 @@ __device__ __forceinline__ void pass_in(X x, int t, const cplx<T> (*pw)[logv<V>(
         const int j = t + b * TPF;
 #pragma unroll
         for (int r = 0; r < R; ++r) v[b][r] = x(j + r * NB);
-        if constexpr (NS > 1) twiddled_dft<T, R, DIR>(v[b], pw[b]);
+        if constexpr (NS > 1) twiddled_dft<T, LOGN, V, R, DIR>(v[b], pw[b]);
         else dftR<T, R, DIR>(v[b]);
     }
 }
@@ -239,7 +310,7 @@ template <bool WAVE> __device__ __forceinline__ void pass_sync() {
 }
 
 template <typename T, int LOGN, int R, int NS, int DIR, int V = 16, bool WAVE = false, class X>
-__device__ __forceinline__ void pass16(X x, int t, bool active, const cplx<T> (*pw)[logv<V>()]) {
+__device__ __forceinline__ void pass16(X x, int t, bool active, const cplx<T> (*pw)[tw_count<T, LOGN, V>()]) {
     cplx<T> v[V / R][R];
     if (active) pass_in<T, LOGN, R, NS, DIR, V>(x, t, pw, v);
     pass_sync<WAVE>();

@@ -360,8 +360,8 @@ template <typename T, int LOGN, int EQ> struct RowsPlan {
     // (2048^2 mixed: 1.39 against 1.43 ms with 8); in FP64 4 up to 256^2, where the
     // workgroup has threads to spare (256^2 Allen-Cahn 527 -> 512 us, Cahn-Hilliard
     // 1190 -> 1155, FCH 3143 -> 3020, 128^2 458 -> 445; FP32 gains nothing there, and
-    // 512^2 loses: 685 -> 726)
-    static constexpr int V = sizeof(T) == 8 && LOGN <= 8 ? 4 : NRI * N / 8 <= 512 ? 8 : 16;
+    // 512^2 loses: 685 -> 726).  16 points: 4, for their rounding error (col_values)
+    static constexpr int V = LOGN == 4 || (sizeof(T) == 8 && LOGN <= 8) ? 4 : NRI * N / 8 <= 512 ? 8 : 16;
     static constexpr int TPF = N / V;
     static constexpr int NTH = NRI * TPF <= 256 ? 256 : 512;
     static constexpr size_t lds = (size_t)NRI * lds_region<LOGN>() * sizeof(cplx<T>);
@@ -1015,8 +1015,10 @@ template <int LOGN> constexpr int col_region() { return lds_region<LOGN>() + COL
 // 1024^2 still gains (steps, 16 -> 8 values: mixed Allen-Cahn 602 -> 553 us, FP64
 // Cahn-Hilliard 3.40 -> 3.26 ms, mixed Schnakenberg 990 -> 972 us) except with two FP64
 // components (1557 -> 1595); 2048^2 and 4096^2 lose (mixed 1.25 -> 1.31, 6.0 -> 8.3 ms).
+// 16 points: two radix-4 passes, whose rounding error is that of one radix-16 pass (of a
+// transform and its inverse, in units of the rounding, 1.42; 1.48 by radix 8 and 2).
 template <typename T, int LOGN, int C> constexpr int col_values() {
-    return LOGN <= 9 || (LOGN == 10 && (C == 1 || sizeof(T) == 4)) ? 8 : 16;
+    return LOGN == 4 ? 4 : LOGN <= 9 || (LOGN == 10 && (C == 1 || sizeof(T) == 4)) ? 8 : 16;
 }
 
 template <typename T, int LOGN, int C> constexpr int col_jobs() {
@@ -1073,9 +1075,9 @@ __device__ __forceinline__ void cols_regs(SlotRef s, int c, int kx0, const cplx<
     constexpr int V = col_values<T, LOGN, C>();
     constexpr int N = 1 << LOGN, H = N / 2, TPF = N / V;
     constexpr int R = rows_per_block<T, LOGN, C>();
-    // with 8 values there is room to keep the twiddles and to read the eigenvalues
+    // with up to 8 values there is room to keep the twiddles and to read the eigenvalues
     // ahead; with 16 they are read again where they are used
-    constexpr bool KEEP = V == 8;
+    constexpr bool KEEP = V <= 8;
     typedef T v2_t __attribute__((ext_vector_type(2)));
     const int idx = threadIdx.x;
     const int team = (idx / R) % CB;
@@ -1200,7 +1202,7 @@ __global__ __launch_bounds__((col_threads<T, LOGN, C>()), (col_waves_per_eu<T, L
     }
     const cplx<T> *twd = (const cplx<T> *)s.twd;
     constexpr int V = col_values<T, LOGN, C>();
-    if constexpr (V == 8) {
+    if constexpr (V <= 8) {
         // everything else the pass reads is loaded beside the spectrum
         constexpr int IPT = pair_items_per_thread<LOGN, CB, NTH>();
         Tw16<T, LOGN, V> twr;

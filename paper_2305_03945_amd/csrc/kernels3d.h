@@ -26,8 +26,10 @@ namespace rdk {
 // Values per thread of the 3-D transforms: the passes of at most 2 M points (128^3) hold
 // too few waves to hide their serial chains, which 8 values halve (128^3 mixed step
 // 1.25 -> 1.07 ms, 64^3 767 -> 580 us).
-// 256^3 fills the chip (FP64 step 14.4 ms; 15.0 with 8).
-template <int LOGN> constexpr int V3() { return LOGN <= 7 ? 8 : 16; }
+// 256^3 fills the chip (FP64 step 14.4 ms; 15.0 with 8).  16 points: two radix-4 passes,
+// whose rounding error is that of one radix-16 pass (of a transform and its inverse, in
+// units of the rounding, 1.42; 1.48 by radix 8 and 2).
+template <int LOGN> constexpr int V3() { return LOGN == 4 ? 4 : LOGN <= 7 ? 8 : 16; }
 
 // ---------------------------------------------------------------- 3-D stencil windows
 // Four consecutive points (z, y, x0 .. x0+3), x0 a multiple of 4, and their 7-point
@@ -754,7 +756,7 @@ __global__ __launch_bounds__((line_threads<T, LOGN>())) void k3_lines(Slot *cons
 // (its FP64 outer updates take 52 instead of 20 us on 128 workgroups); FP64 then 2152 with
 // neither, 2159 with the inverse one.
 template <typename T, int LOGN> constexpr int plane_threads() {
-    constexpr int t = (1 << LOGN) / 2 * ((1 << LOGN) / 8);
+    constexpr int t = (1 << LOGN) / 2 * ((1 << LOGN) / V3<LOGN>());
     return t < 256 ? 256 : t;
 }
 // Which sides of an iteration take plane passes (the forward one only with the inverse).
@@ -776,11 +778,11 @@ template <typename T, int LOGN, int BC, bool NATURAL> struct PlaneLine {
 // The y transforms of every slot of a plane; consecutive lanes take consecutive slots
 // (contiguous in LDS).  Ends with a barrier.
 template <typename T, int LOGN, int BC, int DIR, int NTH>
-__device__ __forceinline__ void plane_fft_y(cplx<T> *buf, const Tw16<T, LOGN, 8> &w) {
+__device__ __forceinline__ void plane_fft_y(cplx<T> *buf, const Tw16<T, LOGN, V3<LOGN>()> &w) {
     constexpr int N = 1 << LOGN, H = N / 2;
-    const bool active = threadIdx.x < H * (N / 8);
+    const bool active = threadIdx.x < H * (N / V3<LOGN>());
     const PlaneLine<T, LOGN, BC, false> x{buf, (int)threadIdx.x % H};
-    passes16<T, LOGN, DIR, 0, 8, false>(x, active ? threadIdx.x / H : 0, active, w);
+    passes16<T, LOGN, DIR, 0, V3<LOGN>(), false>(x, active ? threadIdx.x / H : 0, active, w);
 }
 
 // The two real sequences packed in a line (periodic: slot 0 only), as rows_post_forward
@@ -871,9 +873,9 @@ __device__ __forceinline__ void plane_forward_pass(SlotRef s, StateRef sst, cplx
     constexpr int NTH = plane_threads<T, LOGN>();
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
     const int z = tile / C, c = tile % C;
-    Tw16<T, LOGN, 8> twx, twy;
-    load_tw16<T, LOGN, 8>(twx, (const cplx<T> *)s.tw);
-    load_tw16<T, LOGN, 8>(twy, (const cplx<T> *)s.tw, (int)threadIdx.x / H % (N / 8));
+    Tw16<T, LOGN, V3<LOGN>()> twx, twy;
+    load_tw16<T, LOGN, V3<LOGN>()>(twx, (const cplx<T> *)s.tw);
+    load_tw16<T, LOGN, V3<LOGN>()>(twy, (const cplx<T> *)s.tw, (int)threadIdx.x / H % (N / V3<LOGN>()));
     double acc[2 * C];
 #pragma unroll
     for (int k = 0; k < 2 * C; ++k) acc[k] = 0.0;
@@ -935,9 +937,9 @@ __global__ __launch_bounds__((plane_threads<T, LOGN>())) void k3_plane_inverse(S
     if (skip_launch<K_ITER64>(sst)) return;
     const int z = blockIdx.x / C, c = blockIdx.x % C;
     const cplx<T> *S = (const cplx<T> *)s.S;
-    Tw16<T, LOGN, 8> twx, twy;
-    load_tw16<T, LOGN, 8>(twx, (const cplx<T> *)s.tw);
-    load_tw16<T, LOGN, 8>(twy, (const cplx<T> *)s.tw, (int)threadIdx.x / H % (N / 8));
+    Tw16<T, LOGN, V3<LOGN>()> twx, twy;
+    load_tw16<T, LOGN, V3<LOGN>()>(twx, (const cplx<T> *)s.tw);
+    load_tw16<T, LOGN, V3<LOGN>()>(twy, (const cplx<T> *)s.tw, (int)threadIdx.x / H % (N / V3<LOGN>()));
 #pragma unroll 8
     for (int idx = threadIdx.x; idx < N * H; idx += NTH) {
         const int j = idx % H, y = idx / H;

@@ -82,14 +82,17 @@ template <int LOGN, int BC> struct ColMap {
 // element j + r N/R of butterfly j, multiplies input r by W_{NS R}^{r k} (k = j mod
 // NS), applies DFT_R and writes output q to (j - k) R + k + q NS.  The twiddles of a
 // thread depend only on its index in its team, so they are read from the table
-// exp(-2 pi i m / N) once per step and kept in registers; the inverse conjugates.
+// exp(-2 pi i m / N) once per step and kept in registers; the inverse conjugates.  FP64
+// butterflies are those of fft16.h; FP32 ones multiply all R - 1 twiddles in first, whose
+// rounding error is the smaller there (64 points, in units of the rounding: 1.33; 1.41 by
+// radix-2 steps) and for whose registers the FP32 step has room.
 template <int LOGN> constexpr int r8_radix(int q) { return LOGN - 3 * q >= 3 ? 8 : (1 << (LOGN - 3 * q)); }
 template <int LOGN> constexpr int r8_passes() { return (LOGN + 2) / 3; }
 
 template <typename T, int LOGN> struct TwR8 {
     // pass 1 (the only pass with NS > 1 for N <= 64): butterflies b < 8 / R, powers
-    // w, w^2, w^4 of the twiddle
-    cplx<T> w[4][3];
+    // FP64: gather_twiddles; FP32: the twiddles of inputs 1 .. R - 1
+    cplx<T> w[4][sizeof(T) == 8 ? tw_count<T, LOGN, 8>() : 7];
 };
 
 template <typename T, int LOGN>
@@ -104,9 +107,12 @@ __device__ __forceinline__ void load_twr8(TwR8<T, LOGN> &tw, const cplx<T> *tabl
             const int j = t + b * TPT;
             const int k = j & (NS - 1);
             (void)NB;
+            if constexpr (sizeof(T) == 8) {
+                gather_twiddles<T, LOGN, 8, R>(tw.w[b], table, k * STEP);
+            } else {
 #pragma unroll
-            for (int e = 0; e < 3; ++e)
-                if ((1 << e) < R) tw.w[b][e] = table[((k * STEP) << e) & (N - 1)];
+                for (int r = 1; r < R; ++r) tw.w[b][r - 1] = table[(r * k * STEP) & (N - 1)];
+            }
         }
     }
 }
@@ -122,8 +128,16 @@ __device__ __forceinline__ void r8_pass(cplx<T> *buf, int reg, int t, bool activ
             const int j = t + b * TPT;
 #pragma unroll
             for (int r = 0; r < R; ++r) v[b][r] = buf[M::at(reg, j + r * NB)];
-            if constexpr (NS > 1) twiddled_dft<T, R, DIR>(v[b], tw.w[b]);
-            else dftR<T, R, DIR>(v[b]);
+            if constexpr (NS > 1 && sizeof(T) == 8) {
+                twiddled_dft<T, LOGN, 8, R, DIR>(v[b], tw.w[b]);
+            } else {
+                if constexpr (NS > 1) {
+#pragma unroll
+                    for (int r = 1; r < R; ++r)
+                        v[b][r] = cmul(v[b][r], DIR < 0 ? tw.w[b][r - 1] : cconj(tw.w[b][r - 1]));
+                }
+                dftR<T, R, DIR>(v[b]);
+            }
         }
     }
     pass_sync<true>();

@@ -1,0 +1,45 @@
+"""Rounding error of the preconditioner against 80-bit transforms.  The bounds are the
+errors on the same inputs of transforms whose twiddles are all formed and multiplied in
+first, then exact-sum DFTs: a cheaper butterfly must not be less accurate than that."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+sf = pytest.importorskip("scipy.fft")
+
+# dimension, grid, boundary -> bound in FP64 and in the mixed precision's FP32
+BOUNDS = {
+    (2, 512, "periodic"): (4.489e-16, 2.731e-07),
+    (2, 512, "neumann"): (4.816e-16, 2.894e-07),
+    (2, 1024, "periodic"): (4.709e-16, 2.825e-07),
+    (2, 1024, "neumann"): (4.996e-16, 2.999e-07),
+    (3, 128, "periodic"): (5.086e-16, 2.963e-07),
+    (3, 128, "neumann"): (5.691e-16, 3.155e-07),
+}
+
+
+@pytest.mark.parametrize("dim,N,bc", sorted(BOUNDS))
+def test_preconditioner_rounding_error(dim, N, bc):
+    from paper_2305_03945_amd import rd
+    if np.finfo(np.longdouble).nmant < 63:
+        pytest.skip("long double has no 80-bit format here")
+    ht, lam = 1e-3, 1e-4
+    k, pi = np.arange(N).astype(np.longdouble), np.longdouble("3.14159265358979323846264338327950288")
+    s = 4 * np.longdouble(N) ** 2 * np.sin(pi * k / (N if bc == "periodic" else 2 * N)) ** 2
+    mu = sum(s.reshape([N if i == a else 1 for i in range(dim)]) for a in range(dim))
+    g = (1 + np.longdouble(lam) * np.longdouble(ht) * mu) ** 2
+    ctx = rd.Context(0)
+    p = rd.make_problem("allen_cahn", N, bc=bc, diff=(lam,), dim=dim)
+    err, norm = {"fp64": 0.0, "mixed": 0.0}, 0.0
+    for rep in range(2):
+        w = np.random.default_rng(N + 1000 * rep).standard_normal((N,) * dim)
+        W = w.astype(np.longdouble)
+        ref = sf.ifftn(sf.fftn(W) / g).real if bc == "periodic" else sf.idctn(sf.dctn(W) / g)
+        norm += float(np.sum(ref ** 2))
+        for prec in err:
+            y = ctx.precond_solve(torch.tensor(w, device="cuda"), ht, p, precision=prec).cpu().numpy()
+            err[prec] += float(np.sum((y - ref) ** 2))
+    ctx.close()
+    for prec, bound in zip(("fp64", "mixed"), BOUNDS[dim, N, bc]):
+        assert (err[prec] / norm) ** 0.5 <= bound, (prec, (err[prec] / norm) ** 0.5, bound)
