@@ -169,24 +169,17 @@ __device__ __forceinline__ void rows_pre_inverse(cplx<T> *buf, const cplx<T> *__
     __syncthreads();
 }
 
-// Symbol multiplier invNd / g, g = (1 + alpha mu + beta mu^2 + gamma mu^3)^2 >= 1, invNd a
-// power of two.  The reciprocal is the hardware's estimate and two Newton steps, which
-// leave its last rounding; the full division's scaling and fix-up are for operands
-// that do not occur here.  g is bounded so that an overflowing one still gives 0.
+// Symbol multiplier invNd / g, g = (1 + alpha mu + beta mu^2 + gamma mu^3)^2, invNd a power
+// of two.  The reciprocal is the hardware's estimate (within 2^-22) and two Newton steps,
+// which leave its last rounding: the division's bits, without its scaling.  The fix-up
+// is the division's: an overflowing g gives 0, a vanishing one infinity.
 __device__ __forceinline__ double symbol_of(double mu, double alpha, double beta, double gamma, double invNd) {
     const double a = 1.0 + mu * (alpha + mu * (beta + gamma * mu));
-    double g = a * a;
-    g = g > 0x1p+1000 ? 0x1p+1000 : g;
+    const double g = a * a;
     double r = __builtin_amdgcn_rcp(g);
     r = __builtin_fma(__builtin_fma(-g, r, 1.0), r, r);
     r = __builtin_fma(__builtin_fma(-g, r, 1.0), r, r);
-    return invNd * r;
-}
-
-// mu = s_kx + s_ky.
-__device__ __forceinline__ double symbol_mult(const double *__restrict__ eig, int kx, int ky, double alpha,
-                                              double beta, double gamma, double invN2) {
-    return symbol_of(eig[kx] + eig[ky], alpha, beta, gamma, invN2);
+    return __builtin_amdgcn_div_fixup(invNd * r, g, invNd);
 }
 
 // What a pair item of the symbol pass reads besides its two bins: the eigenvalues

@@ -43,3 +43,20 @@ def test_preconditioner_rounding_error(dim, N, bc):
     ctx.close()
     for prec, bound in zip(("fp64", "mixed"), BOUNDS[dim, N, bc]):
         assert (err[prec] / norm) ** 0.5 <= bound, (prec, (err[prec] / norm) ** 0.5, bound)
+
+
+@pytest.mark.parametrize("dim,N,period", [(2, 16, 2), (2, 128, 2), (2, 128, 4), (2, 2048, 4), (3, 32, 2), (3, 32, 4)])
+def test_symbol_beyond_the_range(dim, N, period):
+    """One Fourier mode of huge amplitude: a symbol near the end of the range divides it as
+    any other, and one that overflows removes it."""
+    from paper_2305_03945_amd import rd
+    line = torch.tensor({2: [1.0, -1.0], 4: [1.0, 0.0, -1.0, 0.0]}[period], dtype=torch.float64).repeat(N // period)
+    w = (line * 1e290).expand((N,) * dim).contiguous().cuda()
+    mu = 4.0 * N * N * np.sin(np.pi / period) ** 2
+    ctx = rd.Context(0)
+    y = ctx.precond_solve(w, 1.0, rd.make_problem("allen_cahn", N, diff=(1e151 / mu,), dim=dim))
+    ref = w / 1e302
+    assert float((y - ref).abs().max()) <= 1e-13 * float(ref.abs().max())
+    y = ctx.precond_solve(w, 1.0, rd.make_problem("allen_cahn", N, diff=(1e160,), dim=dim))
+    assert float(y.abs().max()) == 0.0
+    ctx.close()
