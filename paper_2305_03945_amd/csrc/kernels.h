@@ -2,9 +2,11 @@
 // residual passes of the mixed-precision step.
 //
 // One iteration n -> n+1 is the column pass and the row-parallel steps, over every
-// active slot.  The row-parallel steps are one launch, k_rows (kernels_rows.h),
-// where its rows fit in LDS, and k_rowinv, k_upd and k_row_forward elsewhere (FP64
-// on 4096^2, wide stencils and two components on 2048^2 and 4096^2):
+// active slot.  The row-parallel steps are one launch, k_rows (kernels_rows.h), where
+// that is faster (rows_fused), and k_rowinv, k_upd and k_row_forward elsewhere: FP64 on
+// 4096^2; two components from 2048^2; the 13-point stencil on 2048^2 in FP64 and on
+// 4096^2; the sixth-order equation from 1024^2 in FP64 and from 2048^2 in FP32.
+//
 //   k_cols       column pass of G^-1: forward column FFT, multiply by 1 / (N^2 g),
 //                inverse column FFT, from the spectrum S that the row pass before
 //                it left into S2 (k_rows) or in place on S (the separate kernels).
@@ -374,10 +376,21 @@ template <typename T, int LOGN, int EQ> struct RowsPlan {
     static constexpr int QW = R / 2 * N / 4 >= NTH ? 4 : R / 2 * N / 2 >= NTH ? 2 : 1;
 };
 
-// Whether the fused row pass serves (T, N, equation): its LDS fits.
+// Whether the fused row pass serves (T, N, equation): its rows fit in LDS, and it is the
+// faster way.  60 iterations, us, separate kernels / one launch, periodic (Neumann):
+//   2048^2 FP32  Allen-Cahn 3552 / 2926 (4077 / 3497), Cahn-Hilliard 4283 / 3950
+//                (4954 / 4675), Schnakenberg 6112 / 7131 (7031 / 8170): with two components
+//                only two rows fit, for which it transforms six back
+//   1024^2 FCH   FP64 2745 / 2916 (3059 / 3068): sixteen rows back for four, one
+//                workgroup per CU; FP32 2562 / 1971 (2786 / 2194)
+//   2048^2 FCH   FP32 6901 / 9483 (7441 / 6790)
+//   4096^2 FP32  Allen-Cahn 13836 / 13306 (15345 / 15381)
+// Every other case gains more (512^2 FCH FP64 1565 / 1306).
 template <typename T, int LOGN, int EQ> constexpr bool rows_fused() {
-    return RowsPlan<T, LOGN, EQ>::lds + 1024 <= 163840 && RowsPlan<T, LOGN, EQ>::N >= RowsPlan<T, LOGN, EQ>::RP &&
-           !(EQ == EQ_FCH && LOGN > 10);
+    using Pl = RowsPlan<T, LOGN, EQ>;
+    if (Pl::lds + 1024 > 163840 || Pl::N < Pl::RP) return false;
+    if (Pl::C == 2 && LOGN >= 11) return false;
+    return !(EQ == EQ_FCH && LOGN >= (sizeof(T) == 8 ? 10 : 11));
 }
 
 // ---------------------------------------------------------------- deterministic block sums
