@@ -37,6 +37,14 @@ namespace {
         }                                                                                    \
     } while (0)
 
+#define RD_ALLOC(call)                                                                       \
+    do {                                                                                     \
+        if (!(call)) {                                                                       \
+            if (std::getenv("RD_LOG")) std::fprintf(stderr, "[rd] %s:%d %s\n", __FILE__, __LINE__, #call); \
+            return RD_E_DEVICE;                                                              \
+        }                                                                                    \
+    } while (0)
+
 std::once_flag g_register_once;
 void register_all() {
     register_logn_4();
@@ -277,6 +285,22 @@ void free_workspace(Workspace *w) {
 
 constexpr size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// Device and pinned memory.  A failure is the caller's to report or to make good: the
+// runtime keeps it as the thread's last error, also after later calls that succeed, so it
+// is cleared here, or the check after the next launch would report it.
+template <class P> bool device_alloc(P *&p, size_t bytes) {
+    if (hipMalloc((void **)&p, bytes) == hipSuccess) return true;
+    (void)hipGetLastError();
+    p = nullptr;
+    return false;
+}
+template <class P> bool pinned_alloc(P *&p, size_t bytes) {
+    if (hipHostMalloc((void **)&p, bytes, hipHostMallocDefault) == hipSuccess) return true;
+    (void)hipGetLastError();
+    p = nullptr;
+    return false;
+}
+
 // One device and one pinned allocation per workspace: an allocation costs tens of
 // microseconds, and a served trajectory pays for its workspace before its first step.
 rd_status make_workspace(const Desc &d, int mode, std::unique_ptr<Workspace> &out) {
@@ -295,10 +319,7 @@ rd_status make_workspace(const Desc &d, int mode, std::unique_ptr<Workspace> &ou
     w->bytes = workspace_bytes(d.pts, d.rows, C, mode, k.rows_per_block);
     Slot &s = w->proto;
     std::memset(&s, 0, sizeof(Slot));
-    if (hipMalloc(&w->slab, w->bytes) != hipSuccess) {
-        w->slab = nullptr;
-        return RD_E_NOMEM;
-    }
+    if (!device_alloc(w->slab, w->bytes)) return RD_E_NOMEM;
     size_t off = 0;
     auto take = [&](auto *&ptr, size_t bytes) {
         ptr = (std::remove_reference_t<decltype(ptr)>)((char *)w->slab + off);
@@ -326,8 +347,7 @@ rd_status make_workspace(const Desc &d, int mode, std::unique_ptr<Workspace> &ou
         return RD_E_DEVICE;
     }
     const size_t st_off = align256(sizeof(Slot));
-    if (hipHostMalloc((void **)&w->slot_host, st_off + sizeof(State), hipHostMallocDefault) != hipSuccess) {
-        w->slot_host = nullptr;
+    if (!pinned_alloc(w->slot_host, st_off + sizeof(State))) {
         free_workspace(w.get());
         return RD_E_NOMEM;
     }
@@ -406,9 +426,9 @@ double *take_state(Ctx *c, size_t bytes) {
         return u;
     }
     double *u = nullptr;
-    if (hipMalloc((void **)&u, bytes) == hipSuccess) return u;
+    if (device_alloc(u, bytes)) return u;
     trim_spares(c, 0);
-    return hipMalloc((void **)&u, bytes) == hipSuccess ? u : nullptr;
+    return device_alloc(u, bytes) ? u : nullptr;
 }
 
 void give_state(Ctx *c, double *u, size_t bytes) {
@@ -449,11 +469,11 @@ rd_status get_tables(Ctx *c, int N, int bc, double h, Tables *&out) {
     fill_tables_host(N, bc, h, eig.data(), tw.data(), twd.data());
     std::vector<float> tw32(tw.begin(), tw.end()), twd32(twd.begin(), twd.end());
     Tables t;
-    RD_CHECK(hipMalloc((void **)&t.eig, N * sizeof(double)));
-    RD_CHECK(hipMalloc(&t.tw[0], 2 * N * sizeof(double)));
-    RD_CHECK(hipMalloc(&t.twd[0], 2 * N * sizeof(double)));
-    RD_CHECK(hipMalloc(&t.tw[1], 2 * N * sizeof(float)));
-    RD_CHECK(hipMalloc(&t.twd[1], 2 * N * sizeof(float)));
+    RD_ALLOC(device_alloc(t.eig, N * sizeof(double)));
+    RD_ALLOC(device_alloc(t.tw[0], 2 * N * sizeof(double)));
+    RD_ALLOC(device_alloc(t.twd[0], 2 * N * sizeof(double)));
+    RD_ALLOC(device_alloc(t.tw[1], 2 * N * sizeof(float)));
+    RD_ALLOC(device_alloc(t.twd[1], 2 * N * sizeof(float)));
     RD_CHECK(hipMemcpy(t.eig, eig.data(), N * sizeof(double), hipMemcpyHostToDevice));
     RD_CHECK(hipMemcpy(t.tw[0], tw.data(), 2 * N * sizeof(double), hipMemcpyHostToDevice));
     RD_CHECK(hipMemcpy(t.twd[0], twd.data(), 2 * N * sizeof(double), hipMemcpyHostToDevice));
@@ -741,8 +761,7 @@ rd_status rd_create(int device, rd_ctx **out) {
     if (r != RD_OK) return r;
     auto *c = new Ctx();
     c->device = device;
-    if (hipMalloc((void **)&c->scratch_slot_dev, sizeof(Slot)) != hipSuccess ||
-        hipHostMalloc((void **)&c->scratch_slot_host, sizeof(Slot), hipHostMallocDefault) != hipSuccess) {
+    if (!device_alloc(c->scratch_slot_dev, sizeof(Slot)) || !pinned_alloc(c->scratch_slot_host, sizeof(Slot))) {
         if (c->scratch_slot_dev) (void)hipFree(c->scratch_slot_dev);
         delete c;
         return RD_E_NOMEM;
@@ -1113,7 +1132,7 @@ rd_status rd_advance(rd_ctx *ctx, const rd_problem *prob, const rd_opts *opts, c
     hipStream_t st = (hipStream_t)hip_stream;
     const size_t fb = field_bytes(d.pts, d.C, 8);
     double *next = nullptr;
-    if (hipMalloc((void **)&next, fb) != hipSuccess) return RD_E_NOMEM;
+    if (!device_alloc(next, fb)) return RD_E_NOMEM;
     std::memset(info, 0, sizeof(*info));
     double t = t0, ht = a->ht0;
     int rejects = 0, n = 0;
@@ -1185,7 +1204,7 @@ rd_status rd_residual(rd_ctx *ctx, const rd_problem *prob, double h_t, const dou
         if (c->scratch_partials) (void)hipFree(c->scratch_partials);
         c->scratch_partials = nullptr;
         c->scratch_partials_n = 0;
-        RD_CHECK(hipMalloc((void **)&c->scratch_partials, need * sizeof(double)));
+        RD_ALLOC(device_alloc(c->scratch_partials, need * sizeof(double)));
         c->scratch_partials_n = need;
     }
     RD_CHECK(hipMemcpyAsync(c->scratch_slot_dev, &s, sizeof(Slot), hipMemcpyHostToDevice, st));
@@ -1355,8 +1374,8 @@ rd_status batch_list(Ctx *c, const GroupKey &key, int role, const std::vector<Tr
         b.host = nullptr;
         b.cap = 0;
         const int cap = std::max(16, 2 * n);
-        RD_CHECK(hipMalloc((void **)&b.dev, cap * sizeof(Slot *)));
-        RD_CHECK(hipHostMalloc((void **)&b.host, cap * sizeof(Slot *), hipHostMallocDefault));
+        RD_ALLOC(device_alloc(b.dev, cap * sizeof(Slot *)));
+        RD_ALLOC(pinned_alloc(b.host, cap * sizeof(Slot *)));
         b.cap = cap;
     }
     for (int i = 0; i < n; ++i) b.host[i] = ts[i]->ws->slot_dev;
