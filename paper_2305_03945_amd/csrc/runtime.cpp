@@ -285,25 +285,61 @@ void free_workspace(Workspace *w) {
 
 constexpr size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Device and pinned memory.  A failure is the caller's to report or to make good: the
-// runtime keeps it as the thread's last error, also after later calls that succeed, so it
-// is cleared here, or the check after the next launch would report it.
-template <class P> bool device_alloc(P *&p, size_t bytes) {
-    if (hipMalloc((void **)&p, bytes) == hipSuccess) return true;
+// ---------------------------------------------------------------- spare memory of closed trajectories
+// Short-lived trajectories come and go in a serving stream; a context keeps the
+// workspaces and resident states of closed ones for later ones of the same shape, up to
+// SPARE_LIMIT bytes (with a budget, only what the budget leaves beside the admitted
+// workspaces), and gives them back when an allocation of its own would fail and when it
+// is destroyed.
+// Whoever gives memory here has waited for the work that used it.
+constexpr size_t SPARE_LIMIT = (size_t)256 << 20;
+
+void trim_spares(Ctx *c, size_t limit) {
+    while (c->spare_bytes > limit && !c->spare_ws.empty()) {
+        Workspace *w = c->spare_ws.front().get();
+        c->spare_bytes -= w->bytes;
+        free_workspace(w);
+        c->spare_ws.erase(c->spare_ws.begin());
+    }
+    while (c->spare_bytes > limit && !c->spare_states.empty()) {
+        c->spare_bytes -= c->spare_states.front().first;
+        (void)hipFree(c->spare_states.front().second);
+        c->spare_states.erase(c->spare_states.begin());
+    }
+}
+
+size_t spare_limit(const Ctx *c) {
+    if (!c->budget) return SPARE_LIMIT;
+    return std::min(SPARE_LIMIT, c->budget > c->resident ? c->budget - c->resident : 0);
+}
+
+// Device and pinned memory of a context: where there is none left, the spares go first.
+// A failure is the caller's to report or to make good: the runtime keeps it as the
+// thread's last error, also after later calls that succeed, so it is cleared here, or
+// the check after the next launch would report it.
+template <class Alloc> bool alloc_or_trim(Ctx *c, Alloc alloc) {
+    if (alloc() == hipSuccess) return true;
     (void)hipGetLastError();
+    if (c->spare_ws.empty() && c->spare_states.empty()) return false;
+    trim_spares(c, 0);
+    if (alloc() == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
+}
+template <class P> bool device_alloc(Ctx *c, P *&p, size_t bytes) {
+    if (alloc_or_trim(c, [&] { return hipMalloc((void **)&p, bytes); })) return true;
     p = nullptr;
     return false;
 }
-template <class P> bool pinned_alloc(P *&p, size_t bytes) {
-    if (hipHostMalloc((void **)&p, bytes, hipHostMallocDefault) == hipSuccess) return true;
-    (void)hipGetLastError();
+template <class P> bool pinned_alloc(Ctx *c, P *&p, size_t bytes) {
+    if (alloc_or_trim(c, [&] { return hipHostMalloc((void **)&p, bytes, hipHostMallocDefault); })) return true;
     p = nullptr;
     return false;
 }
 
 // One device and one pinned allocation per workspace: an allocation costs tens of
 // microseconds, and a served trajectory pays for its workspace before its first step.
-rd_status make_workspace(const Desc &d, int mode, std::unique_ptr<Workspace> &out) {
+rd_status make_workspace(Ctx *c, const Desc &d, int mode, std::unique_ptr<Workspace> &out) {
     auto w = std::make_unique<Workspace>();
     const int C = d.C;
     const size_t N = d.pts;   // the field sizes below are per point
@@ -319,7 +355,7 @@ rd_status make_workspace(const Desc &d, int mode, std::unique_ptr<Workspace> &ou
     w->bytes = workspace_bytes(d.pts, d.rows, C, mode, k.rows_per_block);
     Slot &s = w->proto;
     std::memset(&s, 0, sizeof(Slot));
-    if (!device_alloc(w->slab, w->bytes)) return RD_E_NOMEM;
+    if (!device_alloc(c, w->slab, w->bytes)) return RD_E_NOMEM;
     size_t off = 0;
     auto take = [&](auto *&ptr, size_t bytes) {
         ptr = (std::remove_reference_t<decltype(ptr)>)((char *)w->slab + off);
@@ -347,7 +383,7 @@ rd_status make_workspace(const Desc &d, int mode, std::unique_ptr<Workspace> &ou
         return RD_E_DEVICE;
     }
     const size_t st_off = align256(sizeof(Slot));
-    if (!pinned_alloc(w->slot_host, st_off + sizeof(State))) {
+    if (!pinned_alloc(c, w->slot_host, st_off + sizeof(State))) {
         free_workspace(w.get());
         return RD_E_NOMEM;
     }
@@ -359,33 +395,6 @@ rd_status make_workspace(const Desc &d, int mode, std::unique_ptr<Workspace> &ou
     }
     out = std::move(w);
     return RD_OK;
-}
-
-// ---------------------------------------------------------------- spare memory of closed trajectories
-// Short-lived trajectories come and go in a serving stream; a context keeps the
-// workspaces and resident states of closed ones for later ones of the same shape, up to
-// SPARE_LIMIT bytes (with a budget, only what the budget leaves beside the admitted
-// workspaces), and gives them back when memory runs short and when it is destroyed.
-// Whoever gives memory here has waited for the work that used it.
-constexpr size_t SPARE_LIMIT = (size_t)256 << 20;
-
-void trim_spares(Ctx *c, size_t limit) {
-    while (c->spare_bytes > limit && !c->spare_ws.empty()) {
-        Workspace *w = c->spare_ws.front().get();
-        c->spare_bytes -= w->bytes;
-        free_workspace(w);
-        c->spare_ws.erase(c->spare_ws.begin());
-    }
-    while (c->spare_bytes > limit && !c->spare_states.empty()) {
-        c->spare_bytes -= c->spare_states.front().first;
-        (void)hipFree(c->spare_states.front().second);
-        c->spare_states.erase(c->spare_states.begin());
-    }
-}
-
-size_t spare_limit(const Ctx *c) {
-    if (!c->budget) return SPARE_LIMIT;
-    return std::min(SPARE_LIMIT, c->budget > c->resident ? c->budget - c->resident : 0);
 }
 
 rd_status take_workspace(Ctx *c, const Desc &d, int mode, std::unique_ptr<Workspace> &out) {
@@ -400,12 +409,7 @@ rd_status take_workspace(Ctx *c, const Desc &d, int mode, std::unique_ptr<Worksp
         c->spare_ws.erase(it);
         return RD_OK;
     }
-    rd_status r = make_workspace(d, mode, out);
-    if (r == RD_E_NOMEM && c->spare_bytes > 0) {
-        trim_spares(c, 0);
-        r = make_workspace(d, mode, out);
-    }
-    return r;
+    return make_workspace(c, d, mode, out);
 }
 
 void give_workspace(Ctx *c, std::unique_ptr<Workspace> w) {
@@ -426,9 +430,7 @@ double *take_state(Ctx *c, size_t bytes) {
         return u;
     }
     double *u = nullptr;
-    if (device_alloc(u, bytes)) return u;
-    trim_spares(c, 0);
-    return device_alloc(u, bytes) ? u : nullptr;
+    return device_alloc(c, u, bytes) ? u : nullptr;
 }
 
 void give_state(Ctx *c, double *u, size_t bytes) {
@@ -469,11 +471,11 @@ rd_status get_tables(Ctx *c, int N, int bc, double h, Tables *&out) {
     fill_tables_host(N, bc, h, eig.data(), tw.data(), twd.data());
     std::vector<float> tw32(tw.begin(), tw.end()), twd32(twd.begin(), twd.end());
     Tables t;
-    RD_ALLOC(device_alloc(t.eig, N * sizeof(double)));
-    RD_ALLOC(device_alloc(t.tw[0], 2 * N * sizeof(double)));
-    RD_ALLOC(device_alloc(t.twd[0], 2 * N * sizeof(double)));
-    RD_ALLOC(device_alloc(t.tw[1], 2 * N * sizeof(float)));
-    RD_ALLOC(device_alloc(t.twd[1], 2 * N * sizeof(float)));
+    RD_ALLOC(device_alloc(c, t.eig, N * sizeof(double)));
+    RD_ALLOC(device_alloc(c, t.tw[0], 2 * N * sizeof(double)));
+    RD_ALLOC(device_alloc(c, t.twd[0], 2 * N * sizeof(double)));
+    RD_ALLOC(device_alloc(c, t.tw[1], 2 * N * sizeof(float)));
+    RD_ALLOC(device_alloc(c, t.twd[1], 2 * N * sizeof(float)));
     RD_CHECK(hipMemcpy(t.eig, eig.data(), N * sizeof(double), hipMemcpyHostToDevice));
     RD_CHECK(hipMemcpy(t.tw[0], tw.data(), 2 * N * sizeof(double), hipMemcpyHostToDevice));
     RD_CHECK(hipMemcpy(t.twd[0], twd.data(), 2 * N * sizeof(double), hipMemcpyHostToDevice));
@@ -628,7 +630,7 @@ rd_status get_step_workspace(Ctx *c, const Desc &d, int mode, Workspace *&out) {
         return RD_OK;
     }
     std::unique_ptr<Workspace> w;
-    rd_status r = make_workspace(d, mode, w);
+    rd_status r = make_workspace(c, d, mode, w);
     if (r != RD_OK) return r;
     out = w.get();
     c->step_ws[key] = std::move(w);
@@ -761,7 +763,7 @@ rd_status rd_create(int device, rd_ctx **out) {
     if (r != RD_OK) return r;
     auto *c = new Ctx();
     c->device = device;
-    if (!device_alloc(c->scratch_slot_dev, sizeof(Slot)) || !pinned_alloc(c->scratch_slot_host, sizeof(Slot))) {
+    if (!device_alloc(c, c->scratch_slot_dev, sizeof(Slot)) || !pinned_alloc(c, c->scratch_slot_host, sizeof(Slot))) {
         if (c->scratch_slot_dev) (void)hipFree(c->scratch_slot_dev);
         delete c;
         return RD_E_NOMEM;
@@ -1132,7 +1134,7 @@ rd_status rd_advance(rd_ctx *ctx, const rd_problem *prob, const rd_opts *opts, c
     hipStream_t st = (hipStream_t)hip_stream;
     const size_t fb = field_bytes(d.pts, d.C, 8);
     double *next = nullptr;
-    if (!device_alloc(next, fb)) return RD_E_NOMEM;
+    if (!device_alloc(c, next, fb)) return RD_E_NOMEM;
     std::memset(info, 0, sizeof(*info));
     double t = t0, ht = a->ht0;
     int rejects = 0, n = 0;
@@ -1204,7 +1206,7 @@ rd_status rd_residual(rd_ctx *ctx, const rd_problem *prob, double h_t, const dou
         if (c->scratch_partials) (void)hipFree(c->scratch_partials);
         c->scratch_partials = nullptr;
         c->scratch_partials_n = 0;
-        RD_ALLOC(device_alloc(c->scratch_partials, need * sizeof(double)));
+        RD_ALLOC(device_alloc(c, c->scratch_partials, need * sizeof(double)));
         c->scratch_partials_n = need;
     }
     RD_CHECK(hipMemcpyAsync(c->scratch_slot_dev, &s, sizeof(Slot), hipMemcpyHostToDevice, st));
@@ -1374,8 +1376,8 @@ rd_status batch_list(Ctx *c, const GroupKey &key, int role, const std::vector<Tr
         b.host = nullptr;
         b.cap = 0;
         const int cap = std::max(16, 2 * n);
-        RD_ALLOC(device_alloc(b.dev, cap * sizeof(Slot *)));
-        RD_ALLOC(pinned_alloc(b.host, cap * sizeof(Slot *)));
+        RD_ALLOC(device_alloc(c, b.dev, cap * sizeof(Slot *)));
+        RD_ALLOC(pinned_alloc(c, b.host, cap * sizeof(Slot *)));
         b.cap = cap;
     }
     for (int i = 0; i < n; ++i) b.host[i] = ts[i]->ws->slot_dev;

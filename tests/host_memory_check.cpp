@@ -65,10 +65,62 @@ void failed_allocations_leave_no_error() {
     rd_destroy(ctx);
 }
 
+// Whatever a context needs memory for, it gets that of its closed trajectories: every call
+// on a device that is full but for it succeeds as it does on an empty one.
+void kept_memory_serves_every_call() {
+    for (int call = 0; call < 8; ++call) {
+        rd_ctx *ctx = nullptr;
+        CHECK(rd_create(0, &ctx) == RD_OK);
+        serve_one(ctx, 256);
+        const int N = 128;
+        rd_problem p = ac(N);
+        rd_opts o = opts(1e-3, call == 4 ? RD_FP32_MIXED : RD_FP64);
+        double *u = (double *)std::calloc((size_t)N * N, sizeof(double)), *v = (double *)std::calloc((size_t)N * N, 8);
+        const size_t full = hipmem::used();
+        hipmem::capacity() = full;
+        rd_info info;
+        if (call == 0 || call == 4) {
+            CHECK(rd_step(ctx, &p, &o, 0.01, u, u, nullptr, &info) == RD_OK);
+        } else if (call == 1) {
+            rd_adapt a{};
+            a.ht0 = 0.02;
+            a.eta = 0.5;
+            a.n_hi = 12;
+            a.n_lo = 4;
+            a.ht_min = 1e-9;
+            a.max_rejects = 5;
+            rd_adapt_info ai;
+            CHECK(rd_advance(ctx, &p, &o, &a, 0.0, 0.1, u, nullptr, &ai, nullptr, nullptr, nullptr, 0) == RD_OK);
+        } else if (call == 2) {
+            CHECK(rd_precond_solve(ctx, &p, 0.01, RD_FP64, u, v, nullptr) == RD_OK);
+        } else if (call == 3) {
+            double res;
+            CHECK(rd_residual(ctx, &p, 0.01, u, v, v, nullptr, &res) == RD_OK);
+        } else if (call == 5) {
+            serve_one(ctx, N);
+        } else if (call == 6) {
+            rd_traj *t = nullptr;
+            CHECK(rd_traj_open(ctx, &p, &o, u, nullptr, &t) == RD_OK);
+        } else {
+            // the same shape again: nothing is given back, nothing new is needed
+            hipmem::failures() = 0;
+            serve_one(ctx, 256);
+            CHECK(hipmem::failures() == 0 && hipmem::used() == full);
+        }
+        CHECK(hipmem::used() <= full && hipmem::last_error() == hipSuccess);
+        hipmem::capacity() = (size_t)1 << 40;
+        std::free(u);
+        std::free(v);
+        rd_destroy(ctx);
+        CHECK(hipmem::used() == 0);
+    }
+}
+
 }  // namespace
 
 int main() {
     failed_allocations_leave_no_error();
+    kept_memory_serves_every_call();
     CHECK(hipmem::used() == 0);
     if (g_fail) {
         std::fprintf(stderr, "%d checks failed\n", g_fail);
