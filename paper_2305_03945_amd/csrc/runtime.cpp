@@ -308,9 +308,10 @@ void trim_spares(Ctx *c, size_t limit) {
     }
 }
 
-size_t spare_limit(const Ctx *c) {
+// Bytes of spares that the budget leaves beside the admitted workspaces and one of `more`.
+size_t spare_limit(const Ctx *c, size_t more = 0) {
     if (!c->budget) return SPARE_LIMIT;
-    return std::min(SPARE_LIMIT, c->budget > c->resident ? c->budget - c->resident : 0);
+    return std::min(SPARE_LIMIT, c->budget > c->resident + more ? c->budget - c->resident - more : 0);
 }
 
 // Device and pinned memory of a context: where there is none left, the spares go first.
@@ -397,7 +398,9 @@ rd_status make_workspace(Ctx *c, const Desc &d, int mode, std::unique_ptr<Worksp
     return RD_OK;
 }
 
-rd_status take_workspace(Ctx *c, const Desc &d, int mode, std::unique_ptr<Workspace> &out) {
+// need: the workspace's bytes.  A new one is allocated after the spares have made room for
+// it in the budget, so that these never hold more than it together.
+rd_status take_workspace(Ctx *c, const Desc &d, int mode, size_t need, std::unique_ptr<Workspace> &out) {
     for (auto it = c->spare_ws.begin(); it != c->spare_ws.end(); ++it) {
         Workspace &w = **it;
         if (w.N != d.N || w.C != d.C || w.mode != mode || w.dim != d.dim) continue;
@@ -409,6 +412,7 @@ rd_status take_workspace(Ctx *c, const Desc &d, int mode, std::unique_ptr<Worksp
         c->spare_ws.erase(it);
         return RD_OK;
     }
+    trim_spares(c, spare_limit(c, need));
     return make_workspace(c, d, mode, out);
 }
 
@@ -1516,12 +1520,11 @@ rd_status rd_serve_pump(rd_ctx *ctx, int32_t max_wait_us) {
                                             kset(t->d.mode, t->d).rows_per_block);
         if (c->budget && c->resident + need > c->budget && c->resident > 0) break;
         std::unique_ptr<Workspace> w;
-        r = take_workspace(c, t->d, t->d.mode, w);
+        r = take_workspace(c, t->d, t->d.mode, need, w);
         if (r == RD_E_NOMEM && c->resident > 0) break;
         if (r != RD_OK) return r;
         t->ws = std::move(w);
         c->resident += need;
-        trim_spares(c, spare_limit(c));
         c->admit_queue.pop_front();
         t->queued_for_admission = false;
     }

@@ -116,9 +116,36 @@ void kept_memory_serves_every_call() {
     }
 }
 
+// With a budget, admitted workspaces and kept memory together never exceed it, also while an
+// admission allocates: served one after another, trajectories of several shapes need at most
+// the budget beside their own states, tables and lists.
+void kept_memory_stays_in_the_budget() {
+    rd_ctx *ctx = nullptr;
+    CHECK(rd_create(0, &ctx) == RD_OK);
+    const int sizes[] = {64, 128, 256};
+    for (int N : sizes) serve_one(ctx, N);   // tables, lists and streams of every size
+    rd_opts o = opts(1e-3, RD_FP64);
+    rd_problem big = ac(256);
+    const size_t budget = rd_footprint_bytes(&big, &o);
+    CHECK(rd_serve_set_budget(ctx, 1) == RD_OK);   // nothing kept
+    const size_t base = hipmem::used();
+    CHECK(rd_serve_set_budget(ctx, budget) == RD_OK);
+    for (int r = 0; r < 12; ++r) {
+        const int N = sizes[(r * 2 + r / 3) % 3];
+        hipmem::peak() = hipmem::used();
+        serve_one(ctx, N);
+        CHECK(hipmem::peak() <= base + budget + (size_t)N * N * sizeof(double));
+        CHECK(hipmem::used() <= base + budget);
+    }
+    // two shapes that fit together are both kept
+    CHECK(hipmem::used() > base);
+    rd_destroy(ctx);
+}
+
 }  // namespace
 
 int main() {
+    kept_memory_stays_in_the_budget();
     failed_allocations_leave_no_error();
     kept_memory_serves_every_call();
     CHECK(hipmem::used() == 0);
