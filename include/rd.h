@@ -298,8 +298,8 @@ rd_status rd_traj_read(rd_traj *traj, double *u_out, void *hip_stream);
  * returns RD_E_INVALID for every ticket of it, finished or not (unfinished steps are
  * dropped).  The context keeps released memory for later trajectories of the same shape,
  * at most 256 MiB and, with a budget, at most what the budget leaves beside the admitted
- * workspaces; any call of the context that finds no other memory takes it, and rd_destroy
- * frees it.                                                                              */
+ * workspaces; any call of the context that finds no other memory takes it, and
+ * rd_serve_set_budget and rd_destroy free it.                                             */
 rd_status rd_traj_close(rd_traj *traj);
 
 typedef struct {

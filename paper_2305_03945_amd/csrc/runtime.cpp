@@ -289,8 +289,8 @@ constexpr size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // Short-lived trajectories come and go in a serving stream; a context keeps the
 // workspaces and resident states of closed ones for later ones of the same shape, up to
 // SPARE_LIMIT bytes (with a budget, only what the budget leaves beside the admitted
-// workspaces), and gives them back when an allocation of its own would fail and when it
-// is destroyed.
+// workspaces), and gives them back when an allocation of its own would fail, when the
+// budget is set and when it is destroyed.
 // Whoever gives memory here has waited for the work that used it.
 constexpr size_t SPARE_LIMIT = (size_t)256 << 20;
 
@@ -1295,7 +1295,7 @@ rd_status rd_serve_set_budget(rd_ctx *ctx, size_t bytes) {
     Ctx *c = (Ctx *)ctx;
     RD_CHECK(hipSetDevice(c->device));
     c->budget = bytes;
-    trim_spares(c, spare_limit(c));
+    trim_spares(c, 0);
     return RD_OK;
 }
 

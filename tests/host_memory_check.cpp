@@ -137,8 +137,12 @@ void kept_memory_stays_in_the_budget() {
         CHECK(hipmem::peak() <= base + budget + (size_t)N * N * sizeof(double));
         CHECK(hipmem::used() <= base + budget);
     }
-    // two shapes that fit together are both kept
-    CHECK(hipmem::used() > base);
+    // some is kept; setting the budget, also to the same or to none, gives it back
+    for (size_t b : {budget, (size_t)0}) {
+        CHECK(hipmem::used() > base);
+        CHECK(rd_serve_set_budget(ctx, b) == RD_OK && hipmem::used() == base);
+        serve_one(ctx, 128);
+    }
     rd_destroy(ctx);
 }
 
