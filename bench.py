@@ -72,14 +72,16 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def launch_ms(ms):
+def launch_ms(ms, N, prec):
     """profile_iteration's durations by launch: a launch that makes several steps has
-    given each of them an equal share (one row launch: "rows"; 3-D plane passes)."""
+    given each of them an equal share (one row launch: "rows"; 3-D plane passes, which
+    only grids up to 64^3 and, for the inverse one, 128^3 mixed have: two launches of
+    their own may well take equally long)."""
     if "zsym" not in ms and ms["rowinv"] == ms["upd"] == ms["rowfwd"]:
         return {"cols": ms["cols"], "rows": 3 * ms["rowinv"]}
-    if "zsym" in ms and ms["yinv"] == ms["rowinv"]:
+    if "zsym" in ms and (N <= 64 or (N == 128 and prec == "mixed")) and ms["yinv"] == ms["rowinv"]:
         out = {"zsym": ms["zsym"], "planeinv": 2 * ms["yinv"], "upd": ms["upd"]}
-        if ms["yfwd"] == ms["rowfwd"]:
+        if N <= 64 and ms["yfwd"] == ms["rowfwd"]:
             return dict(out, planefwd=2 * ms["yfwd"])
         return dict(out, yfwd=ms["yfwd"], rowfwd=ms["rowfwd"])
     return ms
@@ -276,7 +278,7 @@ def config_leg(ctx, rd, torch, wl, name, precs, steps=None, oracle=True):
             # iteration must move per grid point, times the number of species
             p = rd.problem_from_config(cfg)
             o = rd.make_opts(tol=cfg["tol"], tau_u=cfg["tau"], tau_p=cfg["tau"], omega=cfg["omega"], precision=prec)
-            ms = launch_ms(ctx.profile_iteration(u0, cfg["ht"], p, o, reps=20))
+            ms = launch_ms(ctx.profile_iteration(u0, cfg["ht"], p, o, reps=20), cfg["N"], prec)
             it_ms = sum(ms.values())
             b = ALG_BYTES[prec] * ncomp * cfg["N"] ** 2
             out[prec]["iteration"] = dict(kernels_us={k: round(v * 1e3, 2) for k, v in ms.items()},
@@ -397,7 +399,7 @@ def adaptive_leg(ctx, rd, torch, cfg, u0):
 def kernel_table(ctx, rd, cfg, u0, prec, pts, reps=20):
     p = rd.problem_from_config(cfg)
     o = rd.make_opts(tol=cfg["tol"], tau_u=cfg["tau"], tau_p=cfg["tau"], precision=prec)
-    ms = launch_ms(ctx.profile_iteration(u0, cfg["ht"], p, o, reps=reps))
+    ms = launch_ms(ctx.profile_iteration(u0, cfg["ht"], p, o, reps=reps), cfg["N"], prec)
     return {k: dict(ms=t, bytes=BYTES_PER_POINT[prec][k] * pts,
                     gbs=BYTES_PER_POINT[prec][k] * pts / (t * 1e-3) / 1e9) for k, t in ms.items()}
 
@@ -546,7 +548,7 @@ def main():
     p = rd.problem_from_config(cfg)
     for prec in ("fp64", "mixed"):
         o = rd.make_opts(tol=cfg["tol"], tau_u=cfg["tau"], tau_p=cfg["tau"], precision=prec)
-        ms = launch_ms(ctx.profile_iteration(u0, cfg["ht"], p, o, reps=args.reps))
+        ms = launch_ms(ctx.profile_iteration(u0, cfg["ht"], p, o, reps=args.reps), N, prec)
         kernels[prec] = {}
         for k, t in ms.items():
             nbytes = BYTES_PER_POINT[prec][k] * N * N
