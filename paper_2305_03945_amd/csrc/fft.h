@@ -14,10 +14,10 @@
 //    The inverse rebuilds V_k = conj(w_k) (X_k - i X_{N-k}) (X_N = 0) and applies
 //    an inverse FFT.  Two real sequences are again packed into one complex FFT.
 //
-// The complex FFTs themselves are in fft16.h (radix-16 Stockham passes in LDS);
+// The complex FFTs themselves are in fft16.h (Stockham passes in LDS);
 // forward sign -1, both directions unnormalised; the 1/N^2 of the 2-D inverse is
-// folded into the symbol multiplier.  This file holds the small DFT kernels and
-// the pair / cosine pre- and post-processing over padded LDS regions.
+// folded into the symbol multiplier.  This file holds the pair / cosine pre- and
+// post-processing over padded LDS regions and the symbol.
 #pragma once
 #include "rd_dev.h"
 

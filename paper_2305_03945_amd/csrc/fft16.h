@@ -5,8 +5,9 @@
 // writes of a Stockham pass off a single bank group.  Threads of one wave synchronise
 // within it, a transform over several waves by the workgroup's barrier.  Passes are
 // Stockham autosort passes of radix V, then one pass of a smaller radix for the
-// remaining bits; each thread runs V/R butterflies of a radix-R pass.  A butterfly gathers the powers W^{k}, W^{2k}, W^{4k}, W^{8k}
-// of its twiddle and applies them in its radix-2 steps (twiddled_dft).
+// remaining bits; each thread runs V/R butterflies of a radix-R pass.  A butterfly gathers
+// the powers W^{k}, W^{2k}, W^{4k}, W^{8k} of its twiddle and applies them in its radix-2
+// steps (twiddled_dft).
 #pragma once
 #include "fft.h"
 

@@ -957,7 +957,8 @@ __device__ __forceinline__ void row_forward_pass(SlotRef s, StateRef sst, cplx<T
         // complex value (row 2p + i row 2p+1) goes to LDS in one write.  The FP64
         // iteration (2048^2: 27.7 -> 25.2 us), the mixed outer update, and the FP32
         // inner pass at 4096^2, whose one-row windows re-fetch the stencil rows they
-        // share once the rows in flight exceed the L2 (75 -> 71 us); at 2048^2 the
+        // share once the rows in flight exceed the L2 (60 iterations, ms: Cahn-Hilliard
+        // 16.7 -> 15.6, FCH 23.4 -> 21.1, Schnakenberg 28.2 -> 28.1); at 2048^2 the
         // FP32 inner pass measured no gain.
 #pragma unroll 2
         for (int idx = threadIdx.x; idx < (R / 2) * N / 4; idx += NTH) {
@@ -1011,7 +1012,7 @@ __global__ __launch_bounds__(NT) void k_row_forward(Slot *const *slots) {
 
 // ---------------------------------------------------------------- column pass
 // A workgroup takes CB adjacent columns of one component, one transform per
-// N/16 threads.  CB is chosen so that the CB x R block of a spectrum tile it
+// N/V threads (V = col_values).  CB is chosen so that the CB x R block of a spectrum tile it
 // reads is at least 64 bytes (and the workgroup at least one wave), as far as
 // 156 KB of LDS (of the 160 KB a gfx950 workgroup may hold) and 1024 threads allow.
 // Column blocks are mapped to XCDs in contiguous ranges (xcd_tile), so the two
@@ -1066,7 +1067,7 @@ template <typename T, int LOGN, int C> constexpr int col_waves_per_eu() {
 }
 
 // Periodic column pass with the transforms ended in registers (fft16_regs): each
-// thread loads its 16 values of one column straight from S, and the forward
+// thread loads its V values of one column straight from S, and the forward
 // transform's last pass, the symbol and the inverse transform's first pass run
 // on the same registers, so LDS is touched only between passes.  Lanes are laid
 // out so that R*CB consecutive lanes read R consecutive rows of the CB columns
