@@ -23,21 +23,20 @@ namespace rdk {
 // when its 15 twiddles are formed and applied first.
 //
 // The rounding error is to be no larger than with twiddles formed and applied first.  G^-1
-// at 512^2 against 80-bit transforms: 4.3e-16 (FP64) and 2.5e-7 (FP32), 4.5e-16 and 2.7e-7
+// at 512^2 against 80-bit transforms: 4.3e-16 (FP64) and 2.4e-7 (FP32), 4.5e-16 and 2.7e-7
 // that way, 5.2e-16 and 2.8e-7 with the cheaper butterfly of the next lines, against which
-// this one costs 2 % of a step (2048^2 1240 -> 1268 us mixed, 2640 -> 2702 FP64).  Of a
+// this one costs 2 % of a step (2048^2 1246 -> 1276 us mixed, 2608 -> 2673 FP64).  Of a
 // 512-point FP64 transform and its inverse, in units of the rounding (FP32): 2.57 (2.80)
-// that way; 2.45 (2.56) this with 8 values per thread, 2.45 (2.70) with 16.  What was
+// that way; 2.51 (2.59) this with 8 values per thread, 2.45 (2.65) with 16.  What was
 // found to cost accuracy:
 //  - V_{q+R/2} as 2 E_q - V_q, which saves two operations but takes over V_q's rounding
 //    (one transform: 2.01 against 1.80 formed first);
-//  - w W_8 as a product, which puts the error of the rounded sqrt(1/2) into every value
-//    with the same sign (2.60, 16 values).  It is gathered (tw_has_w8) but for FP32
-//    transforms of 2048 points by 16 values, whose kernels have no register left (3.13,
-//    formed first 3.19);
+//  - w W_8 by the rounded sqrt(1/2), whose error goes into every value with the same sign
+//    (2.60, 16 values; turn8 adds its lower part);
 //  - radix-2 steps down to two points on short transforms, whose error is small (32
 //    points, 8 values: 1.69, formed first 1.65).  Up to 64 points the DFTs of four multiply
-//    their twiddles in first (1.61); above, the third twiddle would cost registers.
+//    their twiddles in first and w W_8 is gathered (1.61); above, the two twiddles more
+//    would cost registers.
 template <typename T> __device__ __forceinline__ T fma_(T a, T b, T c) { return __builtin_elementwise_fma(a, b, c); }
 
 // exp(DIR 2 pi i m / 16), m = 1, 2, 3
@@ -46,6 +45,14 @@ template <typename T, int DIR, int M> __device__ __forceinline__ cplx<T> root16(
     constexpr T c[4] = {(T)1, (T)0.923879532511286756128183189396788934, (T)0.707106781186547524400844362104849039,
                         (T)0.382683432365089771728459984030398867};
     return {c[M], (T)DIR * c[4 - M]};
+}
+
+// w exp(DIR 2 pi i / 8), with sqrt(1/2) in two parts.
+template <typename T, int DIR> __device__ __forceinline__ cplx<T> turn8(cplx<T> w) {
+    constexpr T hi = (T)0.707106781186547524400844362104849039;
+    constexpr T lo = (T)(sizeof(T) == 8 ? -4.83364665672645651859e-17 : 1.21016171044788e-08);
+    const cplx<T> c = cadd(w, rot90<T, DIR>(w));
+    return {fma_(hi, c.re, lo * c.re), fma_(hi, c.im, lo * c.im)};
 }
 
 // a + t b and a - t b.  QUARTER: t is to be turned by DIR 90 degrees.
@@ -147,11 +154,9 @@ template <typename T, int R, int DIR> __device__ __forceinline__ void dftR(cplx<
 template <int V> constexpr int logv() { return V == 16 ? 4 : V == 8 ? 3 : 2; }
 template <int LOGN> constexpr bool twiddles_first() { return LOGN <= 6; }
 template <int LOGN, int V> constexpr bool tw_has_w3() { return twiddles_first<LOGN>() && V <= 8; }
-template <typename T, int LOGN, int V> constexpr bool tw_has_w8() {
-    return V == 8 || (V == 16 && !(sizeof(T) == 4 && LOGN == 11));
-}
-template <typename T, int LOGN, int V> constexpr int tw_count() {
-    return logv<V>() + (tw_has_w3<LOGN, V>() ? 1 : 0) + (tw_has_w8<T, LOGN, V>() ? 1 : 0);
+template <int LOGN, int V> constexpr bool tw_has_w8() { return twiddles_first<LOGN>() && V == 8; }
+template <int LOGN, int V> constexpr int tw_count() {
+    return logv<V>() + (tw_has_w3<LOGN, V>() ? 1 : 0) + (tw_has_w8<LOGN, V>() ? 1 : 0);
 }
 
 // Gather a radix-R butterfly's twiddles: w = W_N^i, table tw of W_N (forward sign).
@@ -163,7 +168,7 @@ __device__ __forceinline__ void gather_twiddles(cplx<T> *p, TAB tw, int i) {
     for (int e = 0; e < logv<V>(); ++e)
         if ((1 << e) < R) p[e] = at(i << e);
     if constexpr (tw_has_w3<LOGN, V>() && R >= 4) p[logv<V>()] = at(i * (3 * R / 4));
-    if constexpr (tw_has_w8<T, LOGN, V>() && R >= 8) p[tw_count<T, LOGN, V>() - 1] = at(i * (R / 8) + N / 8);
+    if constexpr (tw_has_w8<LOGN, V>() && R >= 8) p[tw_count<LOGN, V>() - 1] = at(i * (R / 8) + N / 8);
 }
 
 // DFT_R of v in place, input r multiplied by w^r first; p: gather_twiddles (forward sign,
@@ -204,8 +209,8 @@ __device__ __forceinline__ void twiddled_dft(cplx<T> *v, const cplx<T> *p) {
             for (int q = 0; q < 4; ++q) v[q] = a[0][q];
         } else {
             cplx<T> t8[2] = {tw(E - 1)};
-            if constexpr (tw_has_w8<T, LOGN, V>()) t8[1] = tw(tw_count<T, LOGN, V>() - 1);
-            else t8[1] = cmul(t8[0], root16<T, DIR, 2>());
+            if constexpr (tw_has_w8<LOGN, V>()) t8[1] = tw(tw_count<LOGN, V>() - 1);
+            else t8[1] = turn8<T, DIR>(t8[0]);
             if constexpr (R == 8) {
                 radix2_step<T, 8, DIR>(a[0], a[1], t8, v);
             } else {
@@ -213,7 +218,7 @@ __device__ __forceinline__ void twiddled_dft(cplx<T> *v, const cplx<T> *p) {
                 radix2_step<T, 8, DIR>(a[0], a[2], t8, e);
                 radix2_step<T, 8, DIR>(a[1], a[3], t8, o);
                 const cplx<T> w = tw(0);
-                const cplx<T> t16[4] = {w, cmul(w, root16<T, DIR, 1>()), cmul(w, root16<T, DIR, 2>()),
+                const cplx<T> t16[4] = {w, cmul(w, root16<T, DIR, 1>()), turn8<T, DIR>(w),
                                         cmul(w, root16<T, DIR, 3>())};
                 radix2_step<T, 16, DIR>(e, o, t16, v);
             }
@@ -235,7 +240,7 @@ template <int LOGN, int V = 16> constexpr int pass_radix(int q) {
 // index in its transform team, so a kernel loads them once, at its start, and
 // every transform (forward and inverse) of the kernel reuses them.
 template <typename T, int LOGN, int V = 16> struct Tw16 {
-    cplx<T> p[npasses16<LOGN, V>() > 1 ? npasses16<LOGN, V>() - 1 : 1][V / 2][tw_count<T, LOGN, V>()];
+    cplx<T> p[npasses16<LOGN, V>() > 1 ? npasses16<LOGN, V>() - 1 : 1][V / 2][tw_count<LOGN, V>()];
 };
 
 template <typename T, int LOGN, int V, int Q = 1>
@@ -269,7 +274,7 @@ template <typename T, int LOGN> struct Region {
 
 // pass_in: the reads, twiddles and butterflies of the thread (outputs in v).
 template <typename T, int LOGN, int R, int NS, int DIR, int V = 16, class X>
-__device__ __forceinline__ void pass_in(X x, int t, const cplx<T> (*pw)[tw_count<T, LOGN, V>()], cplx<T> (*v)[R]) {
+__device__ __forceinline__ void pass_in(X x, int t, const cplx<T> (*pw)[tw_count<LOGN, V>()], cplx<T> (*v)[R]) {
     constexpr int N = 1 << LOGN;
     constexpr int TPF = N / V;       // threads per transform
     constexpr int NB = N / R;        // butterflies
@@ -311,7 +316,7 @@ template <bool WAVE> __device__ __forceinline__ void pass_sync() {
 }
 
 template <typename T, int LOGN, int R, int NS, int DIR, int V = 16, bool WAVE = false, class X>
-__device__ __forceinline__ void pass16(X x, int t, bool active, const cplx<T> (*pw)[tw_count<T, LOGN, V>()]) {
+__device__ __forceinline__ void pass16(X x, int t, bool active, const cplx<T> (*pw)[tw_count<LOGN, V>()]) {
     cplx<T> v[V / R][R];
     if (active) pass_in<T, LOGN, R, NS, DIR, V>(x, t, pw, v);
     pass_sync<WAVE>();

@@ -92,7 +92,7 @@ template <int LOGN> constexpr int r8_passes() { return (LOGN + 2) / 3; }
 template <typename T, int LOGN> struct TwR8 {
     // pass 1 (the only pass with NS > 1 for N <= 64): butterflies b < 8 / R, powers
     // FP64: gather_twiddles; FP32: the twiddles of inputs 1 .. R - 1
-    cplx<T> w[4][sizeof(T) == 8 ? tw_count<T, LOGN, 8>() : 7];
+    cplx<T> w[4][sizeof(T) == 8 ? tw_count<LOGN, 8>() : 7];
 };
 
 template <typename T, int LOGN>
